@@ -64,8 +64,8 @@ PROFILES = os.path.join(ROOT, "profiles")
 
 # every source that decides what the replay kernel does on the GPU (front
 # end, validator, scheduler, launch code, kernel)
-REPLAY_SOURCES = ("abi.cpp", "common.h", "frontend.cpp", "kernels.hip", "sched.cpp", "sched.h", "slot.h",
-                  "slot_exec.h", "tape.cpp")
+REPLAY_SOURCES = ("abi.cpp", "common.h", "frontend.cpp", "kernels.hip", "plan.h", "sched.cpp", "sched.h", "slot.h",
+                  "slot_exec.h", "tape.cpp", "wide.h", "wide.hip", "wide_exec.h", "wide_sched.cpp")
 
 
 def kernel_sources_sha256() -> str:

@@ -20,8 +20,9 @@ BUILD = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["frontend.cpp", "tape.cpp", "sched.cpp", "abi.cpp", "kernels.hip", "optim.hip", "walk_host.cpp", "walk.hip"]
-EMU_SOURCES = ["frontend.cpp", "tape.cpp", "sched.cpp", "emu.cpp"]
+SOURCES = ["frontend.cpp", "tape.cpp", "sched.cpp", "wide_sched.cpp", "abi.cpp", "kernels.hip", "wide.hip", "optim.hip",
+           "walk_host.cpp", "walk.hip"]
+EMU_SOURCES = ["frontend.cpp", "tape.cpp", "sched.cpp", "wide_sched.cpp", "emu.cpp"]
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-ffp-contract=off", "-fno-fast-math", "-Wall",
           "-Wno-unused-function"]
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -37,12 +38,16 @@ REPLAY = [
     "-mllvm", "-sink-common-insts=false", "-mllvm", "-enable-tail-merge=false"]
 # sources built with the replay kernel's options (the device walker is not:
 # with its loops the first option makes the code generator fail)
-REPLAY_OPTIONS_FOR = {"frontend.cpp", "tape.cpp", "sched.cpp", "abi.cpp", "kernels.hip", "optim.hip", "emu.cpp"}
+REPLAY_OPTIONS_FOR = {"wide_sched.cpp", "frontend.cpp", "tape.cpp", "sched.cpp", "abi.cpp", "kernels.hip", "optim.hip", "emu.cpp"}
+
+# The wide kernel: the library functions' branches on wave-uniform values stay
+# branches; the registers its inline asm names are not the compiler's.
+WIDE = ["-mllvm", "-structurizecfg-skip-uniform-regions=true", "-Wno-inline-asm"]
 
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    extra = REPLAY if src in REPLAY_OPTIONS_FOR else []
+    extra = REPLAY if src in REPLAY_OPTIONS_FOR else WIDE if src == "wide.hip" else []
     cmd = [HIPCC] + COMMON + DEVICE + extra + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"

@@ -12,17 +12,21 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <set>
 #include <thread>
 #include <new>
 
 #include "common.h"
 #include "slot.h"
 #include "sched.h"
+#include "wide.h"
 
 namespace ndvm {
 hipError_t launch_replay(const LaunchArgs &A, const ProgStatic *d_table, const ProgStatic &single, uint32_t n_prog,
                          uint32_t r_lds, int variant, bool skips, int order, uint32_t slots,
                          hipStream_t stream);
+hipError_t launch_wide(const LaunchArgs &A, const wide::Prog *d_table, const wide::Prog &single, uint32_t n_prog,
+                       hipStream_t stream);
 bool slots_supported(uint32_t S);
 size_t scratch_bytes();
 hipError_t launch_fold_points(const double *term, const double *tgrad, int64_t L, int64_t N, int64_t P,
@@ -112,6 +116,16 @@ struct DevProg {
     }
 };
 
+// A program of the wide kernel; it does not depend on the lane count.
+struct WideProg {
+    WideSchedule meta;      // host copy of counts (code and constants released)
+    void *buf = nullptr;    // device: code | constants
+    wide::Prog prog{};
+    ~WideProg() {
+        if (buf) (void)hipFree(buf);
+    }
+};
+
 std::atomic<uint64_t> g_next_id{1};
 
 }  // namespace
@@ -126,6 +140,10 @@ struct ndvm_tape {
     std::mutex mu;
     std::map<uint32_t, std::unique_ptr<DevProg>> fwd;    // keyed by slot count
     std::map<uint64_t, std::unique_ptr<DevProg>> grad;   // keyed by (slot count, register budget)
+    // programs of the wide kernel, null where it does not take the tape
+    std::unique_ptr<WideProg> wide_fwd, wide_grad;
+    bool wide_grad_tried = false;
+    std::set<uint32_t> sized;   // register budgets of the lane counts sized for gradients
 };
 
 namespace {
@@ -166,6 +184,76 @@ ndvm_status upload_program(Schedule &&S, const Tape &t, hipStream_t stream, std:
     dp->meta = std::move(S);
     *out = std::move(dp);
     (void)t;
+    return NDVM_OK;
+}
+
+// The wide kernel takes scalar programs without skippable branch arms whose
+// live values fit its register file; the slot kernel takes the others (its
+// slots hold matrices and spill, and it has the skip tests that a tape with
+// branches uploaded with NDVM_BRANCH_SKIP asks for).  Both give the same bits.
+// Slot kernel against wide kernel, ms a call: Lotka-Volterra (1000 steps,
+// 65,536 lanes) 7.36 against 3.46, saving (300 steps, 9,999 lanes) 5.75
+// against 1.23, losses alone (20,000 lanes) 7.91 against 0.65; logistic (500
+// steps, 4,096 lanes) 0.917 against 0.678; exponential decay (64 points, 256
+// lanes) 0.0558 against 0.0490; 1,024 random programs of 1,024 lanes 17.7
+// against 4.74.
+bool wide_candidate(const ndvm_tape *t) { return !(t->arms && t->n_selects > 0); }
+
+// Wide schedule of a tape, or one that is not ok.
+WideSchedule wide_schedule_of(const ndvm_tape *t, bool with_grad) {
+    if (!wide_candidate(t)) return WideSchedule{};
+    return schedule_wide(t->tape, with_grad, t->policy == NDVM_POLICY_SAVE);
+}
+
+// Copy a wide program to the device (S.ok).
+ndvm_status upload_wide(WideSchedule &&S, const Tape &t, bool with_grad, hipStream_t stream,
+                        std::unique_ptr<WideProg> *out) {
+    auto w = std::make_unique<WideProg>();
+    const size_t code_b = S.code.size() * 4, con_off = (code_b + 255) / 256 * 256;
+    const size_t total = con_off + std::max<size_t>(S.consts.size(), 1) * 8;
+    if (hipMalloc(&w->buf, total) != hipSuccess) {
+        (void)hipGetLastError();
+        w->buf = nullptr;
+        set_error("hipMalloc of the device program failed");
+        return NDVM_E_NOMEM;
+    }
+    std::vector<uint8_t> host(total, 0);
+    std::memcpy(host.data(), S.code.data(), code_b);
+    if (!S.consts.empty()) std::memcpy(host.data() + con_off, S.consts.data(), S.consts.size() * 8);
+    if (hipMemcpyAsync(w->buf, host.data(), total, hipMemcpyHostToDevice, stream) != hipSuccess ||
+        hipStreamSynchronize(stream) != hipSuccess) {
+        set_error("copy of the device program failed");
+        return NDVM_E_DEVICE;
+    }
+    w->prog.code = reinterpret_cast<const uint32_t *>(w->buf);
+    w->prog.consts = reinterpret_cast<const double *>(static_cast<uint8_t *>(w->buf) + con_off);
+    w->prog.ckpt_row0 = 0;
+    w->prog.trash_row = S.n_ckpt_rows;
+    std::memcpy(w->prog.first, S.first, sizeof w->prog.first);
+    w->prog.n_params = t.n_params;
+    w->prog.n_consts = uint32_t(S.consts.size());
+    w->prog.adjoints = with_grad;
+    S.code = {};
+    S.consts = {};
+    w->meta = std::move(S);
+    *out = std::move(w);
+    return NDVM_OK;
+}
+
+// Wide gradient program of a tape (null: the slot kernel runs it), made and
+// copied at its first sizing call.  `pre`: the schedule, when the caller made
+// it already.
+ndvm_status wide_grad_program(ndvm_tape *tape, bool build, WideProg **out, WideSchedule *pre = nullptr) {
+    std::lock_guard<std::mutex> lk(tape->mu);
+    if (!tape->wide_grad_tried && build) {
+        WideSchedule S = pre ? std::move(*pre) : wide_schedule_of(tape, true);
+        if (S.ok) {
+            ndvm_status st = upload_wide(std::move(S), tape->tape, true, nullptr, &tape->wide_grad);
+            if (st != NDVM_OK) return st;
+        }
+        tape->wide_grad_tried = true;
+    }
+    *out = tape->wide_grad.get();
     return NDVM_OK;
 }
 
@@ -220,6 +308,34 @@ ndvm_status grad_program(ndvm_tape *tape, uint32_t S, uint32_t b, bool build, De
     return NDVM_OK;
 }
 
+// f(0) .. f(n - 1) on all host threads; what f throws becomes the status and
+// message of its index.
+template <class F>
+void for_all(size_t n, F f, std::vector<ndvm_status> *code, std::vector<std::string> *msg) {
+    std::atomic<size_t> next{0};
+    auto work = [&]() {
+        for (size_t i; (i = next.fetch_add(1)) < n;) {
+            try {
+                f(i);
+            } catch (const std::length_error &e) {
+                (*code)[i] = NDVM_E_UNSUPPORTED;
+                (*msg)[i] = std::string("program too large for the device format: ") + e.what();
+            } catch (const std::bad_alloc &) {
+                (*code)[i] = NDVM_E_NOMEM;
+                (*msg)[i] = "out of host memory";
+            } catch (const std::exception &e) {
+                (*code)[i] = NDVM_E_INTERNAL;
+                (*msg)[i] = std::string("internal error: ") + e.what();
+            }
+        }
+    };
+    const size_t n_threads = std::min<size_t>(n, std::max(1u, std::thread::hardware_concurrency()));
+    std::vector<std::thread> pool;
+    for (size_t k = 1; k < n_threads; ++k) pool.emplace_back(work);
+    if (n) work();
+    for (auto &th : pool) th.join();
+}
+
 // Schedules of the programs among `tapes` that have no device program for
 // (S, b) yet, made on all host threads (each program's schedule is
 // independent of the others); the uploads stay with the caller.  On a
@@ -240,28 +356,7 @@ ndvm_status schedule_many(const ndvm_tape *const *tapes, int n_prog, uint32_t S,
     std::vector<Schedule> res(todo.size());
     std::vector<ndvm_status> code(todo.size(), NDVM_OK);
     std::vector<std::string> msg(todo.size());
-    std::atomic<size_t> next{0};
-    auto work = [&]() {
-        for (size_t i; (i = next.fetch_add(1)) < todo.size();) {
-            try {
-                res[i] = schedule_grad_of(todo[i], S, b);
-            } catch (const std::length_error &e) {
-                code[i] = NDVM_E_UNSUPPORTED;
-                msg[i] = std::string("program too large for the device format: ") + e.what();
-            } catch (const std::bad_alloc &) {
-                code[i] = NDVM_E_NOMEM;
-                msg[i] = "out of host memory";
-            } catch (const std::exception &e) {
-                code[i] = NDVM_E_INTERNAL;
-                msg[i] = std::string("internal error: ") + e.what();
-            }
-        }
-    };
-    const size_t n_threads = std::min<size_t>(todo.size(), std::max(1u, std::thread::hardware_concurrency()));
-    std::vector<std::thread> pool;
-    for (size_t k = 1; k < n_threads; ++k) pool.emplace_back(work);
-    work();
-    for (auto &th : pool) th.join();
+    for_all(todo.size(), [&](size_t i) { res[i] = schedule_grad_of(todo[i], S, b); }, &code, &msg);
     for (size_t i = 0; i < todo.size(); ++i) {
         if (code[i] != NDVM_OK) {
             set_error(msg[i]);
@@ -331,6 +426,50 @@ ndvm_status fwd_program(ndvm_tape *tape, uint32_t S, hipStream_t stream, DevProg
 
 int64_t lpad_of(int64_t L) { return (L + 63) / 64 * 64; }
 
+// Largest padded lane count of a wide launch (a row's bytes are a 32-bit
+// number there).
+constexpr int64_t kWideMaxLanes = (int64_t(1) << 29) - 64;
+// A wide launch of one wave must fit the static scratch array by itself, so
+// that any launch the array serves can be served in parts.
+bool wide_rows_fit(const WideProg &w) {
+    return (uint64_t(w.meta.n_ckpt_rows) + slot::kMaxBlock) * 64 * sizeof(double) <= scratch_bytes();
+}
+// Workspace rows of a wide program (the slot kernel's trash rows included, so
+// that no launch has an empty workspace).
+uint64_t wide_rows(const WideProg &w) { return uint64_t(w.meta.n_ckpt_rows) + slot::kMaxBlock; }
+
+// The wide program of a gradient launch over L lanes, or null.  As for the
+// slot kernel's programs, a compute call needs a sizing call before it whose
+// lane count gives the same register budget.
+ndvm_status wide_grad_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, int64_t n_prog, bool build,
+                          WideProg **out) {
+    *out = nullptr;
+    if (lpad_of(L) > kWideMaxLanes) return NDVM_OK;
+    WideProg *w = nullptr;
+    ndvm_status st = wide_grad_program(tape, build, &w);
+    if (st != NDVM_OK || !w || !wide_rows_fit(*w)) return st;
+    const uint32_t b = reg_budget(p, waves_of(L, n_prog, slot::kMaxSlots), slot::kMaxSlots);
+    std::lock_guard<std::mutex> lk(tape->mu);
+    if (build) tape->sized.insert(b);
+    if (!tape->sized.count(b)) {
+        set_error("the tape was not sized for this lane count: size the workspace with "
+                  "ndvm_workspace_bytes (ndvm_workspace_bytes_many) for the same lane count first");
+        return NDVM_E_ARG;
+    }
+    *out = w;
+    return NDVM_OK;
+}
+
+ndvm_status check_wide_launch(const LaunchArgs &A, const wide::Prog *table, const wide::Prog &single, uint32_t n_prog,
+                              hipStream_t stream) {
+    const hipError_t e = launch_wide(A, table, single, n_prog, stream);
+    if (e != hipSuccess) {
+        set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
+        return NDVM_E_DEVICE;
+    }
+    return NDVM_OK;
+}
+
 // Workspace rows (fp64 per lane) of one program launched with LDS budget b:
 // checkpoint rows, the trash rows that unused slots store to, spill rows.
 uint64_t ws_rows(const DevProg &dp, uint32_t b) {
@@ -388,6 +527,7 @@ struct ManyLaunch {
     void *d_table = nullptr;
     const uint64_t *d_items = nullptr;   // work item per workgroup (xcd_items), or null
     uint32_t n_wg = 0;
+    bool wide = false;      // every program runs on the wide kernel: d_table holds wide::Prog
 };
 
 // Work items of a many-program launch laid out per XCD.  Each of MI355X's
@@ -401,7 +541,7 @@ struct ManyLaunch {
 // every XCD gets several programs and the largest XCD load is within 5% of
 // the mean; otherwise the launch keeps the plain grid.
 constexpr uint32_t kXcds = 8;
-bool xcd_items(const std::vector<uint32_t> &cost, uint64_t blocks, std::vector<uint64_t> *items) {
+bool xcd_items(const std::vector<uint64_t> &cost, uint64_t blocks, std::vector<uint64_t> *items) {
     const uint32_t n = uint32_t(cost.size());
     if (n < 4 * kXcds || blocks == 0 || blocks > 0xFFFFFFFFull) return false;
     std::vector<uint32_t> order(n);
@@ -433,52 +573,122 @@ bool xcd_items(const std::vector<uint32_t> &cost, uint64_t blocks, std::vector<u
     return true;
 }
 
+// Wide schedules of the programs among `tapes` that have not been tried yet,
+// made on all host threads and copied to the device in order; *all tells
+// whether every program runs on the wide kernel.
+ndvm_status wide_many(const ndvm_tape *const *tapes, int n_prog, const DeviceProps &p, int64_t L, bool build,
+                      std::vector<WideProg *> *progs, bool *all) {
+    *all = false;
+    if (lpad_of(L) > kWideMaxLanes) return NDVM_OK;
+    std::vector<ndvm_tape *> todo;
+    if (build) {
+        std::set<const ndvm_tape *> seen;
+        for (int q = 0; q < n_prog; ++q) {
+            ndvm_tape *t = const_cast<ndvm_tape *>(tapes[q]);
+            std::lock_guard<std::mutex> lk(t->mu);
+            if (!t->wide_grad_tried && seen.insert(t).second) todo.push_back(t);
+        }
+        // a program that cannot run there sends them all to the slot kernel:
+        // nothing is scheduled where the forward programs tell so already
+        for (int q = 0; q < n_prog; ++q)
+            if (!tapes[q]->wide_fwd) return NDVM_OK;
+    }
+    std::vector<WideSchedule> res(todo.size());
+    std::vector<ndvm_status> code(todo.size(), NDVM_OK);
+    std::vector<std::string> msg(todo.size());
+    for_all(todo.size(), [&](size_t i) { res[i] = wide_schedule_of(todo[i], true); }, &code, &msg);
+    for (size_t i = 0; i < todo.size(); ++i) {
+        if (code[i] != NDVM_OK) {
+            set_error(msg[i]);
+            return code[i];
+        }
+        WideProg *w;
+        ndvm_status st = wide_grad_program(todo[i], true, &w, &res[i]);
+        if (st != NDVM_OK) return st;
+    }
+    for (int q = 0; q < n_prog; ++q) {
+        ndvm_tape *t = const_cast<ndvm_tape *>(tapes[q]);
+        WideProg *w = nullptr;
+        ndvm_status st = wide_grad_program(t, false, &w);
+        if (st != NDVM_OK) return st;
+        if (!w || !wide_rows_fit(*w)) return NDVM_OK;
+    }
+    for (int q = 0; q < n_prog; ++q) {
+        WideProg *w = nullptr;
+        ndvm_status st = wide_grad_for(const_cast<ndvm_tape *>(tapes[q]), p, L, n_prog, build, &w);
+        if (st != NDVM_OK) return st;
+        progs->push_back(w);
+    }
+    *all = true;
+    return NDVM_OK;
+}
+
 ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bool build, ManyLaunch *out) {
     DeviceProps p;
     ndvm_status st = device_props(&p);
     if (st != NDVM_OK) return st;
     const uint32_t S = choose_slots(p, L, n_prog);
     const uint32_t b = reg_budget(p, waves_of(L, n_prog, S), S);
-    std::vector<ProgStatic> table(static_cast<size_t>(n_prog), ProgStatic{});
-    std::vector<uint64_t> key;
+    std::vector<uint8_t> table;   // the device table's bytes
+    std::vector<uint64_t> key, cost(static_cast<size_t>(n_prog));
+    std::vector<WideProg *> wide;
+    if ((st = wide_many(tapes, n_prog, p, L, build, &wide, &out->wide)) != NDVM_OK) return st;
     uint64_t row = 0;
-    uint32_t r_launch = 0;
-    int n_spill = 0;
-    std::vector<uint32_t> cost(static_cast<size_t>(n_prog));
-    uint64_t n_mac = 0, n_acc = 0, n_msub = 0, n_block = 0, n_instr = 0;
-    std::map<const ndvm_tape *, Schedule> pre;
-    if (build && (st = schedule_many(tapes, n_prog, S, b, &pre)) != NDVM_OK) return st;
-    for (int q = 0; q < n_prog; ++q) {
-        DevProg *dp;
-        auto pi = pre.find(tapes[q]);
-        Schedule *ps = pi != pre.end() && pi->second.code.size() ? &pi->second : nullptr;
-        if ((st = grad_program(const_cast<ndvm_tape *>(tapes[q]), S, b, build, &dp, ps)) != NDVM_OK) return st;
-        cost[q] = dp->meta.n_instr;
-        uint32_t r_lds = std::min(dp->meta.n_regs, b);
-        r_launch = std::max(r_launch, r_lds);
-        const bool spills = dp->meta.n_regs > r_lds;
-        n_spill += spills;
-        out->skips = out->skips || dp->meta.n_skips > 0;
-        n_mac += dp->meta.n_mac;
-        n_acc += dp->meta.n_acc;
-        n_msub += dp->meta.n_msub;
-        n_block += dp->meta.n_block;
-        n_instr += dp->meta.n_instr;
-        table[q] = ProgStatic{dp->code, dp->consts, row, row + dp->meta.n_ckpt_rows + slot::kMaxBlock,
+    if (out->wide) {
+        std::vector<wide::Prog> t(static_cast<size_t>(n_prog));
+        for (int q = 0; q < n_prog; ++q) {
+            t[q] = wide[q]->prog;
+            t[q].ckpt_row0 = row;
+            t[q].trash_row = row + wide[q]->meta.n_ckpt_rows;
+            row += wide_rows(*wide[q]);
+            cost[q] = wide[q]->meta.cost;
+            key.push_back(tapes[q]->id);
+            key.push_back((uint64_t(S) << 32) | b | uint64_t(1) << 63);
+        }
+        table.resize(t.size() * sizeof(wide::Prog));
+        if (n_prog) std::memcpy(table.data(), t.data(), table.size());
+    } else {
+        std::vector<ProgStatic> t(static_cast<size_t>(n_prog), ProgStatic{});
+        uint32_t r_launch = 0;
+        int n_spill = 0;
+        uint64_t n_mac = 0, n_acc = 0, n_msub = 0, n_block = 0, n_instr = 0;
+        std::map<const ndvm_tape *, Schedule> pre;
+        if (build && (st = schedule_many(tapes, n_prog, S, b, &pre)) != NDVM_OK) return st;
+        for (int q = 0; q < n_prog; ++q) {
+            DevProg *dp;
+            auto pi = pre.find(tapes[q]);
+            Schedule *ps = pi != pre.end() && pi->second.code.size() ? &pi->second : nullptr;
+            if ((st = grad_program(const_cast<ndvm_tape *>(tapes[q]), S, b, build, &dp, ps)) != NDVM_OK) return st;
+            cost[q] = dp->meta.n_instr;
+            uint32_t r_lds = std::min(dp->meta.n_regs, b);
+            r_launch = std::max(r_launch, r_lds);
+            const bool spills = dp->meta.n_regs > r_lds;
+            n_spill += spills;
+            out->skips = out->skips || dp->meta.n_skips > 0;
+            n_mac += dp->meta.n_mac;
+            n_acc += dp->meta.n_acc;
+            n_msub += dp->meta.n_msub;
+            n_block += dp->meta.n_block;
+            n_instr += dp->meta.n_instr;
+            t[q] = ProgStatic{dp->code, dp->consts, row, row + dp->meta.n_ckpt_rows + slot::kMaxBlock,
                               dp->meta.hdr_off, r_lds, spills};
-        row += ws_rows(*dp, b);
-        key.push_back(tapes[q]->id);
-        key.push_back((uint64_t(S) << 32) | b);
+            row += ws_rows(*dp, b);
+            key.push_back(tapes[q]->id);
+            key.push_back((uint64_t(S) << 32) | b);
+        }
+        out->order = dispatch_order(n_mac, n_acc, n_msub, n_block, n_instr);
+        out->r_launch = r_launch;
+        out->variant = n_spill == 0 ? kLdsOnly : n_spill == n_prog ? kSpill : kPerProgram;
+        table.resize(t.size() * sizeof(ProgStatic));
+        if (n_prog) std::memcpy(table.data(), t.data(), table.size());
     }
     out->S = S;
-    out->order = dispatch_order(n_mac, n_acc, n_msub, n_block, n_instr);
-    out->r_launch = r_launch;
     out->rows = row;
-    out->variant = n_spill == 0 ? kLdsOnly : n_spill == n_prog ? kSpill : kPerProgram;
     if (n_prog == 0) return NDVM_OK;
     std::lock_guard<std::mutex> lk(g_table_mu);
     // per-XCD work items (single launches only: at most kMaxProgPerLaunch programs)
-    const uint64_t blocks = uint64_t((L + 64 / S - 1) / (64 / S));
+    const int64_t per_wave = out->wide ? 64 : 64 / S;
+    const uint64_t blocks = uint64_t((L + per_wave - 1) / per_wave);
     std::vector<uint64_t> ikey = key;
     ikey.push_back(blocks);
     auto ii = g_items.find(ikey);
@@ -515,12 +725,12 @@ ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bo
         return NDVM_E_ARG;
     }
     void *d_table = nullptr;
-    if (hipMalloc(&d_table, table.size() * sizeof(ProgStatic)) != hipSuccess) {
+    if (hipMalloc(&d_table, table.size()) != hipSuccess) {
         (void)hipGetLastError();
         set_error("hipMalloc of the program table failed");
         return NDVM_E_NOMEM;
     }
-    if (hipMemcpy(d_table, table.data(), table.size() * sizeof(ProgStatic), hipMemcpyHostToDevice) != hipSuccess) {
+    if (hipMemcpy(d_table, table.data(), table.size(), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(d_table);
         set_error("copy of the program table failed");
         return NDVM_E_DEVICE;
@@ -632,8 +842,13 @@ ndvm_status ndvm_tape_upload(const uint8_t *bytes, size_t len, int policy, void 
             return st;
         h->id = g_next_id++;
         // schedule the forward program now: scheduling limits surface at upload
-        DevProg *fp = nullptr;
-        st = fwd_program(h.get(), 4, static_cast<hipStream_t>(stream), &fp);
+        WideSchedule ws = wide_schedule_of(h.get(), false);
+        if (ws.ok) {
+            st = upload_wide(std::move(ws), h->tape, false, static_cast<hipStream_t>(stream), &h->wide_fwd);
+        } else {
+            DevProg *fp = nullptr;
+            st = fwd_program(h.get(), 4, static_cast<hipStream_t>(stream), &fp);
+        }
         if (st != NDVM_OK) return st;
         *out = h.release();
         return NDVM_OK;
@@ -665,32 +880,15 @@ ndvm_status ndvm_tape_upload_many(const uint8_t *const *tapes, const size_t *len
         std::vector<Schedule> fw(static_cast<size_t>(n));
         std::vector<ndvm_status> code(static_cast<size_t>(n), NDVM_OK);
         std::vector<std::string> msg(static_cast<size_t>(n));
-        std::atomic<int> next{0};
-        auto work = [&]() {
-            for (int i; (i = next.fetch_add(1)) < n;) {
-                try {
-                    if ((code[i] = new_tape(tapes[i], lens[i], save, arms, &hs[i])) != NDVM_OK) {
-                        msg[i] = get_error();
-                        continue;
-                    }
-                    fw[i] = schedule_forward_of(hs[i].get(), 4, fb);
-                } catch (const std::length_error &e) {
-                    code[i] = NDVM_E_UNSUPPORTED;
-                    msg[i] = std::string("program too large for the device format: ") + e.what();
-                } catch (const std::bad_alloc &) {
-                    code[i] = NDVM_E_NOMEM;
-                    msg[i] = "out of host memory";
-                } catch (const std::exception &e) {
-                    code[i] = NDVM_E_INTERNAL;
-                    msg[i] = std::string("internal error: ") + e.what();
-                }
+        std::vector<WideSchedule> ww(static_cast<size_t>(n));
+        for_all(static_cast<size_t>(n), [&](size_t i) {
+            if ((code[i] = new_tape(tapes[i], lens[i], save, arms, &hs[i])) != NDVM_OK) {
+                msg[i] = get_error();
+                return;
             }
-        };
-        const int n_threads = std::min(n, int(std::max(1u, std::thread::hardware_concurrency())));
-        std::vector<std::thread> pool;
-        for (int k = 1; k < n_threads; ++k) pool.emplace_back(work);
-        work();
-        for (auto &th : pool) th.join();
+            ww[i] = wide_schedule_of(hs[i].get(), false);
+            if (!ww[i].ok) fw[i] = schedule_forward_of(hs[i].get(), 4, fb);
+        }, &code, &msg);
         for (int i = 0; i < n; ++i)
             if (code[i] != NDVM_OK) {
                 set_error("ndvm_tape_upload_many: tape " + std::to_string(i) + ": " + msg[i]);
@@ -700,8 +898,12 @@ ndvm_status ndvm_tape_upload_many(const uint8_t *const *tapes, const size_t *len
         for (int i = 0; i < n; ++i) {
             hs[i]->id = g_next_id++;
             DevProg *fp = nullptr;
-            if ((st = fwd_program(hs[i].get(), 4, static_cast<hipStream_t>(stream), &fp, &fw[i])) != NDVM_OK)
-                return st;
+            if (ww[i].ok)
+                st = upload_wide(std::move(ww[i]), hs[i]->tape, false, static_cast<hipStream_t>(stream),
+                                 &hs[i]->wide_fwd);
+            else
+                st = fwd_program(hs[i].get(), 4, static_cast<hipStream_t>(stream), &fp, &fw[i]);
+            if (st != NDVM_OK) return st;
         }
         for (int i = 0; i < n; ++i) out[i] = hs[i].release();
         return NDVM_OK;
@@ -766,11 +968,22 @@ ndvm_status ndvm_workspace_bytes(const ndvm_tape *tape, int64_t L, int with_grad
         DevProg *dp;
         if (with_grad) {
             uint32_t b = 0;
+            WideProg *w = nullptr;
+            st = wide_grad_for(const_cast<ndvm_tape *>(tape), p, L, 1, true, &w);
+            if (st != NDVM_OK) return st;
+            if (w) {
+                *bytes = size_t(wide_rows(*w) * uint64_t(Lp) * sizeof(double));
+                return NDVM_OK;
+            }
             st = single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, true, &dp, &b);
             if (st != NDVM_OK) return st;
             rows = ws_rows(*dp, b);
         } else {
             uint32_t bf = uint32_t(p.lds_per_block / reg_bytes(S));
+            if (tape->wide_fwd) {
+                *bytes = size_t(wide_rows(*tape->wide_fwd) * uint64_t(Lp) * sizeof(double));
+                return NDVM_OK;
+            }
             st = fwd_program(const_cast<ndvm_tape *>(tape), S, nullptr, &dp);
             if (st != NDVM_OK) return st;
             rows = ws_rows(*dp, bf);
@@ -829,6 +1042,16 @@ ndvm_status ndvm_forward(const ndvm_tape *tape, const double *params, int64_t L,
         DeviceProps p;
         if ((st = device_props(&p)) != NDVM_OK) return st;
         const uint32_t S = choose_slots(p, L, 1);
+        if (tape->wide_fwd) {
+            const int64_t Lp = lpad_of(L);
+            const size_t need = size_t(wide_rows(*tape->wide_fwd) * uint64_t(Lp) * sizeof(double));
+            if (!ws || ws_bytes < need) {
+                set_error("ndvm_forward: workspace too small");
+                return NDVM_E_NOMEM;
+            }
+            const LaunchArgs A{obs, params, loss, loss, static_cast<double *>(ws), ld_p, 0, L, Lp, 0, 0};
+            return check_wide_launch(A, nullptr, tape->wide_fwd->prog, 1, static_cast<hipStream_t>(stream));
+        }
         DevProg *fp;
         if ((st = fwd_program(const_cast<ndvm_tape *>(tape), S, static_cast<hipStream_t>(stream), &fp)) != NDVM_OK)
             return st;
@@ -848,6 +1071,56 @@ ndvm_status ndvm_forward(const ndvm_tape *tape, const double *params, int64_t L,
     });
 }
 
+// The static scratch array as the workspace of a launch that needs `need`
+// bytes.
+static ndvm_status static_workspace(size_t need, const char *who, void **ws, size_t *ws_bytes) {
+    if (need > scratch_bytes()) {
+        set_error(std::string(who) + ": this launch needs " + std::to_string(need) +
+                  " bytes of workspace, more than the static scratch of " + std::to_string(scratch_bytes()) +
+                  " bytes; use ndvm_grad with a caller workspace");
+        return NDVM_E_NOMEM;
+    }
+    const hipError_t e = scratch_address(ws);
+    if (e != hipSuccess) {
+        set_error(std::string(who) + ": hipGetSymbolAddress of the scratch array failed: " + hipGetErrorString(e));
+        return NDVM_E_DEVICE;
+    }
+    *ws_bytes = scratch_bytes();
+    return NDVM_OK;
+}
+
+// A gradient launch of the wide kernel.  On the static scratch array, a
+// launch whose rows do not fit runs as several launches over parts of its
+// lanes, one after the other on `stream`: the slot kernel can need fewer rows
+// (its register budget is larger for few lanes, and it stores nothing for the
+// loss), and no launch that fitted the array with it is refused.
+static ndvm_status wide_grad_launch(const WideProg &w, const double *params, int64_t L, int64_t ld_p,
+                                    const double *obs, double *loss, double *grad, int64_t ld_g, void *ws,
+                                    size_t ws_bytes, bool static_ws, void *stream, const char *who) {
+    int64_t part = L;
+    size_t need = size_t(wide_rows(w) * uint64_t(lpad_of(L)) * sizeof(double));
+    if (static_ws) {
+        if (need > scratch_bytes()) {
+            part = int64_t(scratch_bytes() / (wide_rows(w) * sizeof(double))) / 64 * 64;
+            need = size_t(wide_rows(w) * uint64_t(part) * sizeof(double));
+        }
+        const ndvm_status st = static_workspace(need, who, &ws, &ws_bytes);
+        if (st != NDVM_OK) return st;
+    }
+    if (!ws || ws_bytes < need) {
+        set_error(std::string(who) + ": workspace too small");
+        return NDVM_E_NOMEM;
+    }
+    for (int64_t l0 = 0; l0 < L; l0 += part) {
+        const int64_t n = std::min(part, L - l0);
+        const LaunchArgs A{obs, params ? params + l0 * ld_p : nullptr, loss + l0, grad ? grad + l0 * ld_g : nullptr,
+                           static_cast<double *>(ws), ld_p, ld_g, n, lpad_of(n), 0, 0};
+        const ndvm_status st = check_wide_launch(A, nullptr, w.prog, 1, static_cast<hipStream_t>(stream));
+        if (st != NDVM_OK) return st;
+    }
+    return NDVM_OK;
+}
+
 // ndvm_grad and its allocation-free variant: `ws` is the caller's workspace
 // or the static scratch array's device address.
 static ndvm_status grad_impl(const ndvm_tape *tape, const double *params, int64_t L, int64_t ld_p,
@@ -864,26 +1137,15 @@ static ndvm_status grad_impl(const ndvm_tape *tape, const double *params, int64_
     if ((st = device_props(&p)) != NDVM_OK) return st;
     int64_t Lp = lpad_of(L);
     const uint32_t S = choose_slots(p, L, 1);
+    WideProg *wp = nullptr;
+    if ((st = wide_grad_for(const_cast<ndvm_tape *>(tape), p, L, 1, false, &wp)) != NDVM_OK) return st;
+    if (wp) return wide_grad_launch(*wp, params, L, ld_p, obs, loss, grad, ld_g, ws, ws_bytes, static_ws, stream, who);
     uint32_t b = 0;
     DevProg *dp;
     if ((st = single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, false, &dp, &b)) != NDVM_OK) return st;
     uint32_t r_lds = std::min(dp->meta.n_regs, b);
     size_t need = size_t(ws_rows(*dp, b) * uint64_t(Lp) * sizeof(double));
-    if (static_ws) {
-        if (need > scratch_bytes()) {
-            set_error(std::string(who) + ": this launch needs " + std::to_string(need) +
-                      " bytes of workspace, more than the static scratch of " + std::to_string(scratch_bytes()) +
-                      " bytes; use ndvm_grad with a caller workspace");
-            return NDVM_E_NOMEM;
-        }
-        const hipError_t e = scratch_address(&ws);
-        if (e != hipSuccess) {
-            set_error(std::string(who) + ": hipGetSymbolAddress of the scratch array failed: " +
-                      hipGetErrorString(e));
-            return NDVM_E_DEVICE;
-        }
-        ws_bytes = scratch_bytes();
-    }
+    if (static_ws && (st = static_workspace(need, who, &ws, &ws_bytes)) != NDVM_OK) return st;
     if (need && (!ws || ws_bytes < need)) {
         set_error(std::string(who) + ": workspace too small");
         return NDVM_E_NOMEM;
@@ -916,15 +1178,18 @@ ndvm_status ndvm_grad_noalloc(const ndvm_tape *tape, const double *params, int64
 
 // Flattened data axis: L * N lanes.  Workspace: the replay's rows for L*N
 // lanes, then the per-point terms [L*N] and term gradients [L*N, P].
-static ndvm_status points_layout(const ndvm_tape *tape, int64_t L, int64_t N, bool build, DevProg **dp,
-                                 uint32_t *b, uint64_t *replay_bytes, uint64_t *total) {
+static ndvm_status points_layout(const ndvm_tape *tape, int64_t L, int64_t N, bool build, WideProg **wp,
+                                 DevProg **dp, uint32_t *b, uint64_t *replay_bytes, uint64_t *total) {
     DeviceProps p;
     ndvm_status st = device_props(&p);
     if (st != NDVM_OK) return st;
     const int64_t F = L * N;
     const uint32_t S = choose_slots(p, F, 1);
-    if ((st = single_grad_program(const_cast<ndvm_tape *>(tape), p, F, S, build, dp, b)) != NDVM_OK) return st;
-    *replay_bytes = ws_rows(**dp, *b) * uint64_t(lpad_of(F)) * sizeof(double);
+    if ((st = wide_grad_for(const_cast<ndvm_tape *>(tape), p, F, 1, build, wp)) != NDVM_OK) return st;
+    if (!*wp &&
+        (st = single_grad_program(const_cast<ndvm_tape *>(tape), p, F, S, build, dp, b)) != NDVM_OK)
+        return st;
+    *replay_bytes = (*wp ? wide_rows(**wp) : ws_rows(**dp, *b)) * uint64_t(lpad_of(F)) * sizeof(double);
     *total = *replay_bytes + uint64_t(F) * (1 + tape->tape.n_params) * sizeof(double);
     return NDVM_OK;
 }
@@ -935,10 +1200,11 @@ ndvm_status ndvm_workspace_bytes_points(const ndvm_tape *tape, int64_t L, int64_
             set_error("ndvm_workspace_bytes_points: bad argument");
             return NDVM_E_ARG;
         }
+        WideProg *wp;
         DevProg *dp;
         uint32_t b;
         uint64_t rb, total;
-        ndvm_status st = points_layout(tape, L, n_points, true, &dp, &b, &rb, &total);
+        ndvm_status st = points_layout(tape, L, n_points, true, &wp, &dp, &b, &rb, &total);
         if (st != NDVM_OK) return st;
         *bytes = size_t(total);
         return NDVM_OK;
@@ -961,10 +1227,11 @@ ndvm_status ndvm_grad_points(const ndvm_tape *tape, const double *params, int64_
             return NDVM_E_ARG;
         }
         if (L == 0) return NDVM_OK;
+        WideProg *wp;
         DevProg *dp;
         uint32_t b;
         uint64_t rb, total;
-        ndvm_status st = points_layout(tape, L, n_points, false, &dp, &b, &rb, &total);
+        ndvm_status st = points_layout(tape, L, n_points, false, &wp, &dp, &b, &rb, &total);
         if (st != NDVM_OK) return st;
         if (!ws || ws_bytes < total) {
             set_error(std::string(who) + ": workspace too small");
@@ -974,15 +1241,19 @@ ndvm_status ndvm_grad_points(const ndvm_tape *tape, const double *params, int64_
         double *wsd = static_cast<double *>(ws);
         double *term = wsd + rb / sizeof(double), *tgrad = term + F;
         LaunchArgs A{points, params, term, tgrad, wsd, ld_p, P, F, lpad_of(F), 0, 0, n_points, ld_pt};
-        const uint32_t r_lds = std::min(dp->meta.n_regs, b);
-        const bool spills = dp->meta.n_regs > r_lds;
-        ProgStatic D_{dp->code, dp->consts, 0, uint64_t(dp->meta.n_ckpt_rows) + slot::kMaxBlock, dp->meta.hdr_off,
-                      r_lds, spills};
         hipStream_t s = static_cast<hipStream_t>(stream);
-        DeviceProps pr;
-        if ((st = device_props(&pr)) != NDVM_OK) return st;
-        st = check_stream_and_launch(A, nullptr, D_, 1, r_lds, spills ? kSpill : kLdsOnly, dp->meta.n_skips > 0,
-                                     dispatch_order(dp->meta), choose_slots(pr, F, 1), s);
+        if (wp) {
+            st = check_wide_launch(A, nullptr, wp->prog, 1, s);
+        } else {
+            const uint32_t r_lds = std::min(dp->meta.n_regs, b);
+            const bool spills = dp->meta.n_regs > r_lds;
+            ProgStatic D_{dp->code, dp->consts, 0, uint64_t(dp->meta.n_ckpt_rows) + slot::kMaxBlock, dp->meta.hdr_off,
+                          r_lds, spills};
+            DeviceProps pr;
+            if ((st = device_props(&pr)) != NDVM_OK) return st;
+            st = check_stream_and_launch(A, nullptr, D_, 1, r_lds, spills ? kSpill : kLdsOnly, dp->meta.n_skips > 0,
+                                         dispatch_order(dp->meta), choose_slots(pr, F, 1), s);
+        }
         if (st != NDVM_OK) return st;
         const hipError_t e = launch_fold_points(term, tgrad, L, n_points, P, scale, loss, grad, ld_g, s);
         if (e != hipSuccess) {
@@ -1039,8 +1310,11 @@ ndvm_status ndvm_grad_many(const ndvm_tape *const *tapes, int n_prog, const doub
                 A.wg_items = ml.d_items;
                 A.n_wg = ml.n_wg;
             }
-            st = check_stream_and_launch(A, static_cast<const ProgStatic *>(d_table) + q0, none, uint32_t(nq),
-                                         r_launch, variant, ml.skips, ml.order, S, s);
+            if (ml.wide)
+                st = check_wide_launch(A, static_cast<const wide::Prog *>(d_table) + q0, wide::Prog{}, uint32_t(nq), s);
+            else
+                st = check_stream_and_launch(A, static_cast<const ProgStatic *>(d_table) + q0, none, uint32_t(nq),
+                                             r_launch, variant, ml.skips, ml.order, S, s);
             if (st != NDVM_OK) return st;
         }
         return NDVM_OK;

@@ -18,6 +18,8 @@
 #include "common.h"
 #include "sched.h"
 #include "slot_exec.h"
+#include "wide.h"
+#include "wide_exec.h"
 
 using namespace ndvm;
 
@@ -303,6 +305,197 @@ int64_t ndvm_emu_program(const uint8_t *tape, size_t len, int with_grad, uint32_
     if (out && cap >= n) std::copy(S.code.begin(), S.code.end(), out);
     if (hdr_off) *hdr_off = S.hdr_off;
     return int64_t(n);
+}
+
+/*
+ * Schedule `tape` for the wide kernel (mode: 0 forward only, 1 gradient with
+ * the recompute policy, 2 with the save policy) and run its blocks for L lanes
+ * on the host, micro-op by micro-op as the kernel does.  Reads of registers
+ * never written, of load slots whose loads have not been waited for, and
+ * registers, rows and indices out of range are faults.  stats (optional, 6
+ * entries): registers, checkpoint rows, segments, blocks, micro-ops, estimated
+ * cycles.  Returns 0, 1 for a tape the wide kernel does not take, an
+ * ndvm_status from parsing (negated), or 100 + fault code.
+ */
+int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, const double *params, int64_t L, int64_t ld_p,
+                  const double *obs, int64_t n_obs, double *loss, double *grad, int64_t ld_g, uint64_t *stats) {
+    using namespace wide;
+    Tape t;
+    ndvm_status st = parse_tape(tape, len, &t);
+    if (st != NDVM_OK) return -int(st);
+    const WideSchedule S = schedule_wide(t, mode != 0, mode == 2);
+    if (!S.ok) return 1;
+    if (stats) {
+        const uint64_t v[6] = {S.n_regs, S.n_ckpt_rows, S.n_segments, S.n_blocks, S.n_uops, S.cost};
+        for (int i = 0; i < 6; ++i) stats[i] = v[i];
+    }
+    for (int64_t l = 0; l < L; ++l) {
+        std::vector<double> reg(kRegs, NAN), ck(S.n_ckpt_rows, NAN);
+        std::vector<uint8_t> state(kRegs, 0);   // 1 written, 2 load in flight
+        int fault = 0;
+        auto flag = [&](int c) {
+            if (!fault) fault = c;
+        };
+        uint32_t r0 = kSlots;
+        auto init = [&](double v) {
+            if (r0 >= kRegs) return flag(1);
+            reg[r0] = v;
+            state[r0++] = 1;
+        };
+        for (uint32_t p = 0; p < t.n_params; ++p) init(params[l * ld_p + p]);
+        for (uint32_t p = 0; mode && p < t.n_params; ++p) init(0.0);
+        const uint32_t sink = r0;
+        init(0.0);
+        for (double v : S.consts) init(v);
+        auto idx = [&](uint32_t h, uint32_t roles) -> uint32_t {
+            if ((h & 0xF000u) != roles || (h & 0x0F00u) || (h & 1u) || (h & 0xFFu) / 2 >= S.n_regs) flag(2);
+            return (h & 0xFFu) / 2 < kRegs ? (h & 0xFFu) / 2 : 0;
+        };
+        auto get = [&](uint32_t h, uint32_t roles) {
+            const uint32_t r = idx(h, roles);
+            if (state[r] != 1) flag(3);
+            return reg[r];
+        };
+        auto set = [&](uint32_t h, uint32_t roles, double v) {
+            const uint32_t r = idx(h, roles);
+            // statics are never overwritten, parameter adjoints and the sink apart
+            if (r >= kSlots && r < r0 && (r < kSlots + t.n_params || r > sink)) flag(4);
+            reg[r] = v;
+            state[r] = 1;
+        };
+        const uint32_t SD = kSrc | kDst;
+        uint64_t start = S.first[0], next = S.first[2];   // where this block's and the next one's words are read
+        uint32_t where = S.first[1];
+        bool ended = false;
+        for (uint64_t b = 0; !ended && !fault; ++b) {
+            const uint32_t region = where / kRegion, cls = region / 2;
+            if (cls >= kClasses || (region & 1u) != (b & 1u) || start / 4 + kBlockWords > S.code.size() || start % 4) {
+                flag(5);
+                break;
+            }
+            const ClassInfo info = kInfo[cls];
+            const uint32_t skipped = info.bytes ? (where % kRegion) / info.bytes : 0, n = info.max - skipped;
+            if (skipped >= info.max || entry(cls, n, b & 1u) != where) {
+                flag(5);
+                break;
+            }
+            const uint32_t *hdr = S.code.data() + start / 4 + kBlockWords - 2;
+            const uint32_t *w = hdr - size_t(n) * info.words;
+            for (uint32_t i = 0; i < n && !fault && !ended; ++i, w += info.words) {
+                const uint32_t a = info.words > 0 ? w[0] : 0, c = info.words > 1 ? w[1] : 0,
+                               d = info.words > 2 ? w[2] : 0;
+                const uint32_t al = a & 0xFFFFu, ah = a >> 16, cl = c & 0xFFFFu, ch = c >> 16, dl = d & 0xFFFFu,
+                               dh = d >> 16;
+                auto add = [&](uint32_t h, bool on, double v) {
+                    const double o = get(h, SD);
+                    if (on) set(h, SD, o + v);
+                };
+                switch (cls) {
+                case FMA: {
+                    const double x = get(al, kSrc), y = get(ah, kSrc), z = get(cl, kSrc), p = x * y;
+                    set(ch, kDst, p + z);
+                    break;
+                }
+                case DUAL: {
+                    const double g = get(al, kSrc);
+                    set(ah, kDst, 0.0);
+                    const double y = get(cl, kSrc);
+                    add(ch, g != 0.0, y * g);
+                    const double z = get(dl, kSrc);
+                    add(dh, g != 0.0, z * g);
+                    break;
+                }
+                case SEL: {
+                    const bool lt = get(al, kSrc) < get(ah, kSrc);
+                    const double x = get(cl, kSrc), y = get(ch, kSrc);
+                    set(dl, kDst, lt ? x : y);
+                    break;
+                }
+                case SELADJ: {
+                    const double g = get(al, kSrc);
+                    set(ah, kDst, 0.0);
+                    const bool lt = get(cl, kSrc) < get(ch, kSrc);
+                    add(dl, lt, g);
+                    add(dh, !lt, g);
+                    break;
+                }
+                case DIV: {
+                    const double x = get(al, kSrc), y = get(ah, kSrc);
+                    set(cl, kDst, x / y);
+                    break;
+                }
+                case DIVADJ: {
+                    const double g = get(al, kSrc);
+                    set(ah, kDst, 0.0);
+                    const double y = get(cl, kSrc), gz = get(dl, kSrc) * g;
+                    add(ch, g != 0.0, g / y);
+                    add(dh, g != 0.0, -(gz / y));
+                    break;
+                }
+                case ACCD: {
+                    const double g = get(al, kSrc);
+                    set(ah, kDst, 0.0);
+                    const double y = get(cl, kSrc), z = get(dl, kSrc);
+                    add(ch, g != 0.0, z / y);
+                    break;
+                }
+                case CKST:
+                    if (c >= S.n_ckpt_rows) flag(6);
+                    else ck[c] = get(al, kSrc);
+                    break;
+                case LDK0: case LDK1: case LDO0: case LDO1: {
+                    const bool k = cls == LDK0 || cls == LDK1;
+                    const uint32_t half = k ? cls - LDK0 : cls - LDO0;
+                    const uint32_t slot = (k ? 2 * kObsSlots + half * kCkSlots : half * kObsSlots) + skipped + i;
+                    if (k ? a >= S.n_ckpt_rows : (a % 8 || a / 8 >= uint32_t(n_obs))) {
+                        flag(6);
+                        break;
+                    }
+                    reg[slot] = k ? ck[a] : obs[a / 8];
+                    state[slot] = 2;
+                    break;
+                }
+                case PF: case WAITPF:
+                    if (a + kPrefetch > 4 * S.code.size()) flag(6);
+                    if (cls == PF) break;
+                    [[fallthrough]];
+                case WAIT:
+                    for (uint32_t s = 0; s < kSlots; ++s)
+                        if (state[s] == 2) state[s] = 1;
+                    break;
+                case STLOSS: loss[l] = get(al, kSrc); break;
+                case STGRAD:
+                    if (c % 8 || c / 8 >= t.n_params || !grad) flag(6);
+                    else grad[l * ld_g + c / 8] = get(al, kSrc);
+                    break;
+                case EXP: set(ah, kDst, exp(get(al, kSrc))); break;
+                case SIN: set(ah, kDst, sin(get(al, kSrc))); break;
+                case COS: set(ah, kDst, cos(get(al, kSrc))); break;
+                case LOGC: set(ah, kDst, f_logc(get(al, kSrc))); break;
+                case SQRTC: set(ah, kDst, f_sqrtc(get(al, kSrc))); break;
+                case ABS: set(ah, kDst, fabs(get(al, kSrc))); break;
+                case POW: set(cl, kDst, pow(get(al, kSrc), get(ah, kSrc))); break;
+                case ACCSIN: set(ch, kDst, f_accsin(get(al, kSrc), get(ah, kSrc), get(cl, kSrc))); break;
+                case ACCCOS: set(ch, kDst, f_acccos(get(al, kSrc), get(ah, kSrc), get(cl, kSrc))); break;
+                case ACCLOG: set(ch, kDst, f_acclog(get(al, kSrc), get(ah, kSrc), get(cl, kSrc))); break;
+                case ACCABS: set(ch, kDst, f_accabs(get(al, kSrc), get(ah, kSrc), get(cl, kSrc))); break;
+                case ACCPOW: set(dl, kDst, f_accpow(get(al, kSrc), get(ah, kSrc), get(cl, kSrc), get(ch, kSrc))); break;
+                case ACCSQRT: set(dl, kDst, f_accsqrt(get(al, kSrc), get(ah, kSrc), get(cl, kSrc), get(ch, kSrc))); break;
+                default: ended = true;
+                }
+            }
+            where = hdr[0];
+            start = next;
+            next = hdr[1];
+        }
+        if (fault) {
+            char m[96];
+            std::snprintf(m, sizeof m, "wide emulator fault %d in lane %lld", fault, (long long)l);
+            set_error(m);
+            return 100 + fault;
+        }
+    }
+    return 0;
 }
 
 const char *ndvm_emu_error(void) { return get_error(); }

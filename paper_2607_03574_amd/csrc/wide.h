@@ -1,0 +1,137 @@
+// Device program format of the wide replay kernel ("wide" programs): scalar
+// programs, one thread per lane.  Produced by the wide scheduler from a
+// validated tape; not part of the public interface.
+//
+// A wave of 64 threads replays 64 lanes.  Each thread holds its lane's whole
+// register file in vector registers: file register r is v[kFileBase + 2r :
+// kFileBase + 2r + 1], reached through the VGPR index mode (M0 holds the
+// wave-uniform index), so an operand costs one scalar move and no memory
+// access, and a result is ready for the next micro-op a few cycles later.
+// Micro-ops of a thread run one after the other, so they need no packing
+// and may depend on their neighbours.
+//
+// The program is a sequence of blocks.  A block holds 1 .. kMax micro-ops of
+// one class and ends with two header words; it is read through scalar loads
+// into one half of a double buffer (kBlockWords words ending with the headers,
+// so a short block's words are the last of the half) while the block before
+// it runs.  The class's code is straight-line for kMax micro-ops, each reading
+// its words from fixed scalar registers, and a block of n micro-ops enters it
+// at micro-op kMax - n, so nothing is tested inside a block.  Blocks alternate
+// between the halves, which have code of their own.
+//
+// Headers of block b: the entry point of block b + 1 (byte offset from the
+// code base), and where the kBlockWords words of block b + 2 start (byte
+// offset in the program).
+//
+// A micro-op's operands are half words: bits 0-7 twice the register number,
+// bits 12-15 the operand roles the index applies to (kSrc: source 0, kDst:
+// destination), the form M0 takes.
+#pragma once
+#include <cstddef>
+#include <cstdint>
+#include <vector>
+
+namespace ndvm {
+
+struct Tape;
+
+namespace wide {
+
+// The vector registers below the file: 40 for temporaries and library
+// functions, then four addresses.
+constexpr uint32_t kFileBase = 48;
+constexpr uint32_t kRegs = (256 - kFileBase) / 2;
+// Load slots: registers the loads of observations (two halves of kObsSlots
+// from 0) and of checkpoint rows (two halves of kCkSlots behind them) write.
+// The slots a program does not use are ordinary registers.
+constexpr uint32_t kObsSlots = 4, kCkSlots = 12;
+constexpr uint32_t kSlots = 2 * kObsSlots + 2 * kCkSlots;
+
+constexpr uint32_t kSrc = 0x1000, kDst = 0x8000;
+
+// Half words of each class: x (y, z, w) read, d written, a read and written,
+// zr cleared before the adjoint update, "-" unused.  The adjoint forms add to
+// w (a register holding +0 for a first contribution) or to a (cleared by zr).
+enum Class : uint32_t {
+    FMA = 0,   // d = x * y + z (product rounded, then sum rounded): x, y | z, d
+    DUAL,      // the linear adjoint rule with two targets: zr = +0, then where g != 0:
+               // a += g * y, b += g * z: g, zr | y, a | z, b
+    SEL,       // d = x < y ? z : w (unordered takes w): x, y | z, w | d, -
+    SELADJ,    // adjoint of a select: zr = +0, then a += g where x < y, b += g elsewhere:
+               // g, zr | x, y | a, b
+    DIV,       // d = x / y: x, y | d, -
+    DIVADJ,    // adjoint of z = x / y: zr = +0, then where g != 0: a += g / y, b += -((g * z) / y):
+               // g, zr | y, a | z, b
+    ACCD,      // zr = +0, then where g != 0: a += z / y: g, zr | y, a | z, -
+    CKST,      // checkpoint row of this lane = x: x, - | row
+    LDK0, LDK1,   // load slot (by position, of a half) = checkpoint row: row
+    LDO0, LDO1,   // load slot (by position, of a half) = observation: byte offset
+    WAIT,      // the loads have landed
+    WAITPF,    // WAIT, then PF
+    PF,        // fetch kPrefetch bytes of the program into the L2 cache: byte offset
+    STLOSS,    // loss[lane] = x: x, -
+    STGRAD,    // grad[lane, p] = x: x, - | 8 p
+    // library functions
+    EXP,       // d = exp(x): x, d
+    SIN,       // d = sin(x)
+    COS,       // d = cos(x)
+    LOGC,      // d = log(max(x, 1e-8)), NaN kept
+    SQRTC,     // d = sqrt(max(x, 1e-8)), NaN kept
+    POW,       // d = pow(x, y): x, y | d, -
+    ACCSIN,    // d = x != 0 ? w + x * cos(y) : w: x, y | w, d
+    ACCCOS,    // d = x != 0 ? w + x * -sin(y) : w
+    ACCLOG,    // d = x != 0 && y > 1e-8 ? w + x / y : w
+    ACCABS,    // d = x != 0 ? w + (y > 0 ? x : y < 0 ? -x : 0) : w
+    ACCPOW,    // d = x != 0 ? w + z * log(y) : w: x, y | z, w | d, -
+    ACCSQRT,   // d = x != 0 && y > 1e-8 ? w + x / (2 z) : w
+    ABS,       // d = |x|: x, d
+    END,       // the program's end
+    kClasses
+};
+// words per micro-op, micro-ops per block, code bytes per micro-op
+struct ClassInfo {
+    uint8_t words, max, bytes;
+};
+constexpr ClassInfo kInfo[kClasses] = {
+    {2, 15, 40}, {3, 10, 72}, {3, 10, 44}, {3, 10, 64}, {2, 8, 112}, {3, 4, 240}, {3, 6, 140}, {2, 15, 32},
+    {1, kCkSlots, 28}, {1, kCkSlots, 28}, {1, kObsSlots, 28}, {1, kObsSlots, 28}, {0, 1, 0}, {1, 1, 40},
+    {1, 2, 36}, {1, 1, 16}, {2, 8, 32},
+    {1, 10, 48}, {1, 10, 48}, {1, 10, 48}, {1, 10, 48}, {1, 10, 48}, {2, 10, 52}, {2, 10, 64}, {2, 10, 64},
+    {2, 10, 64}, {2, 10, 64}, {3, 10, 68}, {3, 10, 68}, {1, 10, 48}, {0, 1, 0}};
+constexpr uint32_t kPrefetch = 4096;   // one line of 64 bytes per thread
+constexpr uint32_t kRegion = 1024;   // code bytes reserved per class and half
+constexpr uint32_t kBlockWords = 32;
+
+// code offset of a block's entry point
+constexpr uint32_t entry(uint32_t cls, uint32_t n, uint32_t half) {
+    return (2 * cls + half) * kRegion + (kInfo[cls].max - n) * kInfo[cls].bytes;
+}
+
+// Per-program constants read by the kernel.
+struct Prog {
+    const uint32_t *code;    // the blocks, with kBlockWords words of padding in front
+    const double *consts;    // static constants, in register order
+    uint64_t ckpt_row0;      // checkpoint row r of lane l at ws[(ckpt_row0 + r) * Lpad + l]
+    uint64_t trash_row;      // row that the lanes past the last one write their results to
+    uint32_t first[3];       // where the words of block 0 start, entry of block 0, where those of block 1 start
+    uint32_t n_params, n_consts;
+    uint32_t adjoints;       // the program has parameter adjoints (n_params registers after the parameters)
+};
+
+}  // namespace wide
+
+struct WideSchedule {
+    bool ok = false;              // false: not a program this kernel takes (matrices, too many registers)
+    std::vector<uint32_t> code;   // words; kBlockWords padding words in front, kPrefetch bytes behind
+    std::vector<double> consts;
+    uint32_t n_regs = 0, n_ckpt_rows = 0, n_segments = 1, n_blocks = 0;
+    uint32_t first[3] = {0, 0, 0};
+    uint64_t n_uops = 0;
+    uint64_t cost = 0;            // estimated cycles of a lone wave
+};
+
+// Wide program of a tape: forward only, or forward and reverse (save_reads as
+// schedule_grad).
+WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads);
+
+}  // namespace ndvm

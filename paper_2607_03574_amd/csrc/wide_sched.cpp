@@ -1,0 +1,909 @@
+// Scheduler of the wide replay kernel: a scalar tape becomes one sequence of
+// micro-ops per lane (forward sweep, then per checkpoint segment restore,
+// recompute, adjoint rules), over virtual registers that a linear scan places
+// in the lane's register file, then cut into blocks of one class.
+//
+// Which values are computed, stored and recomputed, and the order of the
+// contributions to every adjoint, are those of the slot scheduler (Info,
+// Builder), so both kernels give the same bits.
+#include "wide.h"
+
+#include <algorithm>
+#include <cstring>
+#include <queue>
+#include <stdexcept>
+#include <unordered_map>
+
+#include "plan.h"
+#include "slot.h"
+
+namespace ndvm {
+
+namespace {
+
+using namespace wide;
+
+struct WOp {
+    uint8_t cls = 0, n = 0;
+    bool late = false;     // a load of a row the loss is formed from
+    uint32_t imm = 0;      // row, observation index or output index
+    uint32_t r[6] = {};    // registers in the order of the class's half words
+};
+
+// Half words of a class and their roles: 'u' read, 'd' written after the
+// reads, 'e' written before the last read, 'm' read and written, '-' unused;
+// the immediate's word ('i') stands for two halves.
+const char *roles(uint32_t cls) {
+    switch (cls) {
+    case FMA: return "uuud";
+    case DUAL: return "ueumum";
+    case SEL: return "uuuud-";
+    case SELADJ: return "ueuumm";
+    case DIV: case POW: return "uud-";
+    case DIVADJ: return "ueumum";
+    case ACCD: return "ueumu-";
+    case CKST: case STGRAD: return "u-i";
+    case LDK0: case LDK1: case LDO0: case LDO1: case WAITPF: case PF: return "i";
+    case STLOSS: return "u-";
+    case EXP: case SIN: case COS: case LOGC: case SQRTC: case ABS: return "ud";
+    case ACCSIN: case ACCCOS: case ACCLOG: case ACCABS: return "uuud";
+    case ACCPOW: case ACCSQRT: return "uuuud-";
+    default: return "";
+    }
+}
+
+constexpr uint32_t kNone = 0xFFFFFFFFu;
+constexpr uint32_t kUnsetTime = 0xFFFFFFFFu;
+constexpr uint32_t kVirtual = 1u << 20;   // register numbers from here on are virtual
+// micro-ops a value may wait in its load slot before its last reader; beyond
+// that it is copied to a register so that the slot's next load can start
+constexpr uint32_t kSlotHold = 24;
+// micro-ops to look back for one that can clear a second first-contribution target
+constexpr uint32_t kLookBack = 48;
+
+// Estimated cycles of a lone wave per micro-op and per block (an instruction
+// issues about every 4.5 cycles; a change of EXEC by a compare costs 20 more).
+uint32_t class_cost(uint32_t cls) {
+    switch (cls) {
+    case FMA: return 32;
+    case DUAL: return 72;
+    case SEL: return 46;
+    case SELADJ: return 80;
+    case DIV: return 90;
+    case DIVADJ: return 200;
+    case ACCD: return 130;
+    case CKST: return 35;
+    case LDK0: case LDK1: case LDO0: case LDO1: return 25;
+    case EXP: return 330;
+    case SIN: case COS: case ACCSIN: case ACCCOS: return 450;
+    case LOGC: case ACCPOW: return 450;
+    case POW: return 1100;
+    case ACCLOG: case ACCSQRT: case SQRTC: return 280;
+    case PF: case WAITPF: return 30;
+    default: return 150;
+    }
+}
+constexpr uint32_t kDispatchCost = 62;
+
+struct Lower {
+    const Info &I;
+    Builder &B;
+    const Tape &t;
+    const bool with_grad;
+    const uint32_t N, P;
+    std::vector<double> consts;
+    std::unordered_map<uint64_t, uint32_t> const_of;   // bits -> constant number
+    uint32_t kSink = 0, kConst0 = 0, n_static = 0;
+    std::vector<WOp> ops;
+    uint32_t n_virtual = 0;                            // virtual registers so far (ids from kSlots + n_static)
+    std::unordered_map<uint32_t, uint32_t> neg_param;  // parameter -> register holding its negation
+    std::vector<uint32_t> fval, adj;
+    // of the segment being reversed: the register of each value, and the
+    // checkpoint row of each live-in value (valid where the mark is segment + 1)
+    std::vector<uint32_t> rval, rval_of, row, row_of;
+    std::vector<uint32_t> first_row;                   // of each segment's live-in values
+    // loads, in the order their values are first needed: position in ops of
+    // the placeholder that takes the value (an FMA move whose r[0] becomes the slot)
+    struct Load {
+        uint32_t at, reg;
+        bool ckpt;
+        uint32_t imm;
+        uint32_t after;   // op that stores the row (0 for an observation)
+        bool late;        // read when the loss is formed last
+    };
+    std::vector<Load> loads;
+    std::vector<uint32_t> stored_at;   // op that stores each checkpoint row
+
+    Lower(const Info &info, Builder &b, bool grad) : I(info), B(b), t(info.t), with_grad(grad), N(info.N), P(info.P) {}
+
+    uint32_t konst(double v) {
+        uint64_t bits;
+        std::memcpy(&bits, &v, 8);
+        auto it = const_of.emplace(bits, uint32_t(consts.size()));
+        if (it.second) consts.push_back(v);
+        return kConst0 + it.first->second;
+    }
+    uint32_t vreg() { return kVirtual + n_virtual++; }
+    void put(uint32_t cls, std::initializer_list<uint32_t> r, uint32_t imm = 0) {
+        WOp u;
+        u.cls = uint8_t(cls);
+        u.imm = imm;
+        for (uint32_t x : r) u.r[u.n++] = x;
+        ops.push_back(u);
+    }
+    void fma(uint32_t a, uint32_t x, uint32_t y, uint32_t z) { put(FMA, {x, y, z, a}); }
+    uint32_t one() { return konst(1.0); }
+    uint32_t minus_one() { return konst(-1.0); }
+    uint32_t neg_zero() { return konst(-0.0); }
+    uint32_t zero() { return konst(0.0); }
+    uint32_t param(uint32_t p) const { return kSlots + p; }
+    uint32_t param_adj(uint32_t p) const { return kSlots + P + p; }
+
+    // a value loaded from memory: taken from its slot by the placeholder
+    uint32_t load(bool ckpt, uint32_t imm, bool late_row = false) {
+        const uint32_t v = vreg();
+        loads.push_back({uint32_t(ops.size()), v, ckpt, imm, ckpt ? stored_at.at(imm) : 0, late_row});
+        fma(v, 0, one(), neg_zero());
+        return v;
+    }
+    void store(uint32_t reg, uint32_t row) {
+        if (stored_at.size() <= row) stored_at.resize(row + 1, 0);
+        stored_at[row] = uint32_t(ops.size());
+        put(CKST, {reg}, row);
+    }
+
+    // register of a static slot negated
+    uint32_t negated(uint32_t s) {
+        s = I.rep[s];
+        if (I.kind[s] == K_CONST) return konst(-t.consts[t.ops[s].imm]);
+        const uint32_t p = t.ops[s].imm;
+        auto it = neg_param.find(p);
+        return it != neg_param.end() ? it->second : kNone;
+    }
+
+    template <class F>
+    void forward_op(uint32_t k, F operand, uint32_t dst) {
+        const TapeOp &o = t.ops[k];
+        switch (o.code) {
+        case tp::ADD: case tp::SUB: case tp::MUL: {
+            if (I.fmul[k]) {
+                const uint32_t m = I.fmul[k] - 1;
+                const bool first = I.rep[o.a] == m;
+                const uint32_t z = operand(first ? o.b : o.a);
+                uint32_t x = operand(t.ops[m].a), y = operand(t.ops[m].b);
+                if (o.code == tp::SUB) {   // z - x*y, one factor static
+                    if (I.is_static(t.ops[m].a))
+                        x = negated(t.ops[m].a);
+                    else
+                        y = negated(t.ops[m].b);
+                }
+                fma(dst, x, y, z);
+                return;
+            }
+            const uint32_t a = operand(o.a), b = operand(o.b);
+            if (o.code == tp::ADD) fma(dst, a, one(), b);
+            else if (o.code == tp::SUB) fma(dst, b, minus_one(), a);
+            else fma(dst, a, b, neg_zero());
+            return;
+        }
+        case tp::NEG: fma(dst, operand(o.a), minus_one(), neg_zero()); return;
+        case tp::SELECT:
+            put(SEL, {operand(o.a), operand(o.b), operand(o.c), operand(o.d), dst});
+            return;
+        default: break;
+        }
+        switch (o.code) {
+        case tp::DIV: put(DIV, {operand(o.a), operand(o.b), dst}); return;
+        case tp::POW: put(POW, {operand(o.a), operand(o.b), dst}); return;
+        case tp::EXP: put(EXP, {operand(o.a), dst}); return;
+        case tp::LOG: put(LOGC, {operand(o.a), dst}); return;
+        case tp::SQRT: put(SQRTC, {operand(o.a), dst}); return;
+        case tp::SIN: put(SIN, {operand(o.a), dst}); return;
+        case tp::COS: put(COS, {operand(o.a), dst}); return;
+        case tp::ABS: put(ABS, {operand(o.a), dst}); return;
+        default: throw std::logic_error("unknown tape op in the wide scheduler");
+        }
+    }
+
+    uint32_t fwd_operand(uint32_t s) {
+        s = I.rep[s];
+        switch (I.kind[s]) {
+        case K_CONST: return konst(t.consts[t.ops[s].imm]);
+        case K_PARAM: return param(t.ops[s].imm);
+        case K_OBS:
+            if (fval[s] == kNone) fval[s] = load(false, 8 * t.ops[s].imm);
+            return fval[s];
+        default: return fval[s];
+        }
+    }
+
+    uint32_t rev_operand(uint32_t s, uint32_t j) {
+        s = I.rep[s];
+        if (I.kind[s] == K_CONST || I.kind[s] == K_PARAM) return fwd_operand(s);
+        if (I.kind[s] == K_COMP && B.resident[s]) return fval[s];
+        if (rval_of[s] == j + 1) return rval[s];
+        if (I.kind[s] != K_OBS && row_of[s] != j + 1) throw std::logic_error("value read outside its segment");
+        set_rval(s, j, I.kind[s] == K_OBS ? load(false, 8 * t.ops[s].imm) : load(true, row[s]));
+        return rval[s];
+    }
+    void set_rval(uint32_t s, uint32_t j, uint32_t v) {
+        rval[s] = v;
+        rval_of[s] = j + 1;
+    }
+
+    // register of a target's adjoint; *first: its first contribution
+    uint32_t target(uint32_t s, bool *first) {
+        *first = false;
+        if (I.kind[s] == K_PARAM) return param_adj(t.ops[s].imm);
+        if (I.kind[s] != K_COMP || !I.active[s]) return kNone;
+        if (adj[s] == kNone) {
+            adj[s] = vreg();
+            *first = true;
+        }
+        return adj[s];
+    }
+
+    // +0 in register r: an earlier micro-op near by that clears none does it,
+    // else one of its own (a zero adjoint contributes nothing)
+    void clear(uint32_t r) {
+        for (size_t i = ops.size(), n = 0; i-- > rev_begin && n < kLookBack; ++n)
+            if ((ops[i].cls == DUAL || ops[i].cls == SELADJ || ops[i].cls == DIVADJ || ops[i].cls == ACCD) &&
+                ops[i].r[1] == kSink) {
+                ops[i].r[1] = r;
+                return;
+            }
+        put(DUAL, {zero(), r, one(), kSink, one(), kSink});
+    }
+    size_t rev_begin = 0;
+
+    // a1 += g * y1, a2 += g * y2 where g != 0
+    void dual(uint32_t g, uint32_t a1, bool f1, uint32_t y1, uint32_t a2, bool f2, uint32_t y2) {
+        if (a1 == kNone && a2 == kNone) return;
+        uint32_t zr = kSink;
+        if (a1 == kNone) a1 = kSink, y1 = one();
+        if (a2 == kNone) a2 = kSink, y2 = one();
+        if (f1) zr = a1;
+        if (f2) {
+            if (zr != kSink) clear(a2);
+            else zr = a2;
+        }
+        put(DUAL, {g, zr, y1, a1, y2, a2});
+    }
+    // a, or +0 for a first contribution
+    uint32_t base(uint32_t a, bool first) { return first ? zero() : a; }
+
+    void reverse_op(uint32_t k, uint32_t j) {
+        const TapeOp &o = t.ops[k];
+        const uint32_t g = adj[k];
+        if (g == kNone) throw std::logic_error("adjoint rule laid out before any contribution to it");
+        auto v = [&](uint32_t s) { return rev_operand(s, j); };
+        bool f1 = false, f2 = false;
+        switch (o.code) {
+        case tp::ADD: case tp::SUB: {
+            const uint32_t a1 = target(o.a, &f1), a2 = target(o.b, &f2);
+            dual(g, a1, f1, one(), a2, f2, o.code == tp::ADD ? one() : minus_one());
+            return;
+        }
+        case tp::MUL: {
+            const uint32_t A = I.takes_adjoint(o.b) ? v(o.a) : 0, Bv = I.takes_adjoint(o.a) ? v(o.b) : 0;
+            const uint32_t a1 = target(o.a, &f1), a2 = target(o.b, &f2);
+            dual(g, a1, f1, Bv, a2, f2, A);
+            return;
+        }
+        case tp::NEG: {
+            const uint32_t a1 = target(o.a, &f1);
+            dual(g, a1, f1, minus_one(), kNone, false, 0);
+            return;
+        }
+        case tp::EXP: {
+            const uint32_t Z = v(k), a1 = target(o.a, &f1);
+            dual(g, a1, f1, Z, kNone, false, 0);
+            return;
+        }
+        case tp::DIV: {
+            const uint32_t Bv = v(o.b), Z = I.takes_adjoint(o.b) ? v(k) : 0;
+            uint32_t a1 = target(o.a, &f1), a2 = target(o.b, &f2);
+            if (a2 == kNone) {
+                if (a1 != kNone) put(ACCD, {g, f1 ? a1 : kSink, Bv, a1, g});
+                return;
+            }
+            if (a1 == kNone) a1 = kSink;
+            uint32_t zr = f1 ? a1 : kSink;
+            if (f2) {
+                if (zr != kSink) clear(a2);
+                else zr = a2;
+            }
+            put(DIVADJ, {g, zr, Bv, a1, Z, a2});
+            return;
+        }
+        case tp::POW: {
+            const uint32_t A = v(o.a), Bv = I.takes_adjoint(o.a) ? v(o.b) : 0, Z = v(k);
+            const uint32_t a1 = target(o.a, &f1);
+            if (a1 != kNone) {   // ((g * b) * z) / a
+                const uint32_t t1 = vreg(), t2 = vreg();
+                fma(t1, g, Bv, neg_zero());
+                fma(t2, t1, Z, neg_zero());
+                put(ACCD, {g, f1 ? a1 : kSink, A, a1, t2});
+            }
+            const uint32_t a2 = target(o.b, &f2);
+            if (a2 != kNone) {   // (g * z) * ln a
+                const uint32_t t3 = vreg();
+                fma(t3, g, Z, neg_zero());
+                put(ACCPOW, {g, A, t3, base(a2, f2), a2});
+            }
+            return;
+        }
+        case tp::LOG: case tp::SIN: case tp::COS: case tp::ABS: {
+            const uint32_t A = v(o.a), a1 = target(o.a, &f1);
+            if (a1 == kNone) return;
+            const uint32_t cls = o.code == tp::LOG ? ACCLOG : o.code == tp::SIN ? ACCSIN : o.code == tp::COS ? ACCCOS : ACCABS;
+            put(cls, {g, A, base(a1, f1), a1});
+            return;
+        }
+        case tp::SQRT: {
+            const uint32_t A = v(o.a), Z = v(k), a1 = target(o.a, &f1);
+            if (a1 != kNone) put(ACCSQRT, {g, A, Z, base(a1, f1), a1});
+            return;
+        }
+        case tp::SELECT: {
+            const uint32_t A = v(o.a), Bv = v(o.b);
+            uint32_t a1 = target(o.c, &f1), a2 = target(o.d, &f2);
+            if (a1 == kNone && a2 == kNone) return;
+            if (a1 == kNone) a1 = kSink;
+            if (a2 == kNone) a2 = kSink;
+            uint32_t zr = f1 ? a1 : kSink;
+            if (f2) {
+                if (zr != kSink) clear(a2);
+                else zr = a2;
+            }
+            put(SELADJ, {g, zr, A, Bv, a1, a2});
+            return;
+        }
+        default:
+            throw std::logic_error("unknown tape op in the wide reverse scheduler");
+        }
+    }
+
+    // ---- values that only the loss needs
+    // The recompute policy forms a value twice: in the forward sweep and in its
+    // segment's reverse sweep.  Where nothing the reverse sweep starts from
+    // depends on it (terms of a sum: only the loss reads them), the forward
+    // sweep leaves it out, the reverse sweep stores the last such values that
+    // it recomputes, and the loss is formed from them at the end, by the same
+    // operations in the same order.  Done where the operations left out cost
+    // more than the rows' stores and loads (kRowCost each).
+    static constexpr uint32_t kRowCost = 110;
+    std::vector<uint8_t> in_forward;                    // computed by the forward sweep
+    std::vector<uint8_t> late;                          // computed after the reverse sweep
+    std::unordered_map<uint32_t, uint32_t> late_row;    // value -> row it is stored to for the end
+    void plan_late() {
+        in_forward.assign(N, 1);
+        late.assign(N, 0);
+        if (!with_grad || B.save_reads || I.kind[t.loss] != K_COMP) return;
+        std::vector<uint8_t> need(N, 0), recomputed(N, 0);
+        for (const auto &v : B.livein)
+            for (uint32_t s : v) need[s] = 1;
+        for (uint32_t s = 0; s < N; ++s) need[s] = need[s] || (B.resident[s] && B.comp_live(s));
+        for (uint32_t k = N; k-- > 0;)
+            if (need[k] && I.kind[k] == K_COMP) I.for_operands(k, [&](uint32_t s) { need[s] = 1; });
+        for (const auto &v : B.recomp)
+            for (uint32_t s : v) recomputed[s] = 1;
+        // from the loss back: what is formed at the end, what is loaded
+        std::vector<uint8_t> end(N, 0);
+        std::vector<uint32_t> rows;
+        end[I.rep[t.loss]] = 1;
+        for (uint32_t k = N; k-- > 0;) {
+            if (!end[k] || I.kind[k] != K_COMP) continue;
+            if (B.resident[k]) continue;
+            if (recomputed[k] || need[k]) {
+                rows.push_back(k);
+                continue;
+            }
+            late[k] = 1;
+            I.for_operands(k, [&](uint32_t s) { end[s] = 1; });
+        }
+        uint64_t saved = 0;
+        for (uint32_t k = 0; k < N; ++k)
+            if (B.comp_live(k) && I.rep[k] == k && !need[k] && !late[k]) saved += class_cost(class_of(k));
+        if (saved <= uint64_t(kRowCost) * rows.size()) {
+            late.assign(N, 0);
+            return;
+        }
+        for (uint32_t k = 0; k < N; ++k) in_forward[k] = need[k];
+        for (uint32_t k : rows) late_row[k] = n_rows++;
+    }
+    // class of a value's operation
+    uint32_t class_of(uint32_t k) const {
+        switch (t.ops[k].code) {
+        case tp::DIV: return DIV;
+        case tp::POW: return POW;
+        case tp::EXP: return EXP;
+        case tp::LOG: return LOGC;
+        case tp::SQRT: return SQRTC;
+        case tp::SIN: return SIN;
+        case tp::COS: return COS;
+        case tp::ABS: return ABS;
+        case tp::SELECT: return SEL;
+        default: return FMA;
+        }
+    }
+
+    void run() {
+        const uint32_t m = uint32_t(B.cuts.size());
+        // static registers: parameters, their adjoints, the sink, constants
+        kSink = kSlots + P + (with_grad ? P : 0);
+        kConst0 = kSink + 1;
+        fval.assign(N, kNone);
+        adj.assign(N, kNone);
+        rval.assign(N, 0);
+        rval_of.assign(N, 0);
+        row.assign(N, 0);
+        row_of.assign(N, 0);
+        n_rows = 0;
+        for (uint32_t j = 0; with_grad && j < m; ++j) {
+            first_row.push_back(n_rows);
+            n_rows += uint32_t(B.livein[j].size());
+        }
+        plan_late();
+        const bool late_loss = !late_row.empty();
+        // negated parameters that folded differences multiply by
+        for (uint32_t k = 0; k < N; ++k) {
+            if (!I.fmul[k] || t.ops[k].code != tp::SUB) continue;
+            const TapeOp &mo = t.ops[I.fmul[k] - 1];
+            const uint32_t s = I.rep[I.is_static(mo.a) ? mo.a : mo.b];
+            if (I.kind[s] != K_PARAM || neg_param.count(t.ops[s].imm)) continue;
+            const uint32_t r = vreg();
+            neg_param[t.ops[s].imm] = r;
+            fma(r, param(t.ops[s].imm), minus_one(), neg_zero());
+        }
+        std::unordered_map<uint32_t, std::vector<uint32_t>> saves_of;   // save policy: rows of each stored value
+        if (with_grad && B.save_reads)
+            for (uint32_t j = 0; j < m; ++j)
+                for (uint32_t i = 0; i < B.livein[j].size(); ++i) saves_of[B.livein[j][i]].push_back(first_row[j] + i);
+        uint32_t next_cut = 1;
+        auto fwd = [&](uint32_t s) { return fwd_operand(s); };
+        for (uint32_t k = 0; k < N; ++k) {
+            if (with_grad && !B.save_reads)
+                while (next_cut < m && B.cuts[next_cut] == k) {
+                    for (uint32_t i = 0; i < B.livein[next_cut].size(); ++i)
+                        store(fval[B.livein[next_cut][i]], first_row[next_cut] + i);
+                    ++next_cut;
+                }
+            if (!B.comp_live(k) || I.rep[k] != k || !in_forward[k]) continue;
+            const uint32_t dst = vreg();
+            forward_op(k, fwd, dst);
+            fval[k] = dst;
+            auto lr = late_row.find(k);
+            if (lr != late_row.end()) store(dst, lr->second);
+            if (with_grad && B.save_reads) {
+                auto it = saves_of.find(k);
+                if (it != saves_of.end())
+                    for (uint32_t r : it->second) store(dst, r);
+            }
+        }
+        if (!late_loss) put(STLOSS, {fwd_operand(t.loss)});
+        if (with_grad) {
+            rev_begin = ops.size();
+            bool f;
+            const uint32_t seed = target(t.loss, &f);
+            if (seed != kNone) {
+                if (f) fma(seed, one(), one(), neg_zero());
+                else fma(seed, one(), one(), seed);   // the loss is a parameter
+            }
+            for (uint32_t j = m; j-- > 0;) {
+                for (uint32_t i = 0; i < B.livein[j].size(); ++i) {
+                    row[B.livein[j][i]] = first_row[j] + i;
+                    row_of[B.livein[j][i]] = j + 1;
+                }
+                for (uint32_t s : B.recomp[j]) {
+                    if (I.kind[s] == K_OBS) continue;   // loaded where first read
+                    auto opnd = [&](uint32_t x) { return rev_operand(x, j); };
+                    const uint32_t dst = vreg();
+                    forward_op(s, opnd, dst);
+                    set_rval(s, j, dst);
+                    auto lr = late_row.find(s);
+                    if (lr != late_row.end() && !in_forward[s] && !(lr->second < stored_at.size() && stored_at[lr->second]))
+                        store(dst, lr->second);
+                }
+                for (uint32_t k : B.revops[j]) reverse_op(k, j);
+            }
+            for (uint32_t p = 0; p < P; ++p) put(STGRAD, {param_adj(p)}, 8 * p);
+            if (late_loss) {
+                // the observations read at the end are loaded anew, the values
+                // of the forward sweep (residents apart) are gone
+                for (uint32_t k = 0; k < N; ++k)
+                    if (!(I.kind[k] == K_COMP && B.resident[k])) fval[k] = kNone;
+                auto opnd = [&](uint32_t s) {
+                    s = I.rep[s];
+                    if (I.kind[s] == K_COMP && fval[s] == kNone) fval[s] = load(true, late_row.at(s), true);
+                    return fwd_operand(s);
+                };
+                for (uint32_t k = 0; k < N; ++k) {
+                    if (!late[k]) continue;
+                    const uint32_t dst = vreg();
+                    forward_op(k, opnd, dst);
+                    fval[k] = dst;
+                }
+                put(STLOSS, {opnd(t.loss)});
+            }
+        }
+        put(END, {});
+        n_static = (with_grad ? 2 : 1) * P + 1 + uint32_t(consts.size());
+    }
+    uint32_t n_rows = 0;
+};
+
+// Checkpoint slots per half that a program uses: a recomputing program
+// restores a few rows per segment and is short of registers; a saving one
+// restores every value a rule reads and has registers to spare.  The rows the
+// loss is formed from at the end come one after the other with little work
+// between them, and few registers are live by then: they use all slots.
+uint32_t ck_slots(bool save_reads) { return save_reads ? kCkSlots : 4; }
+
+// Loads issued ahead: the loads of each kind (observations, checkpoint rows)
+// go in batches of up to half its slots.  While the values of one batch are
+// used the next one is in flight: it is issued when the first value of the
+// batch before is taken, or when the last value of the batch before that has
+// left its slot, if later.  The first value taken of a batch waits for it.  A
+// value whose last reader is near is read from its slot directly (its
+// placeholder goes).
+// *late_at: the op from which on every checkpoint slot may be in use.
+std::vector<WOp> place_loads(const Lower &W, uint32_t ck_cap, uint32_t *late_at) {
+    const uint32_t n = uint32_t(W.ops.size());
+    std::vector<uint32_t> last(W.n_virtual, 0);
+    for (uint32_t i = 0; i < n; ++i)
+        for (uint32_t q = 0; q < W.ops[i].n; ++q)
+            if (W.ops[i].r[q] >= kVirtual) last[W.ops[i].r[q] - kVirtual] = i;
+    struct At {
+        std::vector<WOp> before, after;   // of an op
+    };
+    std::unordered_map<uint32_t, At> at;
+    std::vector<uint8_t> drop(n, 0), marked(n, 0);     // marked: in `at`
+    std::vector<uint32_t> alias(W.n_virtual, kNone);   // virtual register -> slot
+    std::unordered_map<uint32_t, uint32_t> slot_at;    // placeholder -> slot
+    std::vector<WOp> head;                             // issued at the program's start
+    for (int kind = 0; kind < 2; ++kind) {
+        const bool ckpt = kind == 1;
+        const uint32_t size = ckpt ? kCkSlots : kObsSlots;
+        std::vector<const Lower::Load *> q;
+        for (const auto &l : W.loads)
+            if (l.ckpt == ckpt) q.push_back(&l);
+        uint32_t done[2] = {kUnsetTime, kUnsetTime};   // last use of the values of the batch in each half
+        // batches: a row is stored before its batch's first value is taken
+        std::vector<size_t> begin{0};
+        for (size_t i = 0; i < q.size(); ++i) {
+            const Lower::Load &f = *q[begin.back()];
+            const uint32_t cap = !ckpt ? kObsSlots : f.late ? kCkSlots : ck_cap;
+            if (i - begin.back() == cap || q[i]->after >= f.at || q[i]->late != f.late) begin.push_back(i);
+        }
+        begin.push_back(q.size());
+        for (size_t nb = 0, half = 0; nb + 1 < begin.size() && !q.empty(); ++nb, half ^= 1) {
+            const size_t b = begin[nb];
+            const uint32_t c = uint32_t(begin[nb + 1] - b);
+            const uint32_t slot0 = (ckpt ? 2 * kObsSlots : 0) + uint32_t(half) * size;
+            // every value of the batch leaves its slot before the first value
+            // of the half's next batch is taken
+            const uint32_t limit = nb + 3 < begin.size() ? q[begin[nb + 2]]->at : n;
+            std::vector<WOp> issue;
+            uint32_t end_of_batch = 0, stored = 0;
+            for (uint32_t i = 0; i < c; ++i) {
+                const Lower::Load &l = *q[b + i];
+                const uint32_t slot = slot0 + size - c + i;   // a short batch enters its block late
+                WOp u;
+                u.cls = uint8_t((ckpt ? LDK0 : LDO0) + half);
+                u.imm = l.imm;
+                u.late = l.late;
+                issue.push_back(u);
+                stored = std::max(stored, l.after);
+                const uint32_t end = last[l.reg - kVirtual];
+                if (end - l.at <= kSlotHold && end < limit) {
+                    alias[l.reg - kVirtual] = slot;
+                    drop[l.at] = 1;
+                    end_of_batch = std::max(end_of_batch, end);
+                } else {
+                    slot_at[l.at] = slot;
+                    at[l.at];   // (marked below)
+                    end_of_batch = std::max(end_of_batch, l.at);
+                }
+            }
+            // Issued when the first value of the batch before is taken, when the
+            // half's last values have left it, and (checkpoint rows) when the
+            // rows have been stored, whichever is last; the first two batches
+            // of observations at the program's start.
+            std::vector<WOp> *dst = &head;
+            uint32_t after = nb >= 2 ? done[half] : 0;
+            if (ckpt) after = std::max(after, stored);
+            if (nb >= 2 || ckpt) {
+                const uint32_t first_before = nb >= 1 ? q[begin[nb - 1]]->at : 0;
+                dst = nb >= 1 && after < first_before ? &at[first_before].before : &at[after].after;
+            }
+            dst->insert(dst->end(), issue.begin(), issue.end());
+            WOp w;
+            w.cls = WAIT;
+            auto &before = at[q[b]->at].before;
+            before.insert(before.begin(), w);
+            done[half] = end_of_batch;
+        }
+    }
+    std::vector<WOp> out;
+    out.reserve(n + W.loads.size() * 2);
+    *late_at = UINT32_MAX;
+    bool pending = false;   // loads issued since the last wait
+    auto add = [&](const WOp &u) {
+        if (u.cls == WAIT && !pending) return;
+        if (u.cls == WAIT) pending = false;
+        if (u.cls >= LDK0 && u.cls <= LDO1) pending = true;
+        if (u.late && *late_at == UINT32_MAX) *late_at = uint32_t(out.size());
+        out.push_back(u);
+    };
+    for (const WOp &u : head) add(u);
+    for (const auto &a : at) marked[a.first] = 1;
+    for (uint32_t i = 0; i < n; ++i) {
+        const At *here = marked[i] ? &at.at(i) : nullptr;
+        if (here)
+            for (const WOp &u : here->before) add(u);
+        if (!drop[i]) {
+            WOp u = W.ops[i];
+            if (here) {
+                auto s = slot_at.find(i);
+                if (s != slot_at.end()) u.r[0] = s->second;
+            }
+            for (uint32_t q = 0; q < u.n; ++q)
+                if (u.r[q] >= kVirtual && alias[u.r[q] - kVirtual] != kNone) u.r[q] = alias[u.r[q] - kVirtual];
+            out.push_back(u);
+        }
+        if (here)
+            for (const WOp &u : here->after) add(u);
+    }
+    return out;
+}
+
+// Linear scan: every virtual register to the lowest register free over its
+// whole life.  A register read for the last time by a micro-op may be the one
+// it writes at its end.  `spare`: registers below the statics that are free
+// (load slots the program does not use); `early`: those free for lives that
+// end before op late_at.  Returns the registers used.
+uint32_t place_registers(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t n_static,
+                         const std::vector<uint32_t> &spare, const std::vector<uint32_t> &early, uint32_t late_at) {
+    std::vector<uint32_t> first(n_virtual, kUnsetTime), last(n_virtual, 0);
+    for (uint32_t i = 0; i < ops.size(); ++i) {
+        const WOp &u = ops[i];
+        const char *role = roles(u.cls);
+        for (uint32_t q = 0; q < u.n; ++q) {
+            if (u.r[q] < kVirtual) continue;
+            const uint32_t v = u.r[q] - kVirtual;
+            const uint32_t when = 2 * i + (role[q] == 'd' ? 1 : 0);
+            if (first[v] == kUnsetTime) first[v] = when;
+            last[v] = std::max(last[v], when);
+        }
+    }
+    std::vector<uint32_t> order;
+    for (uint32_t v = 0; v < n_virtual; ++v)
+        if (first[v] != kUnsetTime) order.push_back(v);
+    std::sort(order.begin(), order.end(),
+              [&](uint32_t a, uint32_t b) { return first[a] != first[b] ? first[a] < first[b] : a < b; });
+    std::vector<uint32_t> reg(n_virtual, 0);
+    std::priority_queue<uint32_t, std::vector<uint32_t>, std::greater<uint32_t>> free_regs;
+    for (uint32_t r : spare) free_regs.push(r);
+    std::vector<uint32_t> free_early(early.rbegin(), early.rend());
+    std::vector<uint8_t> is_early(kSlots, 0);
+    for (uint32_t r : early) is_early[r] = 1;
+    using End = std::pair<uint32_t, uint32_t>;   // (last, register)
+    std::priority_queue<End, std::vector<End>, std::greater<End>> busy;
+    uint32_t next = kSlots + n_static;
+    for (uint32_t v : order) {
+        while (!busy.empty() && busy.top().first < first[v]) {
+            const uint32_t r = busy.top().second;
+            if (r < kSlots && is_early[r]) free_early.push_back(r);
+            else free_regs.push(r);
+            busy.pop();
+        }
+        uint32_t r;
+        if (!free_early.empty() && last[v] / 2 < late_at) {
+            r = free_early.back();
+            free_early.pop_back();
+        } else if (free_regs.empty()) {
+            r = next++;
+        } else {
+            r = free_regs.top();
+            free_regs.pop();
+        }
+        reg[v] = r;
+        busy.push({last[v], r});
+    }
+    for (WOp &u : ops)
+        for (uint32_t q = 0; q < u.n; ++q)
+            if (u.r[q] >= kVirtual) u.r[q] = reg[u.r[q] - kVirtual];
+    return next;
+}
+
+// words of one micro-op
+void encode(const WOp &u, std::vector<uint32_t> *out) {
+    uint32_t q = 0, word = 0, halves = 0;
+    for (const char *c = roles(u.cls); *c; ++c) {
+        if (*c == 'i') {
+            out->push_back(u.imm);
+            continue;
+        }
+        const uint32_t h = *c == '-' ? 0u
+                                     : 2 * u.r[q++] | (*c == 'u' ? kSrc : *c == 'm' ? kSrc | kDst : kDst);
+        word |= h << (16 * (halves & 1u));
+        if (halves++ & 1u) {
+            out->push_back(word);
+            word = 0;
+        }
+    }
+}
+
+// The program is read once, by every wave in turn, and its blocks are short:
+// a block's scalar loads are issued one block ahead, which hides an L2 hit
+// but not a miss.  So the waves also fetch the program into the L2 cache some
+// kPrefetch bytes ahead, where they wait for loads anyway (the fetch must not
+// be in flight at the next wait), or in a block of its own.
+void emit(const std::vector<WOp> &in, WideSchedule *S) {
+    std::vector<WOp> ops;
+    ops.reserve(in.size() + in.size() / 64 + 4);
+    uint64_t total = 4 * kBlockWords;
+    for (const WOp &u : in) total += 4 * kInfo[u.cls].words + 4;   // a header for every other micro-op
+    // blocks of consecutive micro-ops of one class
+    std::vector<std::pair<uint32_t, uint32_t>> blocks;   // (first, count)
+    uint64_t at = 4 * kBlockWords, fetched = 0;          // bytes laid out, bytes fetched ahead
+    auto fetch = [&](uint32_t cls) {
+        WOp u;
+        u.cls = uint8_t(cls);
+        u.imm = uint32_t(fetched);
+        fetched += kPrefetch;
+        return u;
+    };
+    if (total > 2 * kPrefetch) {   // (a shorter program is read before a fetch of it would help)
+        for (int i = 0; i < 2; ++i) ops.push_back(fetch(PF));
+        blocks.push_back({0, 2});
+        at += 4 * (2 * kInfo[PF].words + 2);
+    } else {
+        fetched = UINT64_MAX / 2;
+    }
+    for (uint32_t i = 0; i < in.size();) {
+        uint32_t n = 1;
+        while (n < kInfo[in[i].cls].max && i + n < in.size() && in[i + n].cls == in[i].cls) ++n;
+        const bool wait = in[i].cls == WAIT;
+        if (fetched < total && (wait ? at + 2 * kPrefetch > fetched : at + kPrefetch > fetched)) {
+            const uint32_t cls = wait ? WAITPF : PF;
+            blocks.push_back({uint32_t(ops.size()), 1});
+            ops.push_back(fetch(cls));
+            at += 4 * (kInfo[cls].words + 2);
+            if (wait) {
+                i += n;
+                continue;
+            }
+        }
+        blocks.push_back({uint32_t(ops.size()), n});
+        for (uint32_t q = 0; q < n; ++q) ops.push_back(in[i + q]);
+        at += 4 * (uint64_t(n) * kInfo[in[i].cls].words + 2);
+        i += n;
+    }
+    const uint32_t nb = uint32_t(blocks.size());
+    auto entry_of = [&](uint32_t b) {
+        return b < nb ? entry(ops[blocks[b].first].cls, blocks[b].second, b & 1) : 0u;
+    };
+    // where the words of each block are read from: a whole half ending with
+    // the block's headers
+    std::vector<uint32_t> start(nb);
+    uint64_t words = kBlockWords;
+    for (uint32_t b = 0; b < nb; ++b) {
+        words += uint64_t(blocks[b].second) * kInfo[ops[blocks[b].first].cls].words + 2;
+        if (words > 0x3FFFFFFFu) throw std::length_error("wide program beyond 32-bit offsets");
+        start[b] = uint32_t(4 * (words - kBlockWords));
+    }
+    auto start_of = [&](uint32_t b) { return start[std::min(b, nb - 1)]; };
+    S->code.assign(kBlockWords, 0);
+    S->code.reserve(words);
+    for (uint32_t b = 0; b < nb; ++b) {
+        for (uint32_t i = 0; i < blocks[b].second; ++i) encode(ops[blocks[b].first + i], &S->code);
+        S->code.push_back(entry_of(b + 1));
+        S->code.push_back(start_of(b + 2));
+        S->cost += kDispatchCost + uint64_t(blocks[b].second) * class_cost(ops[blocks[b].first].cls);
+    }
+    // what the fetches read past the program's end
+    S->code.resize(std::max<size_t>(S->code.size(), fetched < UINT64_MAX / 2 ? fetched / 4 : 0), 0);
+    S->first[0] = start_of(0);
+    S->first[1] = entry_of(0);
+    S->first[2] = start_of(1);
+    S->n_blocks = nb;
+    S->n_uops = ops.size();
+}
+
+}  // namespace
+
+WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads) {
+    WideSchedule none;
+    for (const TapeOp &o : t.ops) {
+        if (o.rows != 1 || o.cols != 1) return none;
+        switch (o.code) {
+        case tp::CONST: case tp::PARAM: case tp::OBS: case tp::ADD: case tp::SUB: case tp::MUL: case tp::DIV:
+        case tp::NEG: case tp::EXP: case tp::LOG: case tp::SQRT: case tp::SIN: case tp::COS: case tp::POW:
+        case tp::ABS: case tp::SELECT:
+            break;
+        default: return none;
+        }
+    }
+    if (kSlots + 2 * uint64_t(t.n_params) + 8 > kRegs || t.n_obs >= 1u << 29) return none;
+    Info I(t);
+    I.fold_static_subtrahend = true;
+    I.exact_revreads = true;
+    I.analyse();
+    uint64_t total = 0;
+    for (uint32_t k = 0; k < I.N; ++k)
+        if (I.kind[k] == K_COMP && I.vlive[k]) total++;
+    total = std::max<uint64_t>(total, 1);
+    // (a search over sizes needs the registers only; the chosen one is laid out)
+    auto trial = [&](uint64_t size, bool full = false) {
+        Builder B(I);
+        B.save_reads = save_reads;
+        B.resident.assign(I.N, 0);
+        B.res_off.assign(I.N, 0);
+        if (with_grad) {
+            B.set_cuts(B.choose_cuts(size));
+            B.plan(false);
+            B.choose_residents(2);
+            B.set_cuts(B.choose_cuts(size));
+            B.plan(true);
+        } else {
+            B.set_cuts({0});
+        }
+        Lower W(I, B, with_grad);
+        W.run();
+        WideSchedule S;
+        if (W.consts.size() > kRegs) return S;
+        const uint32_t ck_cap = ck_slots(save_reads);
+        uint32_t late_at;
+        std::vector<WOp> ops = place_loads(W, ck_cap, &late_at);
+        std::vector<uint32_t> spare, early;
+        bool obs[2] = {false, false}, ck[2] = {false, false};
+        for (const WOp &u : ops) {
+            if (u.cls == LDO0 || u.cls == LDO1) obs[u.cls - LDO0] = true;
+            if ((u.cls == LDK0 || u.cls == LDK1) && !u.late) ck[u.cls - LDK0] = true;
+        }
+        for (uint32_t half = 0; half < 2; ++half) {
+            for (uint32_t i = 0; i < kObsSlots && !obs[half]; ++i) spare.push_back(half * kObsSlots + i);
+            for (uint32_t i = 0; i < kCkSlots; ++i)
+                if (!ck[half] || i < kCkSlots - ck_cap)
+                    (late_at == UINT32_MAX ? spare : early).push_back(2 * kObsSlots + half * kCkSlots + i);
+        }
+        S.n_regs = place_registers(ops, W.n_virtual, W.n_static, spare, early, late_at);
+        S.n_ckpt_rows = W.n_rows;
+        S.n_segments = uint32_t(B.cuts.size());
+        S.consts = W.consts;
+        S.ok = S.n_regs <= kRegs && S.n_ckpt_rows < (1u << 31);
+        if (S.ok && full) emit(ops, &S);
+        return S;
+    };
+    if (!with_grad) return trial(0, true);
+    // The largest segment size that fits the register file (doubled or halved
+    // from a usual one, then bisection), and the size that cuts the trace
+    // evenly into as many segments (which cuts every step of a loop at the
+    // same point): the cheaper of the two.
+    if (trial(total).ok) return trial(total, true);   // the whole trace in one segment
+    uint64_t lo = std::min<uint64_t>(80, total), hi = 0;   // lo fits, hi does not
+    while (!trial(lo).ok) {
+        hi = lo;
+        lo /= 2;
+        if (lo < 4) return none;
+    }
+    while (!hi) {
+        if (trial(2 * lo).ok) lo *= 2;
+        else hi = 2 * lo;
+    }
+    while (hi - lo > std::max<uint64_t>(4, lo / 16)) {
+        const uint64_t mid = lo + (hi - lo) / 2;
+        (trial(mid).ok ? lo : hi) = mid;
+    }
+    WideSchedule best = trial(lo, true);
+    const uint64_t even = total / best.n_segments;
+    if (even > 0 && even != lo) {
+        WideSchedule alt = trial(even, true);
+        if (alt.ok && alt.cost < best.cost) best = std::move(alt);
+    }
+    return best;
+}
+
+}  // namespace ndvm

@@ -1,0 +1,54 @@
+"""Wide replay kernel on the GPU: every case at the edges of its format against
+the oracle (both policies, forward, ragged lane counts), and the static-scratch
+entry point in parts."""
+import numpy as np
+import pytest
+
+from parity import compare
+from wide_cases import cases
+from workloads import configs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def nd():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2607_03574_amd as m
+    return m
+
+
+@pytest.mark.parametrize("L", [1, 65])
+def test_cases_equal_oracle(nd, oracle_mod, L):
+    for name, code, obs, rows in cases():
+        if rows.shape[1] == 0:     # the binding takes no empty parameter rows
+            continue
+        p = np.ascontiguousarray(rows[np.arange(L) % len(rows)])
+        ol, og, _ = oracle_mod.run(code, p, obs)
+        t = nd.tape_build(code)
+        P, O = torch.tensor(p, device="cuda"), torch.tensor(obs, device="cuda")
+        for policy in (nd.POLICY_RECOMPUTE, nd.POLICY_SAVE):
+            print(name, L, policy, flush=True)
+            tape = nd.tape_upload(t, policy)
+            loss, grad = nd.grad(tape, P, O)
+            f = nd.forward(tape, P, O)
+            torch.cuda.synchronize()
+            assert torch.equal(f.isnan(), loss.isnan()) and torch.equal(f.nan_to_num(), loss.nan_to_num()), name
+            grads = (grad.cpu().numpy(), og) if og.size else (None, None)
+            compare(loss.cpu().numpy(), grads[0], ol, grads[1])
+
+
+def test_noalloc_in_parts_equals_grad(nd):
+    """A scalar launch whose rows exceed the static scratch array runs in parts
+    of its lanes (the last one ragged), with the results of one launch."""
+    w = configs.lotka_volterra(L=13007, T=1000)
+    tape = nd.tape_upload(nd.tape_build(w.bytecode))
+    p, o = torch.tensor(w.params, device="cuda"), torch.tensor(w.obs, device="cuda")
+    assert nd.workspace_bytes(tape, 13007, True) > nd.NOALLOC_SCRATCH_BYTES
+    l0, g0 = nd.grad(tape, p, o)
+    l1, g1 = torch.empty_like(l0), torch.empty_like(g0)
+    nd.grad_noalloc(tape, p, o, l1, g1)
+    torch.cuda.synchronize()
+    assert torch.equal(l0, l1) and torch.equal(g0, g1)

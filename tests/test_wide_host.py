@@ -1,0 +1,212 @@
+"""Wide replay kernel, no GPU: its scheduler's programs run on the host
+emulator against the oracle, and its machine code against the format (entry
+points, operand roles, registers of the library functions)."""
+import os
+import re
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import emu
+from conftest import ROOT
+from parity import compare
+from wide_cases import cases
+from workloads import configs
+
+nd = pytest.importorskip("paper_2607_03574_amd")
+CASES = cases()
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_programs_equal_oracle(oracle_mod, mode):
+    """Every case, forward only and both policies, by the strict bar."""
+    for name, code, obs, p in CASES:
+        got = emu.wide(nd.tape_build(code), p, obs, mode)
+        assert got is not None, name
+        ol, og, _ = oracle_mod.run(code, p, obs)
+        grads = (got[1], og) if mode and og.size else (None, None)
+        compare(got[0], grads[0], ol, grads[1])
+
+
+def test_same_bits_as_the_slot_programs():
+    for name, code, obs, p in CASES:
+        t = nd.tape_build(code)
+        for mode in (1, 2):
+            wl, wg, _ = emu.wide(t, p, obs, mode)
+            sl, sg, _ = emu.run(t, p, obs, save=mode == 2)
+            for a, b in ((wl, sl), (wg, sg)):
+                same = (a.view(np.int64) == b.view(np.int64)) | (np.isnan(a) & np.isnan(b))
+                assert same.all(), (name, mode, a, b)
+
+
+def test_segments_and_the_loss_formed_last():
+    """Cases that need several checkpoint segments, and sums whose terms the
+    forward sweep leaves out."""
+    w = configs.lotka_volterra(L=1, T=60)
+    _, _, st = emu.wide(nd.tape_build(w.bytecode), w.params, w.obs)
+    assert st["n_segments"] > 5 and st["n_ckpt_rows"] > 0
+    w = configs.exp_decay(L=1)
+    t = nd.tape_build(w.bytecode)
+    _, _, st = emu.wide(t, w.params, w.obs)
+    assert st["n_ckpt_rows"] >= 64     # each term's residual, for the sum at the end
+    fwd = emu.wide(t, w.params, w.obs, 0)[2]
+    assert fwd["n_ckpt_rows"] == 0
+
+
+def test_programs_left_to_the_slot_kernel():
+    w = configs.kalman(L=1, T=2)
+    assert emu.wide(nd.tape_build(w.bytecode), w.params, w.obs) is None      # matrices
+    from workloads.bytecode import Asm
+    A = Asm(50, 0)
+    A.param(0)
+    for i in range(1, 50):
+        A.param(i).mul()
+    assert emu.wide(nd.tape_build(A.halt().bytes()), np.ones((1, 50)), np.zeros(0)) is None   # parameters
+
+
+# ------------------------------------------------------------ machine code
+CSRC = os.path.join(ROOT, "paper_2607_03574_amd", "csrc")
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+ROLE = {"u": {"S"}, "d": {"D"}, "e": {"D"}, "m": {"S", "D"}, "-": set(), "i": set()}
+
+
+def _format():
+    hdr = open(os.path.join(CSRC, "wide.h")).read()
+    body = re.sub(r"//.*", "", re.search(r"enum Class : uint32_t \{(.*?)kClasses", hdr, re.S).group(1))
+    names = [x.split("=")[0].strip() for x in body.split(",") if x.strip()]
+    num = dict(kCkSlots="12", kObsSlots="4")
+    assert "kObsSlots = 4, kCkSlots = 12" in hdr and "kRegion = 1024" in hdr and "kFileBase = 48" in hdr
+    info = re.search(r"kInfo\[kClasses\] = \{(.*?)\};", hdr, re.S).group(1)
+    info = [tuple(int(num.get(x.strip(), x)) for x in t.split(",")) for t in re.findall(r"\{([^{}]*)\}", info)]
+    sch = open(os.path.join(CSRC, "wide_sched.cpp")).read()
+    roles = {}
+    for line in re.search(r"const char \*roles\(uint32_t cls\) \{(.*?)\n\}", sch, re.S).group(1).split(";"):
+        m = re.search(r'return "(.*?)"', line)
+        if m:
+            roles.update({n: m.group(1) for n in re.findall(r"case (\w+):", line)})
+    assert len(names) == len(info)
+    return list(zip(names, info)), roles
+
+
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    """Disassembly of the wide kernel: {address: text}, the functions' address
+    ranges by name, and the code base."""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("_b", os.path.join(ROOT, "paper_2607_03574_amd", "build.py"))
+    b = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(b)
+    if not os.path.exists(b.HIPCC) or not os.path.exists(OBJDUMP):
+        pytest.skip("no device compiler")
+    obj = str(tmp_path_factory.mktemp("wide") / "wide.o")
+    subprocess.run([b.HIPCC] + b.COMMON + b.DEVICE + b.WIDE + ["--cuda-device-only", "--no-gpu-bundle-output", "-c",
+                    os.path.join(CSRC, "wide.hip"), "-o", obj], check=True, capture_output=True)
+    text = subprocess.run([OBJDUMP, "-d", obj], check=True, capture_output=True, text=True).stdout
+    ins, fn, cur = {}, {}, None
+    for line in text.splitlines():
+        m = re.match(r"[0-9a-f]+ <(.*)>:", line)
+        if m:
+            cur = m.group(1)
+            fn[cur] = []
+        m = re.match(r"\s+(.*?)\s+// ([0-9A-F]+): ", line)
+        if m:
+            a = int(m.group(2), 16)
+            ins[a] = m.group(1)
+            fn[cur].append(a)
+    addrs = sorted(ins)
+    i = next(a for a in addrs if ins[a].startswith("s_getpc_b64 s[28:29]"))
+    j = addrs[addrs.index(i) + 1]
+    return ins, fn, j + int(ins[j].split(",")[-1], 16)
+
+
+def test_entry_points_start_micro_ops(code):
+    """Each class's code starts its micro-ops where the format says, reads the
+    words of the half it serves, and ends in that half's dispatch."""
+    ins, _, base = code
+    addrs = sorted(ins)
+    for c, (name, (words, most, size)) in enumerate(_format()[0]):
+        for half in range(2):
+            region = base + (2 * c + half) * 1024
+            end = 66 + 32 * half
+            for k in range(most):
+                at = region + k * size
+                assert at in ins, (name, half, k)
+                text = [ins[a] for a in addrs if at <= a < at + size]
+                used = {int(x) for t in text for x in re.findall(r"\bs(\d+)\b", t)} & set(range(36, 100))
+                first = end - (most - k) * words
+                assert used <= set(range(first, first + words)), (name, half, k, used)
+            after = [ins[a] for a in addrs if region + most * size <= a][:3]
+            if name == "END":
+                assert after[0].startswith("s_branch")
+            elif name == "WAIT":
+                assert after[0] == "s_waitcnt vmcnt(0)" and after[2] == f"s_add_u32 s100, s28, s{end}"
+            else:
+                assert after[0].startswith("s_waitcnt lgkmcnt(0)") and after[1] == f"s_add_u32 s100, s28, s{end}", name
+
+
+def test_operand_roles(code):
+    """The VGPR index applies to exactly the operands that name the file's base
+    register, with the role the micro-op's half word carries."""
+    ins, _, base = code
+    addrs = sorted(ins)
+    fmt, roles = _format()
+    for c, (name, (words, most, size)) in enumerate(fmt):
+        if name in ("WAIT", "END"):
+            continue
+        halves = []
+        for r in roles[name]:
+            halves += [r, "i"] if r == "i" else [r]
+        for half in range(2):
+            for k in range(most):
+                at = base + (2 * c + half) * 1024 + k * size
+                first = 66 + 32 * half - (most - k) * words
+                m0, on = None, True
+
+                def role(operand, high):
+                    return halves[2 * (int(operand[1:]) - first) + high]
+
+                for a in addrs:
+                    if not at <= a < at + size:
+                        continue
+                    op, _, rest = ins[a].partition(" ")
+                    o = [x.strip() for x in rest.split(",")]
+                    if op == "s_mov_b32" and o[0] == "m0":
+                        m0 = set() if o[1] == "0" else ROLE[role(o[1], 0)]
+                    elif op == "s_lshr_b32" and o[0] == "m0":
+                        m0 = ROLE[role(o[1], 1)]
+                    elif op == "s_lshr_b32" and o[0] == "vcc_lo":
+                        assert role(o[1], 1) == "d"
+                    elif op == "s_set_gpr_idx_off":
+                        on = False
+                    elif op == "s_set_gpr_idx_on":
+                        on, m0 = True, {"D"}
+                        assert "DST" in o[1] and (o[0] == "vcc_lo" or role(o[0], 0) == "d")
+                    elif op.startswith("v_") and on:
+                        dst = [] if op.startswith("v_cmp") else o[:1]
+                        src = o[2:] if op.startswith("v_div_scale") else o[1:]
+                        for i, x in [(-1, x) for x in dst] + list(enumerate(src)):
+                            m = re.match(r"-?v\[?(\d+)", x)
+                            if m:
+                                assert m0 is not None, (name, ins[a])
+                                indexed = "D" in m0 if i < 0 else i == 0 and "S" in m0
+                                assert (int(m.group(1)) in (48, 49)) == indexed, (name, ins[a], m0)
+
+
+def test_library_functions_keep_to_their_registers(code):
+    """The functions the interpreter calls use no scratch memory and stay below
+    the registers it holds across a call."""
+    ins, fn, _ = code
+    names = [f for f in fn if f.startswith("ndvm_wide_")]
+    assert len(names) == 13
+    for f in names:
+        for a in fn[f]:
+            t = ins[a]
+            assert "scratch" not in t and "buffer" not in t and "m0" not in t and "swappc" not in t, (f, t)
+            regs = re.findall(r"\b([sv])(?:\[(\d+):(\d+)\]|(\d+)\b)", t)
+            for kind, lo, hi, one in regs:
+                top = int(hi or one)
+                if kind == "s" and lo == "30":
+                    continue                      # the return address
+                assert top < (26 if kind == "s" else 40), (f, t)
