@@ -105,10 +105,12 @@ namespace {
 #define STLOSS_TEXT LO(0) MOV(T, F) "global_store_dwordx2 v[44:45], " T ", off\n"
 #define STGRAD_TEXT LO(0) MOV(T, F) "s_mov_b32 vcc_lo, s[wq+1]\ns_mov_b32 vcc_hi, 0\nv_lshl_add_u64 " U ", vcc, 0, v[46:47]\n" \
     "global_store_dwordx2 " U ", " T ", off\n"
-// call of a library function, its result to the register in half word d(k)
+// Call of a library function, past its first instruction: a function begins
+// with a wait for every outstanding load (4 bytes), which its arguments, all
+// computed here, do not need and which would end the loads issued ahead.
 #define CALL(f) \
-    "s_set_gpr_idx_off\ns_getpc_b64 s[100:101]\ns_add_u32 s100, s100, " f "@rel32@lo+4\n" \
-    "s_addc_u32 s101, s101, " f "@rel32@hi+12\ns_swappc_b64 s[30:31], s[100:101]\n"
+    "s_set_gpr_idx_off\ns_getpc_b64 s[100:101]\ns_add_u32 s100, s100, " f "@rel32@lo+8\n" \
+    "s_addc_u32 s101, s101, " f "@rel32@hi+16\ns_swappc_b64 s[30:31], s[100:101]\n"
 #define RESULT_LO(k) "s_set_gpr_idx_on s[wq+" #k "], 0x8\n" MOV(F, T)
 #define RESULT_HI(k) "s_lshr_b32 vcc_lo, s[wq+" #k "], 16\ns_set_gpr_idx_on vcc_lo, 0x8\n" MOV(F, T)
 #define CALL1(f) CLASS("", 10, 1, LO(0) MOV("v[0:1]", F) CALL(f) RESULT_HI(0))

@@ -195,12 +195,21 @@ def test_operand_roles(code):
 
 
 def test_library_functions_keep_to_their_registers(code):
-    """The functions the interpreter calls use no scratch memory and stay below
-    the registers it holds across a call."""
+    """The functions the interpreter calls use no scratch memory, stay below the
+    registers it holds across a call, and begin with the wait that the calls
+    skip (each call's target is a function's second instruction)."""
     ins, fn, _ = code
     names = [f for f in fn if f.startswith("ndvm_wide_")]
     assert len(names) == 13
+    addrs, entries = sorted(ins), set()
+    for i, a in enumerate(addrs):
+        if ins[a].startswith("s_swappc_b64"):
+            lo = next(x for x in reversed(addrs[:i]) if ins[x].startswith("s_add_u32 s100, s100,"))
+            d = int(ins[lo].split(",")[-1], 16)
+            entries.add(lo + (d - (1 << 32) if d >> 31 else d))
+    assert entries == {fn[f][1] for f in names}
     for f in names:
+        assert ins[fn[f][0]] == "s_waitcnt vmcnt(0) expcnt(0) lgkmcnt(0)" and fn[f][1] == fn[f][0] + 4
         for a in fn[f]:
             t = ins[a]
             assert "scratch" not in t and "buffer" not in t and "m0" not in t and "swappc" not in t, (f, t)
