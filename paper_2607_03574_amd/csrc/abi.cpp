@@ -26,7 +26,7 @@ hipError_t launch_replay(const LaunchArgs &A, const ProgStatic *d_table, const P
                          uint32_t r_lds, int variant, bool skips, int order, uint32_t slots,
                          hipStream_t stream);
 hipError_t launch_wide(const LaunchArgs &A, const wide::Prog *d_table, const wide::Prog &single, uint32_t n_prog,
-                       hipStream_t stream);
+                       uint32_t lds_bytes, hipStream_t stream);
 bool slots_supported(uint32_t S);
 size_t scratch_bytes();
 hipError_t launch_fold_points(const double *term, const double *tgrad, int64_t L, int64_t N, int64_t P,
@@ -116,7 +116,8 @@ struct DevProg {
     }
 };
 
-// A program of the wide kernel; it does not depend on the lane count.
+// A program of the wide kernel.  A scalar one does not depend on the lane
+// count; one with matrices is made for the LDS a wave may use.
 struct WideProg {
     WideSchedule meta;      // host copy of counts (code and constants released)
     void *buf = nullptr;    // device: code | constants
@@ -135,14 +136,15 @@ struct ndvm_tape {
     Tape tape;
     uint64_t tape_bytes = 0;
     uint32_t n_selects = 0;
+    bool wide_takes = false, matrices = false;   // the wide kernel has code for the tape; it has matrices
     int policy = NDVM_POLICY_RECOMPUTE;
     bool arms = false;   // NDVM_BRANCH_SKIP: branch arms behind wave skip tests
     std::mutex mu;
     std::map<uint32_t, std::unique_ptr<DevProg>> fwd;    // keyed by slot count
     std::map<uint64_t, std::unique_ptr<DevProg>> grad;   // keyed by (slot count, register budget)
     // programs of the wide kernel, null where it does not take the tape
-    std::unique_ptr<WideProg> wide_fwd, wide_grad;
-    bool wide_grad_tried = false;
+    std::unique_ptr<WideProg> wide_fwd;
+    std::map<uint32_t, std::unique_ptr<WideProg>> wide_grad;   // by wide_lds_rows
     std::set<uint32_t> sized;   // register budgets of the lane counts sized for gradients
 };
 
@@ -187,22 +189,40 @@ ndvm_status upload_program(Schedule &&S, const Tape &t, hipStream_t stream, std:
     return NDVM_OK;
 }
 
-// The wide kernel takes scalar programs without skippable branch arms whose
-// live values fit its register file; the slot kernel takes the others (its
-// slots hold matrices and spill, and it has the skip tests that a tape with
-// branches uploaded with NDVM_BRANCH_SKIP asks for).  Both give the same bits.
-// Slot kernel against wide kernel, ms a call: Lotka-Volterra (1000 steps,
-// 65,536 lanes) 7.36 against 3.46, saving (300 steps, 9,999 lanes) 5.75
-// against 1.23, losses alone (20,000 lanes) 7.91 against 0.65; logistic (500
-// steps, 4,096 lanes) 0.917 against 0.678; exponential decay (64 points, 256
-// lanes) 0.0558 against 0.0490; 1,024 random programs of 1,024 lanes 17.7
-// against 4.74.
-bool wide_candidate(const ndvm_tape *t) { return !(t->arms && t->n_selects > 0); }
+// The wide kernel takes programs whose live values fit its register file and
+// whose matrices, if any, fit LDS and are large enough for it (wide_pays); the
+// slot kernel takes the others (its registers spill, and it has the skip tests
+// that a tape with branches uploaded with NDVM_BRANCH_SKIP asks for).  Both give
+// the same bits.  Slot kernel against wide kernel, ms a call: Lotka-Volterra
+// (1000 steps, 65,536 lanes) 7.39 against 3.45, saving (300 steps, 9,999 lanes)
+// 5.75 against 1.23, losses alone (20,000 lanes) 7.93 against 0.65; logistic
+// (500 steps, 4,096 lanes) 0.916 against 0.678; exponential decay (64 points,
+// 256 lanes) 0.0557 against 0.0480; 1,024 random programs of 1,024 lanes 17.8
+// against 4.5; Kalman filter of four states (200 steps, 16,384 lanes) 6.93
+// against 4.20, saving 6.54 against 4.36, 80 steps on 1,003 lanes 2.13 against
+// 1.57, its losses alone (50 steps, 65,536 lanes) 2.02 against 0.85.
+bool wide_candidate(const ndvm_tape *t) { return t->wide_takes && !(t->arms && t->n_selects > 0); }
+
+// Matrix elements per lane that a wave may hold in LDS: four waves per CU
+// (320), one per SIMD; more for a launch of fewer waves; for one of more than
+// six waves per CU, half of it lets a second wave on each SIMD.  That is two
+// waves in 1.4 times the time of one, and worth shorter segments, up to that
+// cost.  (A Kalman filter of four states needs some 300.)
+constexpr uint32_t kWideLdsRows = 320;
+uint32_t wide_lds_rows(uint32_t slot_budget) {
+    return slot_budget < kWideLdsRows * 2 / 3 ? kWideLdsRows / 2 : std::max(kWideLdsRows, slot_budget);
+}
 
 // Wide schedule of a tape, or one that is not ok.
-WideSchedule wide_schedule_of(const ndvm_tape *t, bool with_grad) {
+WideSchedule wide_schedule_of(const ndvm_tape *t, bool with_grad, uint32_t lds_rows) {
     if (!wide_candidate(t)) return WideSchedule{};
-    return schedule_wide(t->tape, with_grad, t->policy == NDVM_POLICY_SAVE);
+    auto of = [&](uint32_t rows) { return schedule_wide(t->tape, with_grad, t->policy == NDVM_POLICY_SAVE, rows); };
+    WideSchedule S = of(std::max(kWideLdsRows, lds_rows));
+    if (lds_rows && lds_rows < kWideLdsRows && S.ok && S.lds_rows > lds_rows) {
+        WideSchedule half = of(lds_rows);
+        if (half.ok && half.cost * 7 < S.cost * 10) S = std::move(half);
+    }
+    return S;
 }
 
 // Copy a wide program to the device (S.ok).
@@ -233,6 +253,7 @@ ndvm_status upload_wide(WideSchedule &&S, const Tape &t, bool with_grad, hipStre
     w->prog.n_params = t.n_params;
     w->prog.n_consts = uint32_t(S.consts.size());
     w->prog.adjoints = with_grad;
+    w->prog.lds_bytes = S.matrices ? std::max(S.lds_rows, 4u) * wide::kLdsRow : 0;
     S.code = {};
     S.consts = {};
     w->meta = std::move(S);
@@ -240,20 +261,27 @@ ndvm_status upload_wide(WideSchedule &&S, const Tape &t, bool with_grad, hipStre
     return NDVM_OK;
 }
 
-// Wide gradient program of a tape (null: the slot kernel runs it), made and
-// copied at its first sizing call.  `pre`: the schedule, when the caller made
-// it already.
-ndvm_status wide_grad_program(ndvm_tape *tape, bool build, WideProg **out, WideSchedule *pre = nullptr) {
+// Wide gradient program of a tape for lds_rows (null: the slot kernel runs
+// it), made and copied at its first sizing call.  `pre`: the schedule, when the
+// caller made it already.
+ndvm_status wide_grad_program(ndvm_tape *tape, uint32_t lds_rows, bool build, WideProg **out,
+                              WideSchedule *pre = nullptr) {
+    *out = nullptr;
+    if (!tape->wide_takes) return NDVM_OK;
+    if (!tape->matrices) lds_rows = 0;
     std::lock_guard<std::mutex> lk(tape->mu);
-    if (!tape->wide_grad_tried && build) {
-        WideSchedule S = pre ? std::move(*pre) : wide_schedule_of(tape, true);
+    auto it = tape->wide_grad.find(lds_rows);
+    if (it == tape->wide_grad.end()) {
+        if (!build) return NDVM_OK;
+        WideSchedule S = pre ? std::move(*pre) : wide_schedule_of(tape, true, lds_rows);
+        std::unique_ptr<WideProg> w;
         if (S.ok) {
-            ndvm_status st = upload_wide(std::move(S), tape->tape, true, nullptr, &tape->wide_grad);
+            ndvm_status st = upload_wide(std::move(S), tape->tape, true, nullptr, &w);
             if (st != NDVM_OK) return st;
         }
-        tape->wide_grad_tried = true;
+        it = tape->wide_grad.emplace(lds_rows, std::move(w)).first;
     }
-    *out = tape->wide_grad.get();
+    *out = it->second.get();
     return NDVM_OK;
 }
 
@@ -428,7 +456,7 @@ int64_t lpad_of(int64_t L) { return (L + 63) / 64 * 64; }
 
 // Largest padded lane count of a wide launch (a row's bytes are a 32-bit
 // number there).
-constexpr int64_t kWideMaxLanes = (int64_t(1) << 29) - 64;
+constexpr int64_t kWideMaxLanes = (int64_t(1) << 27) - 64;
 // A wide launch of one wave must fit the static scratch array by itself, so
 // that any launch the array serves can be served in parts.
 bool wide_rows_fit(const WideProg &w) {
@@ -446,9 +474,9 @@ ndvm_status wide_grad_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, int6
     *out = nullptr;
     if (lpad_of(L) > kWideMaxLanes) return NDVM_OK;
     WideProg *w = nullptr;
-    ndvm_status st = wide_grad_program(tape, build, &w);
-    if (st != NDVM_OK || !w || !wide_rows_fit(*w)) return st;
     const uint32_t b = reg_budget(p, waves_of(L, n_prog, slot::kMaxSlots), slot::kMaxSlots);
+    ndvm_status st = wide_grad_program(tape, wide_lds_rows(b), build, &w);
+    if (st != NDVM_OK || !w || !wide_rows_fit(*w)) return st;
     std::lock_guard<std::mutex> lk(tape->mu);
     if (build) tape->sized.insert(b);
     if (!tape->sized.count(b)) {
@@ -461,8 +489,8 @@ ndvm_status wide_grad_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, int6
 }
 
 ndvm_status check_wide_launch(const LaunchArgs &A, const wide::Prog *table, const wide::Prog &single, uint32_t n_prog,
-                              hipStream_t stream) {
-    const hipError_t e = launch_wide(A, table, single, n_prog, stream);
+                              uint32_t lds_bytes, hipStream_t stream) {
+    const hipError_t e = launch_wide(A, table, single, n_prog, lds_bytes, stream);
     if (e != hipSuccess) {
         set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
         return NDVM_E_DEVICE;
@@ -528,6 +556,7 @@ struct ManyLaunch {
     const uint64_t *d_items = nullptr;   // work item per workgroup (xcd_items), or null
     uint32_t n_wg = 0;
     bool wide = false;      // every program runs on the wide kernel: d_table holds wide::Prog
+    uint32_t lds_bytes = 0; // of such a launch's workgroups
 };
 
 // Work items of a many-program launch laid out per XCD.  Each of MI355X's
@@ -580,36 +609,40 @@ ndvm_status wide_many(const ndvm_tape *const *tapes, int n_prog, const DevicePro
                       std::vector<WideProg *> *progs, bool *all) {
     *all = false;
     if (lpad_of(L) > kWideMaxLanes) return NDVM_OK;
+    // programs with matrices and without run on kernels of their own: a launch
+    // that mixes them, or with a program the wide kernel does not take, stays
+    // on the slot kernel
+    for (int q = 0; q < n_prog; ++q) {
+        if (!tapes[q]->wide_fwd || tapes[q]->matrices != tapes[0]->matrices) return NDVM_OK;
+    }
+    const uint32_t rows = wide_lds_rows(reg_budget(p, waves_of(L, n_prog, slot::kMaxSlots), slot::kMaxSlots));
+    const uint32_t key = n_prog && tapes[0]->matrices ? rows : 0;
     std::vector<ndvm_tape *> todo;
     if (build) {
         std::set<const ndvm_tape *> seen;
         for (int q = 0; q < n_prog; ++q) {
             ndvm_tape *t = const_cast<ndvm_tape *>(tapes[q]);
             std::lock_guard<std::mutex> lk(t->mu);
-            if (!t->wide_grad_tried && seen.insert(t).second) todo.push_back(t);
+            if (!t->wide_grad.count(key) && seen.insert(t).second) todo.push_back(t);
         }
-        // a program that cannot run there sends them all to the slot kernel:
-        // nothing is scheduled where the forward programs tell so already
-        for (int q = 0; q < n_prog; ++q)
-            if (!tapes[q]->wide_fwd) return NDVM_OK;
     }
     std::vector<WideSchedule> res(todo.size());
     std::vector<ndvm_status> code(todo.size(), NDVM_OK);
     std::vector<std::string> msg(todo.size());
-    for_all(todo.size(), [&](size_t i) { res[i] = wide_schedule_of(todo[i], true); }, &code, &msg);
+    for_all(todo.size(), [&](size_t i) { res[i] = wide_schedule_of(todo[i], true, key); }, &code, &msg);
     for (size_t i = 0; i < todo.size(); ++i) {
         if (code[i] != NDVM_OK) {
             set_error(msg[i]);
             return code[i];
         }
         WideProg *w;
-        ndvm_status st = wide_grad_program(todo[i], true, &w, &res[i]);
+        ndvm_status st = wide_grad_program(todo[i], key, true, &w, &res[i]);
         if (st != NDVM_OK) return st;
     }
     for (int q = 0; q < n_prog; ++q) {
         ndvm_tape *t = const_cast<ndvm_tape *>(tapes[q]);
         WideProg *w = nullptr;
-        ndvm_status st = wide_grad_program(t, false, &w);
+        ndvm_status st = wide_grad_program(t, key, false, &w);
         if (st != NDVM_OK) return st;
         if (!w || !wide_rows_fit(*w)) return NDVM_OK;
     }
@@ -642,6 +675,7 @@ ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bo
             t[q].trash_row = row + wide[q]->meta.n_ckpt_rows;
             row += wide_rows(*wide[q]);
             cost[q] = wide[q]->meta.cost;
+            out->lds_bytes = std::max(out->lds_bytes, wide[q]->prog.lds_bytes);
             key.push_back(tapes[q]->id);
             key.push_back((uint64_t(S) << 32) | b | uint64_t(1) << 63);
         }
@@ -687,7 +721,8 @@ ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bo
     if (n_prog == 0) return NDVM_OK;
     std::lock_guard<std::mutex> lk(g_table_mu);
     // per-XCD work items (single launches only: at most kMaxProgPerLaunch programs)
-    const int64_t per_wave = out->wide ? 64 : 64 / S;
+    const int64_t per_wave = out->wide && !out->lds_bytes ? 64 : 64 / S;
+    static_assert(wide::kMatLanes == 64 / slot::kMaxSlots, "lanes of a wave");
     const uint64_t blocks = uint64_t((L + per_wave - 1) / per_wave);
     std::vector<uint64_t> ikey = key;
     ikey.push_back(blocks);
@@ -816,6 +851,7 @@ static ndvm_status new_tape(const uint8_t *bytes, size_t len, int save, bool arm
     h->policy = save;
     h->arms = arms;
     for (const TapeOp &o : h->tape.ops) h->n_selects += o.code == tp::SELECT;
+    h->wide_takes = wide_takes(h->tape, &h->matrices) && wide_pays(h->tape);
     *out = std::move(h);
     return NDVM_OK;
 }
@@ -842,7 +878,7 @@ ndvm_status ndvm_tape_upload(const uint8_t *bytes, size_t len, int policy, void 
             return st;
         h->id = g_next_id++;
         // schedule the forward program now: scheduling limits surface at upload
-        WideSchedule ws = wide_schedule_of(h.get(), false);
+        WideSchedule ws = wide_schedule_of(h.get(), false, kWideLdsRows);
         if (ws.ok) {
             st = upload_wide(std::move(ws), h->tape, false, static_cast<hipStream_t>(stream), &h->wide_fwd);
         } else {
@@ -886,7 +922,7 @@ ndvm_status ndvm_tape_upload_many(const uint8_t *const *tapes, const size_t *len
                 msg[i] = get_error();
                 return;
             }
-            ww[i] = wide_schedule_of(hs[i].get(), false);
+            ww[i] = wide_schedule_of(hs[i].get(), false, kWideLdsRows);
             if (!ww[i].ok) fw[i] = schedule_forward_of(hs[i].get(), 4, fb);
         }, &code, &msg);
         for (int i = 0; i < n; ++i)
@@ -1050,7 +1086,8 @@ ndvm_status ndvm_forward(const ndvm_tape *tape, const double *params, int64_t L,
                 return NDVM_E_NOMEM;
             }
             const LaunchArgs A{obs, params, loss, loss, static_cast<double *>(ws), ld_p, 0, L, Lp, 0, 0};
-            return check_wide_launch(A, nullptr, tape->wide_fwd->prog, 1, static_cast<hipStream_t>(stream));
+            return check_wide_launch(A, nullptr, tape->wide_fwd->prog, 1, tape->wide_fwd->prog.lds_bytes,
+                                     static_cast<hipStream_t>(stream));
         }
         DevProg *fp;
         if ((st = fwd_program(const_cast<ndvm_tape *>(tape), S, static_cast<hipStream_t>(stream), &fp)) != NDVM_OK)
@@ -1092,15 +1129,16 @@ static ndvm_status static_workspace(size_t need, const char *who, void **ws, siz
 // A gradient launch of the wide kernel.  On the static scratch array, a
 // launch whose rows do not fit runs as several launches over parts of its
 // lanes, one after the other on `stream`: the slot kernel can need fewer rows
-// (its register budget is larger for few lanes, and it stores nothing for the
-// loss), and no launch that fitted the array with it is refused.
+// (its register budget is larger for few lanes, it stores nothing for the loss
+// and pads no matrix to quads), and no launch that fitted the array with it is
+// refused.  With matrices that is a factor of 4 at most.
 static ndvm_status wide_grad_launch(const WideProg &w, const double *params, int64_t L, int64_t ld_p,
                                     const double *obs, double *loss, double *grad, int64_t ld_g, void *ws,
                                     size_t ws_bytes, bool static_ws, void *stream, const char *who) {
     int64_t part = L;
     size_t need = size_t(wide_rows(w) * uint64_t(lpad_of(L)) * sizeof(double));
     if (static_ws) {
-        if (need > scratch_bytes()) {
+        if (need > scratch_bytes() && (!w.meta.matrices || need <= 4 * scratch_bytes())) {
             part = int64_t(scratch_bytes() / (wide_rows(w) * sizeof(double))) / 64 * 64;
             need = size_t(wide_rows(w) * uint64_t(part) * sizeof(double));
         }
@@ -1115,7 +1153,7 @@ static ndvm_status wide_grad_launch(const WideProg &w, const double *params, int
         const int64_t n = std::min(part, L - l0);
         const LaunchArgs A{obs, params ? params + l0 * ld_p : nullptr, loss + l0, grad ? grad + l0 * ld_g : nullptr,
                            static_cast<double *>(ws), ld_p, ld_g, n, lpad_of(n), 0, 0};
-        const ndvm_status st = check_wide_launch(A, nullptr, w.prog, 1, static_cast<hipStream_t>(stream));
+        const ndvm_status st = check_wide_launch(A, nullptr, w.prog, 1, w.prog.lds_bytes, static_cast<hipStream_t>(stream));
         if (st != NDVM_OK) return st;
     }
     return NDVM_OK;
@@ -1243,7 +1281,7 @@ ndvm_status ndvm_grad_points(const ndvm_tape *tape, const double *params, int64_
         LaunchArgs A{points, params, term, tgrad, wsd, ld_p, P, F, lpad_of(F), 0, 0, n_points, ld_pt};
         hipStream_t s = static_cast<hipStream_t>(stream);
         if (wp) {
-            st = check_wide_launch(A, nullptr, wp->prog, 1, s);
+            st = check_wide_launch(A, nullptr, wp->prog, 1, wp->prog.lds_bytes, s);
         } else {
             const uint32_t r_lds = std::min(dp->meta.n_regs, b);
             const bool spills = dp->meta.n_regs > r_lds;
@@ -1311,7 +1349,8 @@ ndvm_status ndvm_grad_many(const ndvm_tape *const *tapes, int n_prog, const doub
                 A.n_wg = ml.n_wg;
             }
             if (ml.wide)
-                st = check_wide_launch(A, static_cast<const wide::Prog *>(d_table) + q0, wide::Prog{}, uint32_t(nq), s);
+                st = check_wide_launch(A, static_cast<const wide::Prog *>(d_table) + q0, wide::Prog{}, uint32_t(nq),
+                                       ml.lds_bytes, s);
             else
                 st = check_stream_and_launch(A, static_cast<const ProgStatic *>(d_table) + q0, none, uint32_t(nq),
                                              r_launch, variant, ml.skips, ml.order, S, s);

@@ -312,35 +312,57 @@ int64_t ndvm_emu_program(const uint8_t *tape, size_t len, int with_grad, uint32_
  * the recompute policy, 2 with the save policy) and run its blocks for L lanes
  * on the host, micro-op by micro-op as the kernel does.  Reads of registers
  * never written, of load slots whose loads have not been waited for, and
- * registers, rows and indices out of range are faults.  stats (optional, 6
+ * registers, rows and indices out of range are faults.  stats (optional, 7
  * entries): registers, checkpoint rows, segments, blocks, micro-ops, estimated
- * cycles.  Returns 0, 1 for a tape the wide kernel does not take, an
- * ndvm_status from parsing (negated), or 100 + fault code.
+ * cycles, matrix elements.  Returns 0, 1 for a tape the wide kernel does not take, an
+ * ndvm_status from parsing (negated), or 100 + fault code.  lds_rows: matrix
+ * elements a wave may hold.
  */
-int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, const double *params, int64_t L, int64_t ld_p,
+int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, uint32_t lds_rows, const double *params, int64_t L, int64_t ld_p,
                   const double *obs, int64_t n_obs, double *loss, double *grad, int64_t ld_g, uint64_t *stats) {
     using namespace wide;
     Tape t;
     ndvm_status st = parse_tape(tape, len, &t);
     if (st != NDVM_OK) return -int(st);
-    const WideSchedule S = schedule_wide(t, mode != 0, mode == 2);
+    const WideSchedule S = schedule_wide(t, mode != 0, mode == 2, lds_rows);
     if (!S.ok) return 1;
     if (stats) {
-        const uint64_t v[6] = {S.n_regs, S.n_ckpt_rows, S.n_segments, S.n_blocks, S.n_uops, S.cost};
-        for (int i = 0; i < 6; ++i) stats[i] = v[i];
+        const uint64_t v[8] = {S.n_regs, S.n_ckpt_rows, S.n_segments, S.n_blocks, S.n_uops, S.cost, S.lds_rows, wide_pays(t)};
+        for (int i = 0; i < 8; ++i) stats[i] = v[i];
     }
+    const uint32_t NS = S.matrices ? 4 : 1, n_rows = S.n_ckpt_rows / NS;   // threads per lane, checkpoint rows of one store
+    struct Lds {
+        std::vector<double> *v;
+        int *fault;
+        double ld(uint32_t p, uint32_t e) const { return at(p, e); }
+        void st(uint32_t p, uint32_t e, double x) const { at(p, e) = x; }
+        double &at(uint32_t p, uint32_t e) const {
+            const uint32_t i = p / kLdsRow + e;
+            if (p % kLdsRow || i >= v->size()) {
+                *fault = *fault ? *fault : 8;
+                return (*v)[0];
+            }
+            return (*v)[i];
+        }
+    };
     for (int64_t l = 0; l < L; ++l) {
-        std::vector<double> reg(kRegs, NAN), ck(S.n_ckpt_rows, NAN);
-        std::vector<uint8_t> state(kRegs, 0);   // 1 written, 2 load in flight
+        std::vector<double> reg(kRegs * NS, NAN), ck(S.n_ckpt_rows, NAN), lds(std::max(4u, S.lds_rows), NAN);
+        std::vector<uint8_t> state(kRegs * NS, 0);   // 1 written, 2 load in flight
         int fault = 0;
+        uint32_t sl = 0;                             // thread of the lane
+        const Lds mem{&lds, &fault};
+        uint32_t fault_cls = 0, cur_cls = 0;
         auto flag = [&](int c) {
-            if (!fault) fault = c;
+            if (!fault) fault = c, fault_cls = cur_cls;
         };
         uint32_t r0 = kSlots;
         auto init = [&](double v) {
             if (r0 >= kRegs) return flag(1);
-            reg[r0] = v;
-            state[r0++] = 1;
+            for (uint32_t i = 0; i < NS; ++i) {
+                reg[r0 * NS + i] = v;
+                state[r0 * NS + i] = 1;
+            }
+            ++r0;
         };
         for (uint32_t p = 0; p < t.n_params; ++p) init(params[l * ld_p + p]);
         for (uint32_t p = 0; mode && p < t.n_params; ++p) init(0.0);
@@ -352,7 +374,7 @@ int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, const double *param
             return (h & 0xFFu) / 2 < kRegs ? (h & 0xFFu) / 2 : 0;
         };
         auto get = [&](uint32_t h, uint32_t roles) {
-            const uint32_t r = idx(h, roles);
+            const uint32_t r = idx(h, roles) * NS + sl;
             if (state[r] != 1) flag(3);
             return reg[r];
         };
@@ -360,8 +382,8 @@ int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, const double *param
             const uint32_t r = idx(h, roles);
             // statics are never overwritten, parameter adjoints and the sink apart
             if (r >= kSlots && r < r0 && (r < kSlots + t.n_params || r > sink)) flag(4);
-            reg[r] = v;
-            state[r] = 1;
+            reg[r * NS + sl] = v;
+            state[r * NS + sl] = 1;
         };
         const uint32_t SD = kSrc | kDst;
         uint64_t start = S.first[0], next = S.first[2];   // where this block's and the next one's words are read
@@ -390,7 +412,61 @@ int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, const double *param
                     const double o = get(h, SD);
                     if (on) set(h, SD, o + v);
                 };
-                switch (cls) {
+                cur_cls = cls;
+                const uint32_t w3 = info.words > 3 ? w[3] : 0, M = (w3 & 7u), K = (w3 >> 3) & 7u, N = (w3 >> 6) & 7u;
+                const bool fst = w3 & kFirstBit;
+                bool matrix = true;
+                sl = 0;
+                switch (cls) {   // one matrix for the lane's threads
+                case MM:
+#define ROW(k, n) mm_row<k, n>(mem, a, c, d, r)
+                    for (uint32_t r = 0; r < M; ++r) NDVM_WIDE_SIDES(K, N, ROW)
+#undef ROW
+                    break;
+                case MMA: {
+                    const bool on = any_of(mem, a, M * N);
+                    auto gate = [&](bool) { return on; };
+#define ROW(k, n) mma_row<k, n>(mem, a, c, d, r, fst, gate)
+                    for (uint32_t r = 0; r < M; ++r) NDVM_WIDE_SIDES(K, N, ROW)
+#undef ROW
+                    break;
+                }
+                case MMB:
+#define ROW(m, n) mmb_row<m, n>(mem, a, c, d, r, K, fst)
+                    for (uint32_t r = 0; r < K; ++r) NDVM_WIDE_SIDES(M, N, ROW)
+#undef ROW
+                    break;
+                case VADD: for (uint32_t e = 0; e < 4; ++e) vadd(mem, a, c, d, e, w3); break;
+                case VACC: for (uint32_t e = 0; e < 4; ++e) vacc(mem, a, d, e, w3); break;
+                case TRANS: for (uint32_t e = 0; e < 4; ++e) transpose(mem, a, d, e, w3); break;
+                case TRANSACC: for (uint32_t e = 0; e < 4; ++e) transpose_acc(mem, a, d, e, w3); break;
+                case INV2: inv2(mem, a, d); break;
+                case INV2ACC: inv2_acc(mem, a, c, d, w3); break;
+                case VSCALE: for (uint32_t e = 0; e < 4; ++e) vscale(mem, a, c, get(w3 & 0xFFFFu, kSrc), e, d); break;
+                case VACCS: {
+                    const bool on = any_of(mem, a, d & 511u);
+                    for (uint32_t e = 0; e < 4; ++e)
+                        vaccs(mem, a, c, get(w3 & 0xFFFFu, kSrc), e, d & 511u, d & kFirstBit, on);
+                    break;
+                }
+                case LOGDETACC: logdet2_acc(mem, a, c, get(w3 & 0xFFFFu, kSrc), d); break;
+                default: matrix = false;
+                }
+                for (sl = 0; sl < NS && !matrix; ++sl) switch (cls) {
+                case STE: mem.st(c, 0, get(al, kSrc)); break;
+                case STE4: mem.st(c, sl, get(al, kSrc)); break;
+                case LDE: set(cl, kDst, mem.ld(a, 0)); break;
+                case CKSTM:
+                    if (c >= n_rows) flag(6);
+                    else ck[NS * c + sl] = mem.ld(a, sl);
+                    break;
+                case SDOT: set(w3 >> 16, kDst, sdot(mem, a, c, d)); break;
+                case DET2: {
+                    double v[4];
+                    load4(mem, a, v);
+                    set(w3 >> 16, kDst, det2(v));
+                    break;
+                }
                 case FMA: {
                     const double x = get(al, kSrc), y = get(ah, kSrc), z = get(cl, kSrc), p = x * y;
                     set(ch, kDst, p + z);
@@ -440,19 +516,19 @@ int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, const double *param
                     break;
                 }
                 case CKST:
-                    if (c >= S.n_ckpt_rows) flag(6);
-                    else ck[c] = get(al, kSrc);
+                    if (c >= n_rows) flag(6);
+                    else ck[NS * c + sl] = get(al, kSrc);
                     break;
                 case LDK0: case LDK1: case LDO0: case LDO1: {
                     const bool k = cls == LDK0 || cls == LDK1;
                     const uint32_t half = k ? cls - LDK0 : cls - LDO0;
                     const uint32_t slot = (k ? 2 * kObsSlots + half * kCkSlots : half * kObsSlots) + skipped + i;
-                    if (k ? a >= S.n_ckpt_rows : (a % 8 || a / 8 >= uint32_t(n_obs))) {
+                    if (k ? a >= n_rows : (a % 8 || a / 8 >= uint32_t(n_obs))) {
                         flag(6);
                         break;
                     }
-                    reg[slot] = k ? ck[a] : obs[a / 8];
-                    state[slot] = 2;
+                    reg[slot * NS + sl] = k ? ck[NS * a + sl] : obs[a / 8];
+                    state[slot * NS + sl] = 2;
                     break;
                 }
                 case PF: case WAITPF:
@@ -461,7 +537,7 @@ int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, const double *param
                     [[fallthrough]];
                 case WAIT:
                     for (uint32_t s = 0; s < kSlots; ++s)
-                        if (state[s] == 2) state[s] = 1;
+                        if (state[s * NS + sl] == 2) state[s * NS + sl] = 1;
                     break;
                 case STLOSS: loss[l] = get(al, kSrc); break;
                 case STGRAD:
@@ -490,7 +566,7 @@ int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, const double *param
         }
         if (fault) {
             char m[96];
-            std::snprintf(m, sizeof m, "wide emulator fault %d in lane %lld", fault, (long long)l);
+            std::snprintf(m, sizeof m, "wide emulator fault %d in lane %lld, class %u", fault, (long long)l, fault_cls);
             set_error(m);
             return 100 + fault;
         }

@@ -36,6 +36,7 @@ struct Info {
     // constant or a parameter (the wide kernel has no x*y - z; it computes
     // z - x*y as z + (-x)*y with a register holding the negated factor).
     bool fold_static_subtrahend = false;
+    bool fold_scalars_only = false;
 
     explicit Info(const Tape &tape) : t(tape), N(uint32_t(tape.ops.size())), P(tape.n_params) {}
 
@@ -159,6 +160,7 @@ struct Info {
         for (uint32_t c = 0; c < N; ++c) {
             const TapeOp &o = t.ops[c];
             if (!vlive[c] || rep[c] != c || kind[c] != K_COMP || (o.code != tp::ADD && o.code != tp::SUB)) continue;
+            if (fold_scalars_only && nel[c] != 1) continue;
             const bool restricted = fold_static_subtrahend && o.code == tp::SUB;
             for (uint32_t side = restricted ? 1 : 0; side < 2; ++side) {
                 const uint32_t m = rep[side == 0 ? o.a : o.b], other = rep[side == 0 ? o.b : o.a];

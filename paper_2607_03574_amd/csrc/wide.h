@@ -1,9 +1,11 @@
-// Device program format of the wide replay kernel ("wide" programs): scalar
-// programs, one thread per lane.  Produced by the wide scheduler from a
-// validated tape; not part of the public interface.
+// Device program format of the wide replay kernel ("wide" programs).  Produced
+// by the wide scheduler from a validated tape; not part of the public interface.
 //
-// A wave of 64 threads replays 64 lanes.  Each thread holds its lane's whole
-// register file in vector registers: file register r is v[kFileBase + 2r :
+// Scalar programs run one thread per lane, 64 lanes a wave.  Programs with
+// small matrices run four threads per lane, 16 lanes a wave (thread t serves
+// lane t % 16): the four hold the same scalars and share the work of a matrix
+// (a row each, or every fourth element).  Each thread holds its lane's whole
+// register file of scalars in vector registers: file register r is v[kFileBase + 2r :
 // kFileBase + 2r + 1], reached through the VGPR index mode (M0 holds the
 // wave-uniform index), so an operand costs one scalar move and no memory
 // access, and a result is ready for the next micro-op a few cycles later.
@@ -23,6 +25,12 @@
 // code base), and where the kBlockWords words of block b + 2 start (byte
 // offset in the program).
 //
+// Matrices live in LDS, row-major: element e of a matrix at byte offset o is
+// at o + 128 e of the wave's LDS, 8 bytes for each of the 16 lanes; a matrix
+// takes a multiple of four elements.  A checkpoint row holds one value per
+// lane; of a program with matrices, four (thread t stores and loads element
+// t / 16 of a quad, or the scalar).
+//
 // A micro-op's operands are half words: bits 0-7 twice the register number,
 // bits 12-15 the operand roles the index applies to (kSrc: source 0, kDst:
 // destination), the form M0 takes.
@@ -41,6 +49,12 @@ namespace wide {
 // functions, then four addresses.
 constexpr uint32_t kFileBase = 48;
 constexpr uint32_t kRegs = (256 - kFileBase) / 2;
+// With matrices: 96 for temporaries and functions, four addresses, two LDS
+// addresses.
+constexpr uint32_t kMatFileBase = 106;
+constexpr uint32_t kMatRegs = (256 - kMatFileBase) / 2;
+constexpr uint32_t kMatLanes = 16;
+constexpr uint32_t kLdsRow = 8 * kMatLanes;   // bytes of one matrix element of a wave
 // Load slots: registers the loads of observations (two halves of kObsSlots
 // from 0) and of checkpoint rows (two halves of kCkSlots behind them) write.
 // The slots a program does not use are ordinary registers.
@@ -86,6 +100,26 @@ enum Class : uint32_t {
     ACCSQRT,   // d = x != 0 && y > 1e-8 ? w + x / (2 z) : w
     ABS,       // d = |x|: x, d
     END,       // the program's end
+    // ---- matrices (A, B, D, G, T: LDS byte offsets; i: immediate, see
+    // wide_exec.h; a one-element matrix is a scalar register)
+    STE,       // D[0] = x: x, - | D
+    STE4,      // D[t / 16] = x: x, - | D
+    LDE,       // d = A[0]: A | d, -
+    CKSTM,     // checkpoint row = A[0 .. 3]: A | row
+    MM,        // D = A B: A | B | D | i
+    MMA,       // T += G B^T: G | B | T | i
+    MMB,       // T += A^T G: A | G | T | i
+    VADD,      // D = A +/- B: A | B | D | i
+    VACC,      // T += +/- G: G | - | T | i
+    TRANS,     // D = A^T: A | - | D | i
+    TRANSACC,  // T += G^T: G | - | T | i
+    INV2,      // D = A^-1: A | - | D | i
+    INV2ACC,   // T -= Z^T G Z^T: Z | G | T | i
+    VSCALE,    // D = x A: A | D | i | x, sink
+    VACCS,     // T += x G: G | T | i | x, sink
+    SDOT,      // d = sum of G A: G | A | i | x, d
+    DET2,      // d = det A: A | A | i | x, d
+    LOGDETACC, // T += x A^-T where det A > 1e-8: A | T | i | x, sink
     kClasses
 };
 // words per micro-op, micro-ops per block, code bytes per micro-op
@@ -97,7 +131,9 @@ constexpr ClassInfo kInfo[kClasses] = {
     {1, kCkSlots, 28}, {1, kCkSlots, 28}, {1, kObsSlots, 28}, {1, kObsSlots, 28}, {0, 1, 0}, {1, 1, 40},
     {1, 2, 36}, {1, 1, 16}, {2, 8, 32},
     {1, 10, 48}, {1, 10, 48}, {1, 10, 48}, {1, 10, 48}, {1, 10, 48}, {2, 10, 52}, {2, 10, 64}, {2, 10, 64},
-    {2, 10, 64}, {2, 10, 64}, {3, 10, 68}, {3, 10, 68}, {1, 10, 48}, {0, 1, 0}};
+    {2, 10, 64}, {2, 10, 64}, {3, 10, 68}, {3, 10, 68}, {1, 10, 48}, {0, 1, 0},
+    {2, 15, 20}, {2, 15, 20}, {2, 15, 28}, {2, 15, 44}, {4, 7, 48}, {4, 7, 48}, {4, 7, 48}, {4, 7, 48}, {4, 7, 48},
+    {4, 7, 48}, {4, 7, 48}, {4, 7, 48}, {4, 7, 48}, {4, 7, 60}, {4, 7, 60}, {4, 7, 60}, {4, 7, 60}, {4, 7, 60}};
 constexpr uint32_t kPrefetch = 4096;   // one line of 64 bytes per thread
 constexpr uint32_t kRegion = 1024;   // code bytes reserved per class and half
 constexpr uint32_t kBlockWords = 32;
@@ -116,6 +152,7 @@ struct Prog {
     uint32_t first[3];       // where the words of block 0 start, entry of block 0, where those of block 1 start
     uint32_t n_params, n_consts;
     uint32_t adjoints;       // the program has parameter adjoints (n_params registers after the parameters)
+    uint32_t lds_bytes;      // matrices: LDS of one wave (0: a scalar program)
 };
 
 }  // namespace wide
@@ -128,10 +165,17 @@ struct WideSchedule {
     uint32_t first[3] = {0, 0, 0};
     uint64_t n_uops = 0;
     uint64_t cost = 0;            // estimated cycles of a lone wave
+    bool matrices = false;
+    uint32_t lds_rows = 0;        // matrix elements in LDS
 };
 
 // Wide program of a tape: forward only, or forward and reverse (save_reads as
-// schedule_grad).
-WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads);
+// schedule_grad).  lds_rows: matrix elements a wave may hold in LDS.
+WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads, uint32_t lds_rows);
+// Whether a tape is one of matrices and scalars that the wide kernel takes,
+// and whether it has matrices.
+bool wide_takes(const Tape &t, bool *matrices);
+// Whether it is faster there than on the slot kernel.
+bool wide_pays(const Tape &t);
 
 }  // namespace ndvm

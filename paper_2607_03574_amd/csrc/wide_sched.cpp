@@ -16,6 +16,7 @@
 
 #include "plan.h"
 #include "slot.h"
+#include "wide_exec.h"
 
 namespace ndvm {
 
@@ -28,11 +29,14 @@ struct WOp {
     bool late = false;     // a load of a row the loss is formed from
     uint32_t imm = 0;      // row, observation index or output index
     uint32_t r[6] = {};    // registers in the order of the class's half words
+    uint8_t n_mem = 0;
+    uint32_t m[3] = {}, e[3] = {};   // matrices and elements in the order of the class's offset words
 };
 
 // Half words of a class and their roles: 'u' read, 'd' written after the
 // reads, 'e' written before the last read, 'm' read and written, '-' unused;
-// the immediate's word ('i') stands for two halves.
+// the immediate's word ('i') stands for two halves.  Whole words: 'R' offset of
+// a matrix read, 'W' written, 'M' read and written, 'z' nothing.
 const char *roles(uint32_t cls) {
     switch (cls) {
     case FMA: return "uuud";
@@ -48,6 +52,17 @@ const char *roles(uint32_t cls) {
     case EXP: case SIN: case COS: case LOGC: case SQRTC: case ABS: return "ud";
     case ACCSIN: case ACCCOS: case ACCLOG: case ACCABS: return "uuud";
     case ACCPOW: case ACCSQRT: return "uuuud-";
+    case STE: case STE4: return "u-W";
+    case LDE: return "Rd-";
+    case CKSTM: return "Ri";
+    case MM: case VADD: return "RRWi";
+    case MMA: case MMB: case INV2ACC: return "RRMi";
+    case VACC: case TRANSACC: return "RzMi";
+    case TRANS: case INV2: return "RzWi";
+    case VSCALE: return "RWiud";
+    case VACCS: case LOGDETACC: return "RMiud";
+    case SDOT: return "RRiud";
+    case DET2: return "Rziud";
     default: return "";
     }
 }
@@ -80,6 +95,11 @@ uint32_t class_cost(uint32_t cls) {
     case POW: return 1100;
     case ACCLOG: case ACCSQRT: case SQRTC: return 280;
     case PF: case WAITPF: return 30;
+    case STE: case STE4: return 30;
+    case LDE: case CKSTM: return 110;
+    case MM: case MMA: case MMB: return 430;
+    case VADD: case VACC: case TRANS: case TRANSACC: case VSCALE: case VACCS: return 300;
+    case INV2: case INV2ACC: case LOGDETACC: case SDOT: case DET2: return 450;
     default: return 150;
     }
 }
@@ -114,7 +134,40 @@ struct Lower {
     std::vector<Load> loads;
     std::vector<uint32_t> stored_at;   // op that stores each checkpoint row
 
-    Lower(const Info &info, Builder &b, bool grad) : I(info), B(b), t(info.t), with_grad(grad), N(info.N), P(info.P) {}
+    const bool mats;                                   // a program with matrices
+    std::vector<uint32_t> mem_size;                    // elements of each matrix (padded to quads)
+
+    Lower(const Info &info, Builder &b, bool grad, bool matrices)
+        : I(info), B(b), t(info.t), with_grad(grad), N(info.N), P(info.P), mats(matrices) {}
+
+    // ---- matrices: values and adjoints of more than one element are named by
+    // matrix numbers where scalars are named by registers
+    uint32_t mem(uint32_t nel) {
+        mem_size.push_back((nel + 3) / 4 * 4);
+        return uint32_t(mem_size.size() - 1);
+    }
+    uint32_t place_of(uint32_t s) { return I.nel[s] == 1 ? vreg() : mem(I.nel[s]); }
+    void put_m(uint32_t cls, std::initializer_list<uint32_t> m, uint32_t imm = 0, std::initializer_list<uint32_t> r = {},
+               uint32_t element = 0) {
+        put(cls, r, imm);
+        WOp &u = ops.back();
+        for (uint32_t x : m) u.m[u.n_mem++] = x;
+        u.e[0] = element;
+    }
+    // the matrix operand s (a scalar put into a matrix of its own)
+    uint32_t as_matrix(uint32_t nel, uint32_t where) {
+        if (nel > 1) return where;
+        const uint32_t m = mem(1);
+        put_m(STE, {m}, 0, {where});
+        return m;
+    }
+    uint32_t element(uint32_t m, uint32_t e) {
+        const uint32_t v = vreg();
+        put_m(LDE, {m}, 0, {v}, e);
+        return v;
+    }
+    uint32_t quads(uint32_t nel) const { return (nel + 3) / 4; }
+    uint32_t rows_of(uint32_t s) const { return mats ? quads(I.nel[s]) : 1; }
 
     uint32_t konst(double v) {
         uint64_t bits;
@@ -146,10 +199,13 @@ struct Lower {
         fma(v, 0, one(), neg_zero());
         return v;
     }
-    void store(uint32_t reg, uint32_t row) {
-        if (stored_at.size() <= row) stored_at.resize(row + 1, 0);
-        stored_at[row] = uint32_t(ops.size());
-        put(CKST, {reg}, row);
+    void store(uint32_t s, uint32_t where, uint32_t row) {
+        for (uint32_t q = 0; q < rows_of(s); ++q, ++row) {
+            if (stored_at.size() <= row) stored_at.resize(row + 1, 0);
+            stored_at[row] = uint32_t(ops.size());
+            if (I.nel[s] == 1) put(CKST, {where}, row);
+            else put_m(CKSTM, {where}, row, {}, 4 * q);
+        }
     }
 
     // register of a static slot negated
@@ -161,9 +217,62 @@ struct Lower {
         return it != neg_param.end() ? it->second : kNone;
     }
 
+    // a value with a matrix among its operands or as its result; false: none
+    template <class F>
+    bool forward_matrix(uint32_t k, F operand, uint32_t dst) {
+        const TapeOp &o = t.ops[k];
+        const uint32_t n = I.nel[k];
+        switch (o.code) {
+        case tp::MATMUL: {
+            const uint32_t a = as_matrix(I.nel[o.a], operand(o.a)), b = as_matrix(I.nel[o.b], operand(o.b));
+            const uint32_t d = n == 1 ? mem(1) : dst;
+            put_m(MM, {a, b, d}, mat_imm(t.ops[o.a].rows, t.ops[o.a].cols, t.ops[o.b].cols));
+            if (n == 1) put_m(LDE, {d}, 0, {dst});
+            return true;
+        }
+        case tp::ADD: case tp::SUB:
+            if (n == 1) return false;
+            put_m(VADD, {operand(o.a), operand(o.b), dst}, quads(n) | (o.code == tp::SUB ? kNegBit : 0u));
+            return true;
+        case tp::MUL: {
+            if (n == 1) return false;
+            const bool as = I.nel[o.a] == 1;
+            const uint32_t x = operand(as ? o.a : o.b);
+            put_m(VSCALE, {operand(as ? o.b : o.a), dst}, quads(n), {x, kSink});
+            return true;
+        }
+        case tp::TRANSPOSE:
+            if (n == 1) fma(dst, operand(o.a), one(), neg_zero());
+            else put_m(TRANS, {operand(o.a), dst}, mat_imm(t.ops[o.a].rows, t.ops[o.a].cols, 0));
+            return true;
+        case tp::PACK:
+            for (uint32_t i = 0; i < o.b; ++i) {
+                const uint32_t x = operand(t.aux[o.a + i]);
+                if (n == 1) fma(dst, x, one(), neg_zero());
+                else put_m(STE, {dst}, 0, {x}, i);
+            }
+            return true;
+        case tp::INDEX:
+            if (I.nel[o.a] == 1) fma(dst, operand(o.a), one(), neg_zero());
+            else put_m(LDE, {operand(o.a)}, 0, {dst}, o.imm);
+            return true;
+        case tp::INV:
+            put_m(INV2, {operand(o.a), dst});
+            return true;
+        case tp::LOGDET: {
+            const uint32_t d = vreg();
+            put_m(DET2, {operand(o.a)}, 0, {one(), d});
+            put(LOGC, {d, dst});
+            return true;
+        }
+        default: return false;
+        }
+    }
+
     template <class F>
     void forward_op(uint32_t k, F operand, uint32_t dst) {
         const TapeOp &o = t.ops[k];
+        if (mats && forward_matrix(k, operand, dst)) return;
         switch (o.code) {
         case tp::ADD: case tp::SUB: case tp::MUL: {
             if (I.fmul[k]) {
@@ -223,7 +332,13 @@ struct Lower {
         if (I.kind[s] == K_COMP && B.resident[s]) return fval[s];
         if (rval_of[s] == j + 1) return rval[s];
         if (I.kind[s] != K_OBS && row_of[s] != j + 1) throw std::logic_error("value read outside its segment");
-        set_rval(s, j, I.kind[s] == K_OBS ? load(false, 8 * t.ops[s].imm) : load(true, row[s]));
+        if (I.nel[s] == 1) {
+            set_rval(s, j, I.kind[s] == K_OBS ? load(false, 8 * t.ops[s].imm) : load(true, row[s]));
+        } else {
+            const uint32_t m = mem(I.nel[s]);
+            for (uint32_t q = 0; q < rows_of(s); ++q) put_m(STE4, {m}, 0, {load(true, row[s] + q)}, 4 * q);
+            set_rval(s, j, m);
+        }
         return rval[s];
     }
     void set_rval(uint32_t s, uint32_t j, uint32_t v) {
@@ -237,7 +352,7 @@ struct Lower {
         if (I.kind[s] == K_PARAM) return param_adj(t.ops[s].imm);
         if (I.kind[s] != K_COMP || !I.active[s]) return kNone;
         if (adj[s] == kNone) {
-            adj[s] = vreg();
+            adj[s] = place_of(s);
             *first = true;
         }
         return adj[s];
@@ -272,11 +387,108 @@ struct Lower {
     // a, or +0 for a first contribution
     uint32_t base(uint32_t a, bool first) { return first ? zero() : a; }
 
+    // The adjoint rule of an op with matrices; false: it has none.  Where the
+    // contribution is the adjoint itself no gate is needed: a zero changes no
+    // sum, which is never -0 (it starts at +0).
+    bool reverse_matrix(uint32_t k, uint32_t j, uint32_t g) {
+        const TapeOp &o = t.ops[k];
+        const uint32_t n = I.nel[k];
+        auto v = [&](uint32_t s) { return rev_operand(s, j); };
+        bool f1 = false, f2 = false;
+        auto first = [](bool f) { return f ? kFirstBit : 0u; };
+        // a += c for a scalar target
+        auto add = [&](uint32_t a, bool f, uint32_t c) { fma(a, c, one(), base(a, f)); };
+        switch (o.code) {
+        case tp::ADD: case tp::SUB: {
+            if (n == 1) return false;
+            const uint32_t a1 = target(o.a, &f1);
+            if (a1 != kNone) put_m(VACC, {g, a1}, quads(n) | first(f1));
+            const uint32_t a2 = target(o.b, &f2);
+            if (a2 != kNone) put_m(VACC, {g, a2}, quads(n) | first(f2) | (o.code == tp::SUB ? kNegBit : 0u));
+            return true;
+        }
+        case tp::MUL: {
+            if (n == 1) return false;
+            const bool as = I.nel[o.a] == 1;
+            const uint32_t sc = as ? o.a : o.b, ma = as ? o.b : o.a;
+            auto scalar = [&]() {
+                const uint32_t M = I.takes_adjoint(sc) ? v(ma) : 0, a = target(sc, &f1);
+                if (a == kNone) return;
+                const uint32_t c = vreg();
+                put_m(SDOT, {g, M}, n, {one(), c});
+                add(a, f1, c);
+            };
+            auto matrix = [&]() {
+                const uint32_t S = I.takes_adjoint(ma) ? v(sc) : 0, a = target(ma, &f2);
+                if (a != kNone) put_m(VACCS, {g, a}, n | first(f2), {S, kSink});
+            };
+            if (as) scalar(), matrix();
+            else matrix(), scalar();
+            return true;
+        }
+        case tp::MATMUL: {
+            const uint32_t imm = mat_imm(t.ops[o.a].rows, t.ops[o.a].cols, t.ops[o.b].cols);
+            const uint32_t G = as_matrix(n, g);
+            for (int side = 0; side < 2; ++side) {
+                const uint32_t x = side ? o.b : o.a, y = side ? o.a : o.b;
+                const uint32_t other = I.takes_adjoint(x) ? as_matrix(I.nel[y], v(y)) : 0;
+                const uint32_t a = target(x, &f1);
+                if (a == kNone) continue;
+                const bool sc = I.nel[x] == 1;
+                const uint32_t T = sc ? mem(1) : a, im = imm | first(sc || f1);
+                if (side) put_m(MMB, {other, G, T}, im);
+                else put_m(MMA, {G, other, T}, im);
+                if (sc) add(a, f1, element(T, 0));
+            }
+            return true;
+        }
+        case tp::TRANSPOSE: {
+            const uint32_t a = target(o.a, &f1);
+            if (a == kNone) return true;
+            if (n == 1) add(a, f1, g);
+            else put_m(TRANSACC, {g, a}, mat_imm(t.ops[o.a].rows, t.ops[o.a].cols, 0) | first(f1));
+            return true;
+        }
+        case tp::PACK:
+            for (uint32_t i = 0; i < o.b; ++i) {
+                const uint32_t a = target(t.aux[o.a + i], &f1);
+                if (a != kNone) add(a, f1, n == 1 ? g : element(g, i));
+            }
+            return true;
+        case tp::INDEX: {
+            const uint32_t a = target(o.a, &f1), ne = I.nel[o.a];
+            if (a == kNone) return true;
+            if (ne == 1) {
+                add(a, f1, g);
+                return true;
+            }
+            for (uint32_t i = 0; f1 && i < ne; ++i)
+                if (i != o.imm) put_m(STE, {a}, 0, {zero()}, i);
+            const uint32_t c = vreg();
+            fma(c, g, one(), f1 ? zero() : element(a, o.imm));
+            put_m(STE, {a}, 0, {c}, o.imm);
+            return true;
+        }
+        case tp::INV: {
+            const uint32_t Z = v(k), a = target(o.a, &f1);
+            if (a != kNone) put_m(INV2ACC, {Z, g, a}, first(f1));
+            return true;
+        }
+        case tp::LOGDET: {
+            const uint32_t A = v(o.a), a = target(o.a, &f1);
+            if (a != kNone) put_m(LOGDETACC, {A, a}, first(f1), {g, kSink});
+            return true;
+        }
+        default: return false;
+        }
+    }
+
     void reverse_op(uint32_t k, uint32_t j) {
         const TapeOp &o = t.ops[k];
         const uint32_t g = adj[k];
         if (g == kNone) throw std::logic_error("adjoint rule laid out before any contribution to it");
         auto v = [&](uint32_t s) { return rev_operand(s, j); };
+        if (mats && reverse_matrix(k, j, g)) return;
         bool f1 = false, f2 = false;
         switch (o.code) {
         case tp::ADD: case tp::SUB: {
@@ -379,7 +591,7 @@ struct Lower {
     void plan_late() {
         in_forward.assign(N, 1);
         late.assign(N, 0);
-        if (!with_grad || B.save_reads || I.kind[t.loss] != K_COMP) return;
+        if (!with_grad || mats || B.save_reads || I.kind[t.loss] != K_COMP) return;
         std::vector<uint8_t> need(N, 0), recomputed(N, 0);
         for (const auto &v : B.livein)
             for (uint32_t s : v) need[s] = 1;
@@ -442,7 +654,7 @@ struct Lower {
         n_rows = 0;
         for (uint32_t j = 0; with_grad && j < m; ++j) {
             first_row.push_back(n_rows);
-            n_rows += uint32_t(B.livein[j].size());
+            for (uint32_t s : B.livein[j]) n_rows += rows_of(s);
         }
         plan_late();
         const bool late_loss = !late_row.empty();
@@ -459,26 +671,30 @@ struct Lower {
         std::unordered_map<uint32_t, std::vector<uint32_t>> saves_of;   // save policy: rows of each stored value
         if (with_grad && B.save_reads)
             for (uint32_t j = 0; j < m; ++j)
-                for (uint32_t i = 0; i < B.livein[j].size(); ++i) saves_of[B.livein[j][i]].push_back(first_row[j] + i);
+                for (uint32_t i = 0, r = first_row[j]; i < B.livein[j].size(); r += rows_of(B.livein[j][i]), ++i)
+                    saves_of[B.livein[j][i]].push_back(r);
         uint32_t next_cut = 1;
         auto fwd = [&](uint32_t s) { return fwd_operand(s); };
         for (uint32_t k = 0; k < N; ++k) {
             if (with_grad && !B.save_reads)
                 while (next_cut < m && B.cuts[next_cut] == k) {
-                    for (uint32_t i = 0; i < B.livein[next_cut].size(); ++i)
-                        store(fval[B.livein[next_cut][i]], first_row[next_cut] + i);
+                    uint32_t r = first_row[next_cut];
+                    for (uint32_t s : B.livein[next_cut]) {
+                        store(s, fval[s], r);
+                        r += rows_of(s);
+                    }
                     ++next_cut;
                 }
             if (!B.comp_live(k) || I.rep[k] != k || !in_forward[k]) continue;
-            const uint32_t dst = vreg();
+            const uint32_t dst = place_of(k);
             forward_op(k, fwd, dst);
             fval[k] = dst;
             auto lr = late_row.find(k);
-            if (lr != late_row.end()) store(dst, lr->second);
+            if (lr != late_row.end()) store(k, dst, lr->second);
             if (with_grad && B.save_reads) {
                 auto it = saves_of.find(k);
                 if (it != saves_of.end())
-                    for (uint32_t r : it->second) store(dst, r);
+                    for (uint32_t r : it->second) store(k, dst, r);
             }
         }
         if (!late_loss) put(STLOSS, {fwd_operand(t.loss)});
@@ -491,19 +707,21 @@ struct Lower {
                 else fma(seed, one(), one(), seed);   // the loss is a parameter
             }
             for (uint32_t j = m; j-- > 0;) {
-                for (uint32_t i = 0; i < B.livein[j].size(); ++i) {
-                    row[B.livein[j][i]] = first_row[j] + i;
-                    row_of[B.livein[j][i]] = j + 1;
+                uint32_t r = first_row[j];
+                for (uint32_t s : B.livein[j]) {
+                    row[s] = r;
+                    row_of[s] = j + 1;
+                    r += rows_of(s);
                 }
                 for (uint32_t s : B.recomp[j]) {
                     if (I.kind[s] == K_OBS) continue;   // loaded where first read
                     auto opnd = [&](uint32_t x) { return rev_operand(x, j); };
-                    const uint32_t dst = vreg();
+                    const uint32_t dst = place_of(s);
                     forward_op(s, opnd, dst);
                     set_rval(s, j, dst);
                     auto lr = late_row.find(s);
                     if (lr != late_row.end() && !in_forward[s] && !(lr->second < stored_at.size() && stored_at[lr->second]))
-                        store(dst, lr->second);
+                        store(s, dst, lr->second);
                 }
                 for (uint32_t k : B.revops[j]) reverse_op(k, j);
             }
@@ -538,7 +756,7 @@ struct Lower {
 // restores every value a rule reads and has registers to spare.  The rows the
 // loss is formed from at the end come one after the other with little work
 // between them, and few registers are live by then: they use all slots.
-uint32_t ck_slots(bool save_reads) { return save_reads ? kCkSlots : 4; }
+uint32_t ck_slots(bool save_reads, bool matrices) { return save_reads || matrices ? kCkSlots : 4; }
 
 // Loads issued ahead: the loads of each kind (observations, checkpoint rows)
 // go in batches of up to half its slots.  While the values of one batch are
@@ -717,10 +935,53 @@ uint32_t place_registers(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t n_s
     return next;
 }
 
+// Places of the matrices in LDS, in elements: in the order they are first
+// written, each to the lowest run of elements free over its whole life (the
+// micro-op that writes a matrix may read the others throughout).  Returns the
+// elements used.
+uint32_t place_matrices(std::vector<WOp> &ops, const std::vector<uint32_t> &size) {
+    const uint32_t n = uint32_t(size.size());
+    std::vector<uint32_t> first(n, kUnsetTime), last(n, 0), order, at(n, 0);
+    for (uint32_t i = 0; i < ops.size(); ++i)
+        for (uint32_t q = 0; q < ops[i].n_mem; ++q) {
+            const uint32_t v = ops[i].m[q];
+            if (first[v] == kUnsetTime) {
+                first[v] = i;
+                order.push_back(v);
+            }
+            last[v] = i;
+        }
+    struct Run {
+        uint32_t at, size, end;   // elements, last use
+    };
+    std::vector<Run> live;        // by place
+    uint32_t top = 0;
+    for (uint32_t v : order) {
+        live.erase(std::remove_if(live.begin(), live.end(), [&](const Run &r) { return r.end < first[v]; }), live.end());
+        uint32_t place = 0;
+        size_t i = 0;
+        for (; i < live.size() && live[i].at < place + size[v]; ++i) place = live[i].at + live[i].size;
+        live.insert(live.begin() + i, {place, size[v], last[v]});
+        at[v] = place;
+        top = std::max(top, place + size[v]);
+    }
+    for (WOp &u : ops)
+        for (uint32_t q = 0; q < u.n_mem; ++q) u.e[q] += at[u.m[q]];
+    return top;
+}
+
 // words of one micro-op
 void encode(const WOp &u, std::vector<uint32_t> *out) {
-    uint32_t q = 0, word = 0, halves = 0;
+    uint32_t q = 0, word = 0, halves = 0, mem = 0;
     for (const char *c = roles(u.cls); *c; ++c) {
+        if (*c == 'R' || *c == 'W' || *c == 'M') {
+            out->push_back(u.e[mem++] * kLdsRow);
+            continue;
+        }
+        if (*c == 'z') {
+            out->push_back(0);
+            continue;
+        }
         if (*c == 'i') {
             out->push_back(u.imm);
             continue;
@@ -814,26 +1075,66 @@ void emit(const std::vector<WOp> &in, WideSchedule *S) {
 
 }  // namespace
 
-WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads) {
-    WideSchedule none;
+bool wide_takes(const Tape &t, bool *matrices) {
+    *matrices = false;
+    for (const TapeOp &o : t.ops) *matrices = *matrices || o.rows != 1 || o.cols != 1 || o.code == tp::MATMUL;
+    auto nel = [&](uint32_t s) { return t.nel(s); };
     for (const TapeOp &o : t.ops) {
-        if (o.rows != 1 || o.cols != 1) return none;
+        if (o.rows > 4 || o.cols > 4) return false;
+        const bool scalar = o.rows == 1 && o.cols == 1;
         switch (o.code) {
-        case tp::CONST: case tp::PARAM: case tp::OBS: case tp::ADD: case tp::SUB: case tp::MUL: case tp::DIV:
-        case tp::NEG: case tp::EXP: case tp::LOG: case tp::SQRT: case tp::SIN: case tp::COS: case tp::POW:
-        case tp::ABS: case tp::SELECT:
+        case tp::CONST: case tp::PARAM: case tp::OBS: case tp::ADD: case tp::SUB:
+        case tp::MATMUL: case tp::TRANSPOSE: case tp::PACK: case tp::INDEX:
             break;
-        default: return none;
+        case tp::MUL:   // scalars, or a scalar and a matrix
+            if (!scalar && nel(o.a) != 1 && nel(o.b) != 1) return false;
+            break;
+        case tp::DIV: case tp::NEG: case tp::EXP: case tp::LOG: case tp::SQRT: case tp::SIN: case tp::COS:
+        case tp::POW: case tp::ABS: case tp::SELECT:
+            if (!scalar) return false;
+            break;
+        case tp::INV: case tp::LOGDET:
+            if (nel(o.a) != 4) return false;
+            break;
+        default: return false;
         }
     }
-    if (kSlots + 2 * uint64_t(t.n_params) + 8 > kRegs || t.n_obs >= 1u << 29) return none;
+    return kSlots + 2 * uint64_t(t.n_params) + 8 <= (*matrices ? kMatRegs : kRegs) && t.n_obs < 1u << 29;
+}
+
+// A matrix operation costs the wide kernel a call (some 300 cycles before its
+// first product), and the scalars of a program with matrices use a quarter of
+// the lanes that a wave could serve; the slot kernel costs less where the
+// operations are small.  Steps of a 4x4 product and a scaling (40 products or
+// elements an operation) on 16,384 lanes, 150 steps, slot against wide kernel,
+// us: losses 107 against 97, gradients 753 against 669; 3x3 (18 an operation)
+// 129 against 82, 871 against 470; 2x2 (6) 49 against 60, 345 against 317; a
+// 4x4 matrix on a vector, scaled, and its norm (7) 188 against 137, 566 against
+// 575, of 2x2 (2.5) 109 against 128, 449 against 525.
+constexpr uint64_t kMatWork = 12;
+bool wide_pays(const Tape &t) {
+    uint64_t n = 0, work = 0;   // matrix operations, their products or elements
+    for (const TapeOp &o : t.ops) {
+        if (o.code != tp::MATMUL && ((o.rows == 1 && o.cols == 1) || o.code == tp::PACK)) continue;
+        n += 1;
+        work += o.code == tp::MATMUL ? uint64_t(t.nel(o.a)) * o.cols : uint64_t(o.rows) * o.cols;
+    }
+    return work >= kMatWork * n;
+}
+
+WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads, uint32_t lds_rows) {
+    WideSchedule none;
+    bool mats;
+    if (!wide_takes(t, &mats)) return none;
+    const uint32_t regs = mats ? kMatRegs : kRegs;
     Info I(t);
     I.fold_static_subtrahend = true;
+    I.fold_scalars_only = true;
     I.exact_revreads = true;
     I.analyse();
     uint64_t total = 0;
     for (uint32_t k = 0; k < I.N; ++k)
-        if (I.kind[k] == K_COMP && I.vlive[k]) total++;
+        if (I.kind[k] == K_COMP && I.vlive[k]) total += I.nel[k];
     total = std::max<uint64_t>(total, 1);
     // (a search over sizes needs the registers only; the chosen one is laid out)
     auto trial = [&](uint64_t size, bool full = false) {
@@ -850,11 +1151,11 @@ WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads) {
         } else {
             B.set_cuts({0});
         }
-        Lower W(I, B, with_grad);
+        Lower W(I, B, with_grad, mats);
         W.run();
         WideSchedule S;
-        if (W.consts.size() > kRegs) return S;
-        const uint32_t ck_cap = ck_slots(save_reads);
+        if (W.consts.size() > regs) return S;
+        const uint32_t ck_cap = ck_slots(save_reads, mats);
         uint32_t late_at;
         std::vector<WOp> ops = place_loads(W, ck_cap, &late_at);
         std::vector<uint32_t> spare, early;
@@ -870,10 +1171,12 @@ WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads) {
                     (late_at == UINT32_MAX ? spare : early).push_back(2 * kObsSlots + half * kCkSlots + i);
         }
         S.n_regs = place_registers(ops, W.n_virtual, W.n_static, spare, early, late_at);
-        S.n_ckpt_rows = W.n_rows;
+        S.matrices = mats;
+        S.lds_rows = place_matrices(ops, W.mem_size);
+        S.n_ckpt_rows = W.n_rows * (mats ? 4 : 1);
         S.n_segments = uint32_t(B.cuts.size());
         S.consts = W.consts;
-        S.ok = S.n_regs <= kRegs && S.n_ckpt_rows < (1u << 31);
+        S.ok = S.n_regs <= regs && S.lds_rows <= lds_rows && S.n_ckpt_rows < (1u << 31);
         if (S.ok && full) emit(ops, &S);
         return S;
     };

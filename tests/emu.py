@@ -74,23 +74,25 @@ def program(tape: bytes, with_grad=True, budget=320, slots=4, save=False, arms=F
     return headers, words
 
 
-WIDE_STATS = ["n_regs", "n_ckpt_rows", "n_segments", "n_blocks", "n_uops", "cost"]
+WIDE_STATS = ["n_regs", "n_ckpt_rows", "n_segments", "n_blocks", "n_uops", "cost", "lds_rows", "pays"]
 
 
-def wide(tape: bytes, params, obs, mode=1):
+def wide(tape: bytes, params, obs, mode=1, lds_rows=320):
     """The wide kernel's program of `tape` run block by block on the host
-    (mode 0 forward only, 1 gradient, 2 gradient with the save policy):
-    (loss, grad, stats), or None for a tape the wide kernel does not take."""
+    (mode 0 forward only, 1 gradient, 2 gradient with the save policy; lds_rows
+    matrix elements in LDS): (loss, grad, stats), or None for a tape the wide
+    kernel does not take."""
     params = np.ascontiguousarray(params, dtype=np.float64)
     obs = np.ascontiguousarray(obs, dtype=np.float64)
     L, P = params.shape
     loss, grad = np.full(L, np.nan), np.zeros((L, P))
-    stats = (ctypes.c_uint64 * 6)()
+    stats = (ctypes.c_uint64 * 8)()
     f = lib().ndvm_emu_wide
     vp, i64 = ctypes.c_void_p, ctypes.c_int64
     f.restype = ctypes.c_int
-    f.argtypes = [ctypes.c_char_p, ctypes.c_size_t, ctypes.c_int, vp, i64, i64, vp, i64, vp, vp, i64, vp]
-    rc = f(tape, len(tape), mode, params.ctypes.data, L, P, obs.ctypes.data, obs.size, loss.ctypes.data,
+    f.argtypes = [ctypes.c_char_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_uint32, vp, i64, i64, vp, i64, vp, vp, i64,
+                  vp]
+    rc = f(tape, len(tape), mode, lds_rows, params.ctypes.data, L, P, obs.ctypes.data, obs.size, loss.ctypes.data,
            grad.ctypes.data, P, stats)
     if rc == 1:
         return None

@@ -24,7 +24,7 @@ def test_programs_equal_oracle(oracle_mod, mode):
     """Every case, forward only and both policies, by the strict bar."""
     for name, code, obs, p in CASES:
         got = emu.wide(nd.tape_build(code), p, obs, mode)
-        assert got is not None, name
+        assert got is not None and got[2]["pays"], name
         ol, og, _ = oracle_mod.run(code, p, obs)
         grads = (got[1], og) if mode and og.size else (None, None)
         compare(got[0], grads[0], ol, grads[1])
@@ -56,28 +56,37 @@ def test_segments_and_the_loss_formed_last():
 
 
 def test_programs_left_to_the_slot_kernel():
-    w = configs.kalman(L=1, T=2)
-    assert emu.wide(nd.tape_build(w.bytecode), w.params, w.obs) is None      # matrices
     from workloads.bytecode import Asm
     A = Asm(50, 0)
     A.param(0)
     for i in range(1, 50):
         A.param(i).mul()
     assert emu.wide(nd.tape_build(A.halt().bytes()), np.ones((1, 50)), np.zeros(0)) is None   # parameters
+    A = Asm(4, 0)
+    for i in range(4):
+        A.param(i)
+    A.pack(2, 2).exp().trace()
+    assert emu.wide(nd.tape_build(A.halt().bytes()), np.ones((1, 4)), np.zeros(0)) is None    # a form without a class
+    w = configs.kalman(L=1, T=4)
+    t = nd.tape_build(w.bytecode)
+    assert emu.wide(t, w.params, w.obs, 1, lds_rows=100) is None                               # LDS
+    assert emu.wide(t, w.params, w.obs, 1, lds_rows=260)[2]["n_segments"] > 1
+    assert emu.wide(t, w.params, w.obs, 1, lds_rows=1280)[2]["n_segments"] == 1
 
 
 # ------------------------------------------------------------ machine code
 CSRC = os.path.join(ROOT, "paper_2607_03574_amd", "csrc")
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
-ROLE = {"u": {"S"}, "d": {"D"}, "e": {"D"}, "m": {"S", "D"}, "-": set(), "i": set()}
+ROLE = {"u": {"S"}, "d": {"D"}, "e": {"D"}, "m": {"S", "D"}, "-": set()}
 
 
 def _format():
     hdr = open(os.path.join(CSRC, "wide.h")).read()
     body = re.sub(r"//.*", "", re.search(r"enum Class : uint32_t \{(.*?)kClasses", hdr, re.S).group(1))
     names = [x.split("=")[0].strip() for x in body.split(",") if x.strip()]
+    assert names.index("END") + 1 == names.index("STE")
     num = dict(kCkSlots="12", kObsSlots="4")
-    assert "kObsSlots = 4, kCkSlots = 12" in hdr and "kRegion = 1024" in hdr and "kFileBase = 48" in hdr
+    assert "kObsSlots = 4, kCkSlots = 12" in hdr and "kRegion = 1024" in hdr and "kFileBase = 48" in hdr and "kMatFileBase = 106" in hdr
     info = re.search(r"kInfo\[kClasses\] = \{(.*?)\};", hdr, re.S).group(1)
     info = [tuple(int(num.get(x.strip(), x)) for x in t.split(",")) for t in re.findall(r"\{([^{}]*)\}", info)]
     sch = open(os.path.join(CSRC, "wide_sched.cpp")).read()
@@ -92,8 +101,9 @@ def _format():
 
 @pytest.fixture(scope="module")
 def code(tmp_path_factory):
-    """Disassembly of the wide kernel: {address: text}, the functions' address
-    ranges by name, and the code base."""
+    """Disassembly of the wide kernels: {address: text}, the functions' address
+    ranges by name, and of each kernel (scalar, matrices) the code base, the
+    file's first vector register and its classes."""
     import importlib.util
     spec = importlib.util.spec_from_file_location("_b", os.path.join(ROOT, "paper_2607_03574_amd", "build.py"))
     b = importlib.util.module_from_spec(spec)
@@ -116,17 +126,23 @@ def code(tmp_path_factory):
             ins[a] = m.group(1)
             fn[cur].append(a)
     addrs = sorted(ins)
-    i = next(a for a in addrs if ins[a].startswith("s_getpc_b64 s[28:29]"))
-    j = addrs[addrs.index(i) + 1]
-    return ins, fn, j + int(ins[j].split(",")[-1], 16)
+    fmt, _ = _format()
+    scalar = 1 + [n for n, _ in fmt].index("END")
+    kernels = []
+    for name, first, n in (("ndvm_wideE", 48, scalar), ("ndvm_wide_matrixE", 106, len(fmt))):
+        at = next(fn[f] for f in fn if name in f)
+        i = next(a for a in at if ins[a].startswith("s_getpc_b64 s[28:29]"))
+        j = addrs[addrs.index(i) + 1]
+        kernels.append((j + int(ins[j].split(",")[-1], 16), first, fmt[:n]))
+    return ins, fn, kernels
 
 
 def test_entry_points_start_micro_ops(code):
     """Each class's code starts its micro-ops where the format says, reads the
     words of the half it serves, and ends in that half's dispatch."""
-    ins, _, base = code
+    ins, _, kernels = code
     addrs = sorted(ins)
-    for c, (name, (words, most, size)) in enumerate(_format()[0]):
+    for base, c, name, (words, most, size) in [(b, c, *f) for b, _, fmt in kernels for c, f in enumerate(fmt)]:
         for half in range(2):
             region = base + (2 * c + half) * 1024
             end = 66 + 32 * half
@@ -149,15 +165,15 @@ def test_entry_points_start_micro_ops(code):
 def test_operand_roles(code):
     """The VGPR index applies to exactly the operands that name the file's base
     register, with the role the micro-op's half word carries."""
-    ins, _, base = code
+    ins, _, kernels = code
     addrs = sorted(ins)
-    fmt, roles = _format()
-    for c, (name, (words, most, size)) in enumerate(fmt):
+    roles = _format()[1]
+    for base, file, c, name, (words, most, size) in [(b, f, c, *x) for b, f, fmt in kernels for c, x in enumerate(fmt)]:
         if name in ("WAIT", "END"):
             continue
         halves = []
         for r in roles[name]:
-            halves += [r, "i"] if r == "i" else [r]
+            halves += [r, r] if r in "iRWMz" else [r]      # a whole word
         for half in range(2):
             for k in range(most):
                 at = base + (2 * c + half) * 1024 + k * size
@@ -181,8 +197,8 @@ def test_operand_roles(code):
                     elif op == "s_set_gpr_idx_off":
                         on = False
                     elif op == "s_set_gpr_idx_on":
-                        on, m0 = True, {"D"}
-                        assert "DST" in o[1] and (o[0] == "vcc_lo" or role(o[0], 0) == "d")
+                        on, m0 = True, {"D"} if "DST" in o[1] else set()
+                        assert "SRC" not in o[1] and (not m0 or o[0] == "vcc_lo" or role(o[0], 0) == "d")
                     elif op.startswith("v_") and on:
                         dst = [] if op.startswith("v_cmp") else o[:1]
                         src = o[2:] if op.startswith("v_div_scale") else o[1:]
@@ -191,7 +207,7 @@ def test_operand_roles(code):
                             if m:
                                 assert m0 is not None, (name, ins[a])
                                 indexed = "D" in m0 if i < 0 else i == 0 and "S" in m0
-                                assert (int(m.group(1)) in (48, 49)) == indexed, (name, ins[a], m0)
+                                assert (int(m.group(1)) in (file, file + 1)) == indexed, (name, ins[a], m0)
 
 
 def test_library_functions_keep_to_their_registers(code):
@@ -200,7 +216,9 @@ def test_library_functions_keep_to_their_registers(code):
     skip (each call's target is a function's second instruction)."""
     ins, fn, _ = code
     names = [f for f in fn if f.startswith("ndvm_wide_")]
-    assert len(names) == 13
+    assert len(names) == 27
+    scalar = {"ndvm_wide_" + x for x in ("exp", "sin", "cos", "logc", "sqrtc", "pow", "accsin", "acccos", "acclog",
+                                         "accabs", "accpow", "accsqrt", "abs")}
     addrs, entries = sorted(ins), set()
     for i, a in enumerate(addrs):
         if ins[a].startswith("s_swappc_b64"):
@@ -214,8 +232,9 @@ def test_library_functions_keep_to_their_registers(code):
             t = ins[a]
             assert "scratch" not in t and "buffer" not in t and "m0" not in t and "swappc" not in t, (f, t)
             regs = re.findall(r"\b([sv])(?:\[(\d+):(\d+)\]|(\d+)\b)", t)
+            most = 39 if f in scalar else 95      # (39 and 95: where prefetches land)
             for kind, lo, hi, one in regs:
                 top = int(hi or one)
-                if kind == "s" and lo == "30":
-                    continue                      # the return address
-                assert top < (26 if kind == "s" else 40), (f, t)
+                if kind == "s" and (lo == "30" or (one == "27" and f not in scalar)):
+                    continue                      # the return address, the immediate
+                assert top < (26 if kind == "s" else most), (f, t)

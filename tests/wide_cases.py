@@ -1,5 +1,5 @@
-"""Scalar programs at the edges of the wide replay kernel's blocks, load slots
-and register file: shared by the emulator and GPU tests."""
+"""Programs at the edges of the wide replay kernel's blocks, load slots
+register file and matrix functions: shared by the emulator and GPU tests."""
 import numpy as np
 
 from workloads import configs
@@ -52,6 +52,15 @@ def branch(then_first):
     return A.dup().mul().halt().bytes()
 
 
+def large(A):
+    """The program with as many 4x4 products appended as make its matrix
+    operations large enough for the wide kernel (their result enters the loss)."""
+    for i in range(16):
+        A.push((0.3, 1.1, 0.3)[i % 3])
+    A.pack(4, 4).storel(30).loadl(30).storel(31).loop(8).loadl(31).loadl(30).matmul().storel(31).endloop()
+    return A.loadl(31).index(1, 2).mul().halt().bytes()
+
+
 def cases():
     """(name, bytecode, observations, parameter rows)."""
     rng = np.random.default_rng(17)
@@ -95,6 +104,41 @@ def cases():
     for T in (1, 2, 60):
         w = configs.lotka_volterra(L=3, T=T)
         add(f"lotka{T}", w.bytecode, w.obs, w.params)
+    # matrices: every shape of a product and of its adjoints, both operands and
+    # results of one element, transposes, differences, packs of repeated and
+    # constant elements, elements taken out, inverses and log-determinants
+    for m in (1, 2, 3, 4):
+        for k in (1, 2, 3, 4):
+            for n in (1, 2, 3, 4):
+                A = Asm(m * k + k * n, 0)
+                for i in range(m * k):
+                    A.param(i)
+                A.pack(m, k)
+                for i in range(k * n):
+                    A.param(m * k + i)
+                A.pack(k, n).matmul().storel(0).push(0.0)
+                for i in range(m):
+                    for j in range(n):
+                        A.loadl(0).index(i, j).push((0.3, -0.7, 1.1)[(i + 2 * j) % 3]).mul().add()
+                if m * k + k * n <= 16:      # the register file holds the parameters and their adjoints
+                    add(f"matmul{m}{k}{n}", large(A), [], rng.normal(size=(2, m * k + k * n)))
+    A = Asm(6, 2)
+    for i in (0, 1, 2, 3, 4, 5):
+        A.param(i)
+    A.pack(2, 3).storel(0).param(0).param(0).push(1.5).obs(0).obs(1).param(5).pack(3, 2).storel(1)
+    A.loadl(0).loadl(1).transpose().sub().storel(2).loadl(2).loadl(2).transpose().matmul().storel(3)
+    A.param(1).loadl(3).mul().param(2).mul().loadl(3).add().storel(4).loadl(4).inv().storel(5)
+    A.loadl(5).loadl(3).matmul().logdet().loadl(5).index(0, 1).mul().loadl(4).logdet().add().loadl(2).index(1, 2).add()
+    add("matrices", large(A), [0.5, -1.25], rng.normal(size=(5, 6)))
+    A = Asm(5, 0)      # a node whose adjoint is zero against infinite operands
+    for i in range(4):
+        A.param(i)
+    A.pack(2, 2).dup().matmul().storel(0).loadl(0).loadl(0).transpose().matmul().index(0, 0).param(4).mul()
+    add("matrix_zero_inf", large(A), [], [[np.inf, 1.0, 2.0, 3.0, 0.0], [1.0, -0.0, 2.0, 3.0, 0.0],
+                                                  [1e200, 1e200, 1.0, 1.0, 1.0], [0.5, 0.25, -1.0, 2.0, 1.0]])
+    for T in (1, 2, 5):
+        w = configs.kalman(L=3, T=T)
+        add(f"kalman{T}", w.bytecode, w.obs, w.params)
     for seed in range(6):
         w = configs.random_programs(n_prog=3, L=4, n=9, seed=900 + seed)
         for q, code in enumerate(w.programs):
