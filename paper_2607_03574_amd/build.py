@@ -36,9 +36,13 @@ REPLAY = [
     # shared block it would wait there for the memory traffic of every other
     # handler (the program prefetch included)
     "-mllvm", "-sink-common-insts=false", "-mllvm", "-enable-tail-merge=false"]
-# sources built with the replay kernel's options (the device walker is not:
-# with its loops the first option makes the code generator fail)
-REPLAY_OPTIONS_FOR = {"wide_sched.cpp", "frontend.cpp", "tape.cpp", "sched.cpp", "abi.cpp", "kernels.hip", "optim.hip", "emu.cpp"}
+# sources built with the replay kernel's options
+REPLAY_OPTIONS_FOR = {"wide_sched.cpp", "frontend.cpp", "tape.cpp", "sched.cpp", "abi.cpp", "kernels.hip", "optim.hip", "emu.cpp",
+                      "walk.hip"}
+
+# The walker's loop: without lifetime markers leaving a handler's scope is a
+# plain branch, not a value tested by a chain of blocks behind every handler.
+WALK = ["-Xclang", "-disable-lifetime-markers"]
 
 # The wide kernel: the library functions' branches on wave-uniform values stay
 # branches; the registers its inline asm names are not the compiler's.
@@ -48,6 +52,8 @@ WIDE = ["-mllvm", "-structurizecfg-skip-uniform-regions=true", "-Wno-inline-asm"
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
     extra = REPLAY if src in REPLAY_OPTIONS_FOR else WIDE if src == "wide.hip" else []
+    if src == "walk.hip":
+        extra = extra + WALK
     cmd = [HIPCC] + COMMON + DEVICE + extra + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"

@@ -45,23 +45,24 @@ constexpr uint32_t kLeaf = 0x01;    // constant or observation: takes no adjoint
 constexpr uint32_t kParam = 0x02;   // parameter p = node p
 constexpr uint32_t kMerge = 0x40;   // per-lane pick of two arms' values (a if the lane took the first arm)
 
-// Recorded node (one per node and wave, 16 bytes): its kind and operand
-// nodes; for a MERGE, `mask` indexes the ballot word of the lanes that took
-// the first arm (stored after the node records).
+// Recorded operation (16 bytes): its kind, operand nodes and own number (in
+// `mask`); constants and observations are not recorded.  For a MERGE, the ballot
+// word of the lanes that took the first arm is stored under its number.
 struct Node {
     uint32_t op, a, b, mask;
 };
 
-// Per-wave workspace: values[n_nodes][64], adjoints[n_nodes][64] (fp64),
-// nodes[n_nodes], ballot words[n_nodes] (u64, MERGE nodes only).
+// Per-wave workspace: values[n_nodes][64], adjoints[n_nodes][64] (fp64; those
+// moved out of LDS), operations[n_nodes], ballot words[n_nodes] (u64, MERGE
+// nodes only).
 constexpr uint64_t ws_bytes_per_node() { return 64 * 8 * 2 + sizeof(Node) + 8; }
 
-// LDS of one wave.  Rows of 64 doubles first: the parameters' values, then
-// the operand stack's and the locals' values during the forward walk, whose
-// rows the parameters' adjoints take over in the reverse sweep.  Then 32-bit
-// words: the operand stack's and locals' node numbers, loop frames (start,
-// trips, counter), IFLT frames (masks, phase, two snapshots of stack +
-// locals node numbers), and one flag bit per node (adjoint row written).
+// Structural state of one wave, the measure of what the validator accepts.
+// Rows of 64 doubles: the parameters' values, then the operand stack's and the
+// locals' values during the forward walk or the parameters' adjoints during the
+// reverse sweep.  Then 32-bit words: the operand stack's and locals' node
+// numbers, loop frames (start, trips, counter), IFLT frames (masks, phase, two
+// snapshots of stack + locals node numbers), and one flag bit per node.
 constexpr uint32_t kFrameFixed = 8;
 constexpr uint32_t lds_rows(uint32_t depth, uint32_t n_locals, uint32_t n_params) {
     const uint32_t fwd = depth + n_locals;
@@ -77,9 +78,24 @@ constexpr uint64_t lds_bytes(uint32_t depth, uint32_t n_locals, uint32_t n_loops
     return 512ull * lds_rows(depth, n_locals, n_params) + 4ull * lds_words(depth, n_locals, n_loops, n_frames, n_nodes);
 }
 
+// LDS of a launch's workgroup: the same rows with kAdjointRows more for the
+// reverse sweep's other adjoints (where the forward rows do not already give
+// them room), and of the words the IFLT frames and the flags; the stack's, the
+// locals' and the loops' words are held in registers.
+constexpr uint32_t kAdjointRows = 12;
+constexpr uint32_t launch_rows(uint32_t depth, uint32_t n_locals, uint32_t n_params) {
+    const uint32_t fwd = depth + n_locals, rev = n_params + kAdjointRows;
+    return n_params + (fwd > rev ? fwd : rev);
+}
+constexpr uint64_t launch_lds_bytes(uint32_t depth, uint32_t n_locals, uint32_t n_frames, uint32_t n_nodes,
+                                 uint32_t n_params) {
+    return 512ull * launch_rows(depth, n_locals, n_params) +
+           4ull * (n_frames * (kFrameFixed + 2 * (depth + n_locals)) + 64 + (n_nodes + 31) / 32);
+}
+
 // Limits the host validator enforces.
 constexpr uint32_t kMaxDepth = 64, kMaxLocals = 32, kMaxFrames = 32, kMaxLoops = 32;
-constexpr uint64_t kMaxLdsBytes = 64 * 1024;   // a workgroup's LDS
+constexpr uint64_t kMaxLdsBytes = 64 * 1024;   // structural state of a wave
 constexpr uint64_t kMaxNodes = 1u << 22;   // node * 64 + lane fits 32 bits
 
 struct Args {

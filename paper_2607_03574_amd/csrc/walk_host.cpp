@@ -365,7 +365,7 @@ uint32_t wave_slots(const ndvm_walk &w, uint64_t items) {
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) == hipSuccess && v > 0)
             lds = v;
     }
-    const uint64_t lds_wave = walk::lds_bytes(w.depth, w.n_locals, w.n_loops, w.n_frames, w.n_nodes, w.max_params);
+    const uint64_t lds_wave = walk::launch_lds_bytes(w.depth, w.n_locals, w.n_frames, w.n_nodes, w.max_params);
     const uint64_t per_cu = std::max<uint64_t>(1, std::min<uint64_t>(16, uint64_t(lds) / std::max<uint64_t>(lds_wave, 1)));
     return uint32_t(std::min<uint64_t>(items, per_cu * uint64_t(cus)));
 }
@@ -545,7 +545,7 @@ ndvm_status ndvm_walk_grad(const ndvm_walk *w, const double *params, int64_t L, 
         A.n_loops = w->n_loops;
         A.n_frames = w->n_frames;
         A.n_params = w->max_params;
-        A.lds_bytes = uint32_t(walk::lds_bytes(w->depth, w->n_locals, w->n_loops, w->n_frames, w->n_nodes, w->max_params));
+        A.lds_bytes = uint32_t(walk::launch_lds_bytes(w->depth, w->n_locals, w->n_frames, w->n_nodes, w->max_params));
         A.n_items = uint64_t(w->n_prog) * uint64_t((L + 63) / 64);
         A.status = static_cast<int *>(workspace);
         const hipStream_t s = static_cast<hipStream_t>(stream);

@@ -12,6 +12,8 @@ import pytest
 
 from conftest import record
 from parity import judge
+from wide_cases import chain, held_values
+from workloads import bytecode as B
 from workloads import configs
 from workloads.bytecode import Asm
 
@@ -127,6 +129,32 @@ def test_edge_programs(nd, oracle_mod):
         loss, grad = walk(nd, [bc], params[None], [])
         np.testing.assert_allclose(loss[0], lo, rtol=1e-13, atol=0)
         np.testing.assert_allclose(grad[0], go, rtol=1e-13, atol=1e-300)
+
+
+@pytest.mark.parametrize("n", [1, 2, 11, 12, 13, 14, 31])
+def test_live_adjoints(nd, oracle_mod, n):
+    """Fewer, as many and more adjoints alive at a time than the reverse sweep
+    holds in LDS (the others go through the wave's slot)."""
+    bc = held_values(n)
+    p = np.random.default_rng(n).uniform(-1.0, 1.0, (70, 2))
+    lo, go, _ = oracle_mod.run(bc, p, [])
+    loss, grad = walk(nd, [bc], p[None], [])
+    np.testing.assert_allclose(loss[0], lo, rtol=1e-13, atol=1e-15 * n)
+    np.testing.assert_allclose(grad[0], go, rtol=1e-12, atol=1e-13 * n)
+
+
+@pytest.mark.parametrize("op", [B.MUL, B.SUB])
+def test_record_chunks(nd, oracle_mod, op):
+    """Operation counts around the chunks of 64 records and the distance the
+    values are read ahead, several programs a launch."""
+    counts = [1, 2, 3, 4, 5, 63, 64, 65, 66, 67, 127, 128, 129, 200]
+    p = np.random.default_rng(3).uniform(0.9, 1.1, (len(counts), 65, 2))
+    codes = [chain(op, n) for n in counts]
+    loss, grad = walk(nd, codes, p, [])
+    for q, c in enumerate(codes):
+        lo, go, _ = oracle_mod.run(c, p[q], [])
+        np.testing.assert_allclose(loss[q], lo, rtol=1e-13, atol=1e-13)
+        np.testing.assert_allclose(grad[q], go, rtol=1e-13, atol=1e-13)
 
 
 def test_argument_errors(nd):

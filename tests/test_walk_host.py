@@ -7,6 +7,11 @@ one SELECT per merged value, and per parameter use a PARAM op where the
 walker reuses one node per parameter, so the walker records at most
 (tape ops - parameter uses + parameters) nodes; the bound is checked against
 that on every benchmark program and on random programs."""
+import importlib.util
+import os
+import re
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -14,6 +19,7 @@ from workloads import configs
 from workloads.bytecode import Asm
 
 nd = pytest.importorskip("paper_2607_03574_amd")
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _tape_ops(bc):
@@ -97,3 +103,31 @@ def test_nesting_is_measured():
           .else_().push(3.0).endif().halt().bytes())
     info = nd.walk_measure(bc)
     assert info["n_frames"] == 2 and info["n_params"] == 2
+
+
+def test_walk_library_functions(tmp_path):
+    """The walker calls its library functions past their first instruction, a
+    wait, by a call that states what it changes: the functions keep to that
+    (vector registers below 40, scalar ones below 32) and use no scratch."""
+    spec = importlib.util.spec_from_file_location("_b", os.path.join(ROOT, "paper_2607_03574_amd", "build.py"))
+    b = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(b)
+    if not os.path.exists(b.HIPCC):
+        pytest.skip("no device compiler")
+    out = tmp_path / "walk.s"
+    subprocess.run([b.HIPCC] + b.COMMON + b.DEVICE + b.REPLAY + b.WALK +
+                   ["--cuda-device-only", "-S", os.path.join(ROOT, "paper_2607_03574_amd", "csrc", "walk.hip"), "-o",
+                    str(out)], check=True, capture_output=True)
+    text = out.read_text()
+    for f in ("ndvm_walk_sin", "ndvm_walk_cos", "ndvm_walk_pow"):
+        body = text[text.index(f"\n{f}:"):]
+        code = [x.split(";")[0].strip() for x in body[:body.index(".Lfunc_end")].splitlines()[1:] if x.startswith("\t")]
+        code = [x for x in code if x and not x.startswith(".")]
+        assert code[0] == "s_waitcnt vmcnt(0) expcnt(0) lgkmcnt(0)" and code[-1] == "s_setpc_b64 s[30:31]"
+        for t in code:
+            assert not re.search(r"scratch|buffer|m0|swappc", t), (f, t)
+            for kind, lo, hi, one in re.findall(r"\b([sv])(?:\[(\d+):(\d+)\]|(\d+)\b)", t):
+                assert int(hi or one) < (32 if kind == "s" else 40), (f, t)
+    kernel = text[text.index("ndvm_walkENS_4walk4ArgsE:"):]
+    assert kernel.count("s_swappc_b64") == len(re.findall(r"ndvm_walk_\w+@rel32@hi\+16\n\s*s_swappc_b64 s\[30:31\]", kernel))
+    assert "s_endpgm" in kernel and not re.search(r"\bscratch_|\bflat_(load|store)", kernel)
