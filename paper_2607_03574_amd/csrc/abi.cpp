@@ -194,12 +194,12 @@ ndvm_status upload_program(Schedule &&S, const Tape &t, hipStream_t stream, std:
 // slot kernel takes the others (its registers spill, and it has the skip tests
 // that a tape with branches uploaded with NDVM_BRANCH_SKIP asks for).  Both give
 // the same bits.  Slot kernel against wide kernel, ms a call: Lotka-Volterra
-// (1000 steps, 65,536 lanes) 7.39 against 3.45, saving (300 steps, 9,999 lanes)
-// 5.75 against 1.23, losses alone (20,000 lanes) 7.93 against 0.65; logistic
-// (500 steps, 4,096 lanes) 0.916 against 0.678; exponential decay (64 points,
-// 256 lanes) 0.0557 against 0.0480; 1,024 random programs of 1,024 lanes 17.8
-// against 4.5; Kalman filter of four states (200 steps, 16,384 lanes) 6.93
-// against 4.20, saving 6.54 against 4.36, 80 steps on 1,003 lanes 2.13 against
+// (1000 steps, 65,536 lanes) 7.40 against 3.47, saving (300 steps, 9,999 lanes)
+// 5.76 against 0.98, losses alone (20,000 lanes) 7.94 against 0.65; logistic
+// (500 steps, 4,096 lanes) 0.917 against 0.623; exponential decay (64 points,
+// 256 lanes) 0.0558 against 0.0446; 1,024 random programs of 1,024 lanes 17.6
+// against 4.2; Kalman filter of four states (200 steps, 16,384 lanes) 6.95
+// against 4.22, saving 6.55 against 4.37, 80 steps on 1,003 lanes 2.13 against
 // 1.57, its losses alone (50 steps, 65,536 lanes) 2.02 against 0.85.
 bool wide_candidate(const ndvm_tape *t) { return t->wide_takes && !(t->arms && t->n_selects > 0); }
 

@@ -9,7 +9,6 @@
 #include "wide.h"
 
 #include <algorithm>
-#include <cstring>
 #include <queue>
 #include <stdexcept>
 #include <unordered_map>
@@ -935,6 +934,103 @@ uint32_t place_registers(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t n_s
     return next;
 }
 
+// Orders the micro-ops of a scalar program into longer runs of one class (a
+// block costs kDispatchCost however few it holds).  Between loads and waits,
+// where the slots' contents change, any order that keeps each register's reads
+// and writes in order gives the same bits.  Of the `window` oldest micro-ops
+// left, the class is taken next that the longest run can be made of (a run may
+// hold micro-ops that depend on each other); the window bounds what the order
+// adds to the values held at a time.  Estimated cycles of a lone wave, in program
+// order against windows of 8, 16, 32 and 64 (thousands): logistic saving 776
+// against 671, 647, 646, 646; Lotka-Volterra saving 1849 against 1590, 1583,
+// 1559, 1559, recomputing (runs of 9 as it is) 1646 against 1649, 1648, 1647,
+// 1646; twelve random programs 11.8 against 11.6, 11.2, 11.0, 11.0 million.
+constexpr uint32_t kOrderWindow = 32;
+void order_ops(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t sink, uint32_t late_at, uint32_t window) {
+    const uint32_t n_regs = kRegs + n_virtual;
+    auto reg_of = [&](uint32_t r) { return r < kVirtual ? r : kRegs + (r - kVirtual); };
+    // of each register, in this region: its last writer, and the readers since
+    std::vector<uint32_t> writer(n_regs, 0), seen(n_regs, 0);
+    std::vector<std::vector<uint32_t>> readers(n_regs);
+    uint32_t region = 0;
+    std::vector<std::vector<uint32_t>> preds;
+    std::vector<uint32_t> left, taken;   // in order; taken: mark of an op in a run (0: not)
+    std::vector<WOp> out;
+    auto fixed = [&](uint32_t cls) { return cls >= LDK0 && cls <= WAITPF; };
+    for (uint32_t b = 0; b < ops.size();) {
+        uint32_t e = b;
+        while (e < ops.size() && !fixed(ops[e].cls) && ops[e].cls != PF && ops[e].cls != WAIT &&
+               !(e == late_at && e > b))
+            ++e;
+        if (e - b < 3) {
+            b = std::max(e, b + 1);
+            continue;
+        }
+        const uint32_t n = e - b;
+        ++region;
+        preds.assign(n, {});
+        for (uint32_t i = 0; i < n; ++i) {
+            const WOp &u = ops[b + i];
+            const char *role = roles(u.cls);
+            for (uint32_t q = 0; q < u.n; ++q) {
+                if (role[q] == '-' || u.r[q] == sink) continue;
+                const uint32_t r = reg_of(u.r[q]);
+                if (seen[r] != region) {
+                    seen[r] = region;
+                    writer[r] = kNone;
+                    readers[r].clear();
+                }
+                if (writer[r] != kNone && writer[r] != i) preds[i].push_back(writer[r]);
+                if (role[q] == 'u') {
+                    readers[r].push_back(i);
+                } else {
+                    for (uint32_t k : readers[r])
+                        if (k != i) preds[i].push_back(k);
+                    readers[r].clear();
+                    writer[r] = i;
+                }
+            }
+        }
+        left.resize(n);
+        for (uint32_t i = 0; i < n; ++i) left[i] = i;
+        taken.assign(n, 0);
+        uint32_t mark = 0;
+        out.clear();
+        std::vector<uint8_t> done(n, 0);
+        std::vector<uint32_t> run, best;
+        while (!left.empty()) {
+            const uint32_t w = std::min<uint32_t>(window, uint32_t(left.size()));
+            best.clear();
+            uint64_t tried = 0;
+            for (uint32_t c0 = 0; c0 < w; ++c0) {
+                const uint32_t cls = ops[b + left[c0]].cls;
+                if (tried >> cls & 1u) continue;
+                tried |= 1ull << cls;
+                ++mark;
+                run.clear();
+                for (uint32_t k = c0; k < w && run.size() < kInfo[cls].max; ++k) {
+                    const uint32_t i = left[k];
+                    if (ops[b + i].cls != cls) continue;
+                    bool ready = true;
+                    for (uint32_t p : preds[i]) ready = ready && (done[p] || taken[p] == mark);
+                    if (!ready) continue;
+                    taken[i] = mark;
+                    run.push_back(i);
+                }
+                if (run.size() > best.size()) best.swap(run);
+            }
+            for (uint32_t i : best) {
+                done[i] = 1;
+                out.push_back(ops[b + i]);
+            }
+            left.erase(std::remove_if(left.begin(), left.begin() + w, [&](uint32_t i) { return done[i] != 0; }),
+                       left.begin() + w);
+        }
+        std::copy(out.begin(), out.end(), ops.begin() + b);
+        b = e;
+    }
+}
+
 // Places of the matrices in LDS, in elements: in the order they are first
 // written, each to the lowest run of elements free over its whole life (the
 // micro-op that writes a matrix may read the others throughout).  Returns the
@@ -1122,7 +1218,8 @@ bool wide_pays(const Tape &t) {
     return work >= kMatWork * n;
 }
 
-WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads, uint32_t lds_rows) {
+namespace {
+WideSchedule schedule_in(const Tape &t, bool with_grad, bool save_reads, uint32_t lds_rows, bool order) {
     WideSchedule none;
     bool mats;
     if (!wide_takes(t, &mats)) return none;
@@ -1170,6 +1267,7 @@ WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads, uint3
                 if (!ck[half] || i < kCkSlots - ck_cap)
                     (late_at == UINT32_MAX ? spare : early).push_back(2 * kObsSlots + half * kCkSlots + i);
         }
+        if (order && !mats) order_ops(ops, W.n_virtual, W.kSink, late_at, kOrderWindow);
         S.n_regs = place_registers(ops, W.n_virtual, W.n_static, spare, early, late_at);
         S.matrices = mats;
         S.lds_rows = place_matrices(ops, W.mem_size);
@@ -1207,6 +1305,15 @@ WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads, uint3
         if (alt.ok && alt.cost < best.cost) best = std::move(alt);
     }
     return best;
+}
+}  // namespace
+
+// (in program order where the longer runs need registers that are not there)
+WideSchedule schedule_wide(const Tape &t, bool with_grad, bool save_reads, uint32_t lds_rows) {
+    WideSchedule S = schedule_in(t, with_grad, save_reads, lds_rows, true);
+    bool mats;
+    if (!S.ok && wide_takes(t, &mats) && !mats) S = schedule_in(t, with_grad, save_reads, lds_rows, false);
+    return S;
 }
 
 }  // namespace ndvm
