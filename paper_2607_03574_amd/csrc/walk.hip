@@ -239,14 +239,21 @@ __device__ bool walk_item(const Args &A, const Wave &W, const ProgDesc &D, uint3
         case bc::OBS: {
             if (n >= n_nodes || wa > lp || wa > last - pc) return false;
             int64_t idx = imm;
-            for (uint32_t d = 0; d < wa; ++d)
+            // The first stride is in the word read ahead, and the word behind the
+            // strides is read together with the observation: one scalar read after
+            // another otherwise (one program on one lane 1.08 -> 1.05 ms, 1,024
+            // programs on 1,024 lanes 3.93 -> 3.85).
+            if (wa) idx += int64_t(int32_t(next_imm)) * int64_t(get(loop_at, lp - 1));
+            for (uint32_t d = 1; d < wa; ++d)
                 idx += int64_t(int32_t(code[2 * (pc + 1 + d) + 1])) * int64_t(get(loop_at, lp - 1 - d));
-            leaf(obs[idx]);
-            if (wa) {
-                pc += wa + 1;
-                goto jumped;
-            }
-            break;
+            const uint32_t behind = wa < last - pc ? pc + wa + 1 : last;
+            w0 = code[2 * behind];
+            imm = code[2 * behind + 1];
+            double x = obs[idx];
+            asm volatile("" : "+s"(w0), "+s"(imm), "+s"(x));   // one wait for the three
+            leaf(x);
+            pc += wa + 1;
+            continue;
         }
         case bc::PARAM:
             if (imm >= P) return false;
