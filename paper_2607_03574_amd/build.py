@@ -49,11 +49,18 @@ WALK = ["-Xclang", "-disable-lifetime-markers"]
 WIDE = ["-mllvm", "-structurizecfg-skip-uniform-regions=true", "-Wno-inline-asm"]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+# The emulator's copies of the sources check every element access of the
+# standard containers (the process ends at one out of range).
+EMU = ["-D_GLIBCXX_ASSERTIONS"]
+
+
+def _compile(src: str, emu: bool = False) -> str:
+    obj = os.path.join(BUILD, ("emu_" if emu else "") + os.path.splitext(src)[0] + ".o")
     extra = REPLAY if src in REPLAY_OPTIONS_FOR else WIDE if src == "wide.hip" else []
     if src == "walk.hip":
         extra = extra + WALK
+    if emu:
+        extra = extra + EMU
     cmd = [HIPCC] + COMMON + DEVICE + extra + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
@@ -76,11 +83,11 @@ def _link(objs, out):
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    srcs = sorted(set(SOURCES) | set(EMU_SOURCES))
-    with ThreadPoolExecutor(max_workers=len(srcs)) as ex:
-        objs = dict(zip(srcs, ex.map(_compile, srcs)))
-    _link([objs[s] for s in SOURCES], OUT)
-    _link([objs[s] for s in EMU_SOURCES], EMU_OUT)
+    jobs = [(s, False) for s in SOURCES] + [(s, True) for s in EMU_SOURCES]
+    with ThreadPoolExecutor(max_workers=len(jobs)) as ex:
+        objs = list(ex.map(lambda j: _compile(*j), jobs))
+    _link(objs[:len(SOURCES)], OUT)
+    _link(objs[len(SOURCES):], EMU_OUT)
     if verbose:
         print("built", OUT, "and", EMU_OUT)
     return OUT

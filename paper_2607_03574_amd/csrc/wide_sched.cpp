@@ -1251,7 +1251,8 @@ WideSchedule schedule_in(const Tape &t, bool with_grad, bool save_reads, uint32_
         Lower W(I, B, with_grad, mats);
         W.run();
         WideSchedule S;
-        if (W.consts.size() > regs) return S;
+        // (what follows numbers every register below kVirtual as one of the file)
+        if (kSlots + uint64_t(W.n_static) > regs) return S;
         const uint32_t ck_cap = ck_slots(save_reads, mats);
         uint32_t late_at;
         std::vector<WOp> ops = place_loads(W, ck_cap, &late_at);

@@ -12,7 +12,7 @@ import pytest
 import emu
 from conftest import ROOT
 from parity import compare
-from wide_cases import cases
+from wide_cases import cases, lookups
 from workloads import configs
 
 nd = pytest.importorskip("paper_2607_03574_amd")
@@ -53,6 +53,22 @@ def test_segments_and_the_loss_formed_last():
     assert st["n_ckpt_rows"] >= 64     # each term's residual, for the sum at the end
     fwd = emu.wide(t, w.params, w.obs, 0)[2]
     assert fwd["n_ckpt_rows"] == 0
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_parameters_and_constants_at_the_files_end(oracle_mod, mode):
+    """Programs whose parameters and constants alone fill the register file or
+    pass its end: the wide scheduler refuses those it cannot place (the
+    emulator's build checks every container access on the way) and both
+    kernels' programs give the oracle's values."""
+    for name, code, obs, p, fits in lookups():
+        t = nd.tape_build(code)
+        ol, og, _ = oracle_mod.run(code, p, obs)
+        got = emu.wide(t, p, obs, mode)
+        if mode:
+            assert (got is not None) == fits, name
+        for loss, grad in ([got[:2]] if got else []) + [emu.run(t, p, obs, with_grad=mode > 0, save=mode == 2)[:2]]:
+            compare(loss, grad if mode else None, ol, og if mode else None)
 
 
 def test_programs_left_to_the_slot_kernel():

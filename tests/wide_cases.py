@@ -61,6 +61,28 @@ def large(A):
     return A.loadl(31).index(1, 2).mul().halt().bytes()
 
 
+def lookup(params, n):
+    """(p0 * table - y)^2, the table nested branches of n constant leaves over
+    thresholds of the other parameters: parameters and constants (which the
+    register file holds throughout) and hardly any values."""
+    A = Asm(params, 1).param(0)
+    for i in range(n):
+        A.param(i % (params - 1) + 1).push(0.25 + 0.5 * i).iflt().push(1.0 + i).else_()
+    A.push(-1.0)
+    for i in range(n):
+        A.endif()
+    return A.mul().obs(0).sub().dup().mul().halt().bytes()
+
+
+def lookups():
+    """(name, bytecode, observations, parameter rows, whether the file holds
+    its parameters, their adjoints and the constants)."""
+    rng = np.random.default_rng(23)
+    return [(f"lookup{p}_{n}", lookup(p, n), np.ones(1), rng.normal(size=(3, p)), fits)
+            for p, n, fits in ((32, 20, False), (28, 30, False), (24, 30, False), (8, 60, False), (32, 8, False),
+                               (31, 1, True), (28, 5, True), (8, 20, True), (2, 31, True))]
+
+
 def cases():
     """(name, bytecode, observations, parameter rows)."""
     rng = np.random.default_rng(17)
