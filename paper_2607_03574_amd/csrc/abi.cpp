@@ -13,6 +13,7 @@
 #include <memory>
 #include <mutex>
 #include <set>
+#include <stdexcept>
 #include <thread>
 #include <new>
 
@@ -213,10 +214,18 @@ uint32_t wide_lds_rows(uint32_t slot_budget) {
     return slot_budget < kWideLdsRows * 2 / 3 ? kWideLdsRows / 2 : std::max(kWideLdsRows, slot_budget);
 }
 
-// Wide schedule of a tape, or one that is not ok.
+// Wide schedule of a tape, or one that is not ok: also where the scheduler meets
+// a limit of its format or a form it has no code for, the slot kernel runs the
+// tape, and its limits are the library's.
 WideSchedule wide_schedule_of(const ndvm_tape *t, bool with_grad, uint32_t lds_rows) {
     if (!wide_candidate(t)) return WideSchedule{};
-    auto of = [&](uint32_t rows) { return schedule_wide(t->tape, with_grad, t->policy == NDVM_POLICY_SAVE, rows); };
+    auto of = [&](uint32_t rows) {
+        try {
+            return schedule_wide(t->tape, with_grad, t->policy == NDVM_POLICY_SAVE, rows);
+        } catch (const std::logic_error &) {   // (std::length_error is one)
+            return WideSchedule{};
+        }
+    };
     WideSchedule S = of(std::max(kWideLdsRows, lds_rows));
     if (lds_rows && lds_rows < kWideLdsRows && S.ok && S.lds_rows > lds_rows) {
         WideSchedule half = of(lds_rows);

@@ -324,7 +324,13 @@ int ndvm_emu_wide(const uint8_t *tape, size_t len, int mode, uint32_t lds_rows, 
     Tape t;
     ndvm_status st = parse_tape(tape, len, &t);
     if (st != NDVM_OK) return -int(st);
-    const WideSchedule S = schedule_wide(t, mode != 0, mode == 2, lds_rows);
+    WideSchedule S;
+    try {
+        S = schedule_wide(t, mode != 0, mode == 2, lds_rows);
+    } catch (const std::exception &e) {
+        set_error(std::string("wide scheduler: ") + e.what());
+        return 100;
+    }
     if (!S.ok) return 1;
     if (stats) {
         const uint64_t v[8] = {S.n_regs, S.n_ckpt_rows, S.n_segments, S.n_blocks, S.n_uops, S.cost, S.lds_rows, wide_pays(t)};

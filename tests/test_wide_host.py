@@ -12,8 +12,9 @@ import pytest
 import emu
 from conftest import ROOT
 from parity import compare
-from wide_cases import cases, lookups
+from wide_cases import cases, lookups, one_element_forms
 from workloads import configs
+from workloads.bytecode import Asm
 
 nd = pytest.importorskip("paper_2607_03574_amd")
 CASES = cases()
@@ -71,8 +72,27 @@ def test_parameters_and_constants_at_the_files_end(oracle_mod, mode):
             compare(loss, grad if mode else None, ol, og if mode else None)
 
 
+@pytest.mark.parametrize("policy", [nd.POLICY_RECOMPUTE, nd.POLICY_SAVE])
+def test_upload_takes_one_element_forms(policy):
+    """A pack of one element, an element of a scalar and a transposed scalar:
+    an upload, alone or among others, ends as that of a plain product does (on
+    a host without a device, at the device)."""
+    def status(f):
+        try:
+            f()
+        except nd.NdvmError as e:
+            return e.status
+        return 0
+    plain = nd.tape_build(Asm(2, 0).param(0).param(1).mul().halt().bytes())
+    want = status(lambda: nd.tape_upload(plain, policy, 0))
+    assert want != nd.E_INTERNAL
+    for name, code, _, _ in one_element_forms():
+        t = nd.tape_build(code)
+        assert status(lambda: nd.tape_upload(t, policy, 0)) == want, (name, nd.last_error())
+        assert status(lambda: nd.tape_upload_many([plain, t], policy, 0)) == want, (name, nd.last_error())
+
+
 def test_programs_left_to_the_slot_kernel():
-    from workloads.bytecode import Asm
     A = Asm(50, 0)
     A.param(0)
     for i in range(1, 50):

@@ -83,6 +83,26 @@ def lookups():
                                (31, 1, True), (28, 5, True), (8, 20, True), (2, 31, True))]
 
 
+def one_element_forms():
+    """(name, bytecode, observations, parameter rows): matrix words on scalars in
+    programs without a matrix, as values, leaves and the loss."""
+    rows = np.array([[2.0, 3.0], [-0.0, 1.5], [np.inf, 0.0]])
+
+    def forms(name, apply):
+        yield name, apply(Asm(2, 0).param(0)).param(1).mul()
+        yield name + "_loss", apply(Asm(2, 0).param(0).param(1).mul())
+        yield name + "_const", apply(Asm(2, 0).push(0.75)).param(1).mul().param(0).sub()
+        yield name + "_shared", apply(Asm(2, 0).param(0).param(1).sub().dup()).mul().dup().add()
+        A = Asm(2, 2).param(0).storel(0).loop(20)      # several segments, observations
+        yield name + "_loop", apply(A.loadl(0).param(1).mul().sin()).dup().storel(0).obs(1).sub().storel(1) \
+            .endloop().loadl(1).loadl(0).add()
+    out = []
+    for name, apply in (("pack1", lambda A: A.pack(1, 1)), ("index1", lambda A: A.index(0, 0)),
+                        ("transpose1", lambda A: A.transpose())):
+        out += [(n, A.halt().bytes(), np.array([0.5, -1.25] if n.endswith("loop") else []), rows) for n, A in forms(name, apply)]
+    return out
+
+
 def cases():
     """(name, bytecode, observations, parameter rows)."""
     rng = np.random.default_rng(17)
