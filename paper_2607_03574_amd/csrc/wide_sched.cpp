@@ -216,6 +216,11 @@ struct Lower {
         return it != neg_param.end() ? it->second : kNone;
     }
 
+    // whether forward_matrix and reverse_matrix are asked about an op: those of a
+    // program with matrices, and matrix words on scalars (moves) in any program
+    bool has_matrix_form(const TapeOp &o) const {
+        return mats || o.code == tp::TRANSPOSE || o.code == tp::PACK || o.code == tp::INDEX;
+    }
     // a value with a matrix among its operands or as its result; false: none
     template <class F>
     bool forward_matrix(uint32_t k, F operand, uint32_t dst) {
@@ -271,7 +276,7 @@ struct Lower {
     template <class F>
     void forward_op(uint32_t k, F operand, uint32_t dst) {
         const TapeOp &o = t.ops[k];
-        if (mats && forward_matrix(k, operand, dst)) return;
+        if (has_matrix_form(o) && forward_matrix(k, operand, dst)) return;
         switch (o.code) {
         case tp::ADD: case tp::SUB: case tp::MUL: {
             if (I.fmul[k]) {
@@ -487,7 +492,7 @@ struct Lower {
         const uint32_t g = adj[k];
         if (g == kNone) throw std::logic_error("adjoint rule laid out before any contribution to it");
         auto v = [&](uint32_t s) { return rev_operand(s, j); };
-        if (mats && reverse_matrix(k, j, g)) return;
+        if (has_matrix_form(o) && reverse_matrix(k, j, g)) return;
         bool f1 = false, f2 = false;
         switch (o.code) {
         case tp::ADD: case tp::SUB: {

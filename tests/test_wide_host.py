@@ -17,7 +17,7 @@ from workloads import configs
 from workloads.bytecode import Asm
 
 nd = pytest.importorskip("paper_2607_03574_amd")
-CASES = cases()
+CASES = cases() + one_element_forms()
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
