@@ -9,7 +9,6 @@
 #include "wide.h"
 
 #include <algorithm>
-#include <queue>
 #include <stdexcept>
 #include <unordered_map>
 
@@ -184,10 +183,13 @@ struct Lower {
         ops.push_back(u);
     }
     void fma(uint32_t a, uint32_t x, uint32_t y, uint32_t z) { put(FMA, {x, y, z, a}); }
-    uint32_t one() { return konst(1.0); }
-    uint32_t minus_one() { return konst(-1.0); }
-    uint32_t neg_zero() { return konst(-0.0); }
-    uint32_t zero() { return konst(0.0); }
+    // (used by most micro-ops: found once)
+    uint32_t common[4] = {kNone, kNone, kNone, kNone};
+    uint32_t konst(uint32_t i, double v) { return common[i] != kNone ? common[i] : common[i] = konst(v); }
+    uint32_t one() { return konst(0, 1.0); }
+    uint32_t minus_one() { return konst(1, -1.0); }
+    uint32_t neg_zero() { return konst(2, -0.0); }
+    uint32_t zero() { return konst(3, 0.0); }
     uint32_t param(uint32_t p) const { return kSlots + p; }
     uint32_t param_adj(uint32_t p) const { return kSlots + P + p; }
 
@@ -884,54 +886,67 @@ std::vector<WOp> place_loads(const Lower &W, uint32_t ck_cap, uint32_t *late_at)
 // whole life.  A register read for the last time by a micro-op may be the one
 // it writes at its end.  `spare`: registers below the statics that are free
 // (load slots the program does not use); `early`: those free for lives that
-// end before op late_at.  Returns the registers used.
+// end before op late_at, the one freed last first.  Returns the registers used,
+// or `limit` + 1 where they are more than `limit` (at most 128).
 uint32_t place_registers(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t n_static,
-                         const std::vector<uint32_t> &spare, const std::vector<uint32_t> &early, uint32_t late_at) {
-    std::vector<uint32_t> first(n_virtual, kUnsetTime), last(n_virtual, 0);
+                         const std::vector<uint32_t> &spare, const std::vector<uint32_t> &early, uint32_t late_at,
+                         uint32_t limit) {
+    // Lives, in half op steps (a write at a micro-op's end is the later half).
+    std::vector<uint32_t> first(n_virtual, kUnsetTime), last(n_virtual, 0), order;
+    order.reserve(n_virtual);
     for (uint32_t i = 0; i < ops.size(); ++i) {
         const WOp &u = ops[i];
         const char *role = roles(u.cls);
+        const size_t seen = order.size();
         for (uint32_t q = 0; q < u.n; ++q) {
             if (u.r[q] < kVirtual) continue;
             const uint32_t v = u.r[q] - kVirtual;
             const uint32_t when = 2 * i + (role[q] == 'd' ? 1 : 0);
-            if (first[v] == kUnsetTime) first[v] = when;
+            if (first[v] == kUnsetTime) {
+                first[v] = when;
+                order.push_back(v);
+            }
             last[v] = std::max(last[v], when);
         }
+        if (order.size() > seen + 1)
+            std::sort(order.begin() + seen, order.end(),
+                      [&](uint32_t a, uint32_t b) { return first[a] != first[b] ? first[a] < first[b] : a < b; });
     }
-    std::vector<uint32_t> order;
-    for (uint32_t v = 0; v < n_virtual; ++v)
-        if (first[v] != kUnsetTime) order.push_back(v);
-    std::sort(order.begin(), order.end(),
-              [&](uint32_t a, uint32_t b) { return first[a] != first[b] ? first[a] < first[b] : a < b; });
-    std::vector<uint32_t> reg(n_virtual, 0);
-    std::priority_queue<uint32_t, std::vector<uint32_t>, std::greater<uint32_t>> free_regs;
-    for (uint32_t r : spare) free_regs.push(r);
+    // free registers by number, the early ones as a stack; the lives that end
+    // at each half step as a list
+    uint64_t open[2] = {0, 0};
+    auto release = [&](uint32_t r) { open[r / 64] |= 1ull << (r % 64); };
+    for (uint32_t r : spare) release(r);
     std::vector<uint32_t> free_early(early.rbegin(), early.rend());
     std::vector<uint8_t> is_early(kSlots, 0);
     for (uint32_t r : early) is_early[r] = 1;
-    using End = std::pair<uint32_t, uint32_t>;   // (last, register)
-    std::priority_queue<End, std::vector<End>, std::greater<End>> busy;
-    uint32_t next = kSlots + n_static;
+    std::vector<uint32_t> reg(n_virtual, 0), ends(2 * ops.size(), kNone), link(n_virtual, kNone), ended;
+    uint32_t next = kSlots + n_static, now = 0;
     for (uint32_t v : order) {
-        while (!busy.empty() && busy.top().first < first[v]) {
-            const uint32_t r = busy.top().second;
-            if (r < kSlots && is_early[r]) free_early.push_back(r);
-            else free_regs.push(r);
-            busy.pop();
+        for (; now < first[v]; ++now) {
+            if (ends[now] == kNone) continue;
+            ended.clear();
+            for (uint32_t x = ends[now]; x != kNone; x = link[x]) ended.push_back(reg[x]);
+            if (ended.size() > 1) std::sort(ended.begin(), ended.end());
+            for (uint32_t r : ended) {
+                if (r < kSlots && is_early[r]) free_early.push_back(r);
+                else release(r);
+            }
         }
         uint32_t r;
         if (!free_early.empty() && last[v] / 2 < late_at) {
             r = free_early.back();
             free_early.pop_back();
-        } else if (free_regs.empty()) {
-            r = next++;
+        } else if (open[0] | open[1]) {
+            r = open[0] ? uint32_t(__builtin_ctzll(open[0])) : 64 + uint32_t(__builtin_ctzll(open[1]));
+            open[r / 64] &= open[r / 64] - 1;
         } else {
-            r = free_regs.top();
-            free_regs.pop();
+            r = next++;
+            if (next > limit) return next;
         }
         reg[v] = r;
-        busy.push({last[v], r});
+        link[v] = ends[last[v]];
+        ends[last[v]] = v;
     }
     for (WOp &u : ops)
         for (uint32_t q = 0; q < u.n; ++q)
@@ -950,7 +965,7 @@ uint32_t place_registers(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t n_s
 // against 671, 647, 646, 646; Lotka-Volterra saving 1849 against 1590, 1583,
 // 1559, 1559, recomputing (runs of 9 as it is) 1646 against 1649, 1648, 1647,
 // 1646; twelve random programs 11.8 against 11.6, 11.2, 11.0, 11.0 million.
-constexpr uint32_t kOrderWindow = 32;
+constexpr uint32_t kOrderWindow = 32;   // (at most 64: members are bits of a word)
 void order_ops(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t sink, uint32_t late_at, uint32_t window) {
     const uint32_t n_regs = kRegs + n_virtual;
     auto reg_of = [&](uint32_t r) { return r < kVirtual ? r : kRegs + (r - kVirtual); };
@@ -958,8 +973,10 @@ void order_ops(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t sink, uint32_
     std::vector<uint32_t> writer(n_regs, 0), seen(n_regs, 0);
     std::vector<std::vector<uint32_t>> readers(n_regs);
     uint32_t region = 0;
-    std::vector<std::vector<uint32_t>> preds;
-    std::vector<uint32_t> left, taken;   // in order; taken: mark of an op in a run (0: not)
+    std::vector<uint32_t> preds, preds_of;   // of op i in the region: preds[preds_of[i] .. preds_of[i + 1]]
+    std::vector<uint32_t> mark_of;           // run that last held the op (0: none; kNone: placed)
+    std::vector<uint32_t> ahead, run, best, classes;   // ahead: the window's ops, in order
+    uint64_t members[kClasses];
     std::vector<WOp> out;
     auto fixed = [&](uint32_t cls) { return cls >= LDK0 && cls <= WAITPF; };
     for (uint32_t b = 0; b < ops.size();) {
@@ -973,7 +990,8 @@ void order_ops(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t sink, uint32_
         }
         const uint32_t n = e - b;
         ++region;
-        preds.assign(n, {});
+        preds.clear();
+        preds_of.assign(1, 0);
         for (uint32_t i = 0; i < n; ++i) {
             const WOp &u = ops[b + i];
             const char *role = roles(u.cls);
@@ -985,51 +1003,58 @@ void order_ops(std::vector<WOp> &ops, uint32_t n_virtual, uint32_t sink, uint32_
                     writer[r] = kNone;
                     readers[r].clear();
                 }
-                if (writer[r] != kNone && writer[r] != i) preds[i].push_back(writer[r]);
+                if (writer[r] != kNone && writer[r] != i) preds.push_back(writer[r]);
                 if (role[q] == 'u') {
                     readers[r].push_back(i);
                 } else {
                     for (uint32_t k : readers[r])
-                        if (k != i) preds[i].push_back(k);
+                        if (k != i) preds.push_back(k);
                     readers[r].clear();
                     writer[r] = i;
                 }
             }
+            preds_of.push_back(uint32_t(preds.size()));
         }
-        left.resize(n);
-        for (uint32_t i = 0; i < n; ++i) left[i] = i;
-        taken.assign(n, 0);
-        uint32_t mark = 0;
+        mark_of.assign(n, 0);
+        uint32_t mark = 0, next = 0;
         out.clear();
-        std::vector<uint8_t> done(n, 0);
-        std::vector<uint32_t> run, best;
-        while (!left.empty()) {
-            const uint32_t w = std::min<uint32_t>(window, uint32_t(left.size()));
+        ahead.clear();
+        for (;;) {
+            while (next < n && ahead.size() < window) ahead.push_back(next++);
+            if (ahead.empty()) break;
             best.clear();
-            uint64_t tried = 0;
-            for (uint32_t c0 = 0; c0 < w; ++c0) {
-                const uint32_t cls = ops[b + left[c0]].cls;
-                if (tried >> cls & 1u) continue;
-                tried |= 1ull << cls;
+            uint64_t present = 0;   // classes in the window; the ops of each, in the order of the classes' first
+            classes.clear();
+            for (uint32_t k = 0; k < ahead.size(); ++k) {
+                const uint32_t cls = ops[b + ahead[k]].cls;
+                if (!(present >> cls & 1u)) {
+                    present |= 1ull << cls;
+                    members[cls] = 0;
+                    classes.push_back(cls);
+                }
+                members[cls] |= 1ull << k;
+            }
+            for (uint32_t cls : classes) {
+                if (uint32_t(__builtin_popcountll(members[cls])) <= best.size()) continue;   // no longer run
                 ++mark;
                 run.clear();
-                for (uint32_t k = c0; k < w && run.size() < kInfo[cls].max; ++k) {
-                    const uint32_t i = left[k];
-                    if (ops[b + i].cls != cls) continue;
+                for (uint64_t left = members[cls]; left && run.size() < kInfo[cls].max; left &= left - 1) {
+                    const uint32_t i = ahead[__builtin_ctzll(left)];
                     bool ready = true;
-                    for (uint32_t p : preds[i]) ready = ready && (done[p] || taken[p] == mark);
+                    for (uint32_t p = preds_of[i + 1]; ready && p-- > preds_of[i];)
+                        ready = mark_of[preds[p]] == kNone || mark_of[preds[p]] == mark;
                     if (!ready) continue;
-                    taken[i] = mark;
+                    mark_of[i] = mark;
                     run.push_back(i);
                 }
                 if (run.size() > best.size()) best.swap(run);
             }
             for (uint32_t i : best) {
-                done[i] = 1;
+                mark_of[i] = kNone;
                 out.push_back(ops[b + i]);
             }
-            left.erase(std::remove_if(left.begin(), left.begin() + w, [&](uint32_t i) { return done[i] != 0; }),
-                       left.begin() + w);
+            ahead.erase(std::remove_if(ahead.begin(), ahead.end(), [&](uint32_t i) { return mark_of[i] == kNone; }),
+                        ahead.end());
         }
         std::copy(out.begin(), out.end(), ops.begin() + b);
         b = e;
@@ -1238,8 +1263,9 @@ WideSchedule schedule_in(const Tape &t, bool with_grad, bool save_reads, uint32_
     for (uint32_t k = 0; k < I.N; ++k)
         if (I.kind[k] == K_COMP && I.vlive[k]) total += I.nel[k];
     total = std::max<uint64_t>(total, 1);
-    // (a search over sizes needs the registers only; the chosen one is laid out)
-    auto trial = [&](uint64_t size, bool full = false) {
+    bool lds_fit = true;   // whether the last trial's matrices fitted, if its registers did
+    // (a search over sizes needs the registers only; the chosen one is encoded)
+    auto trial = [&](uint64_t size, std::vector<WOp> *out) {
         Builder B(I);
         B.save_reads = save_reads;
         B.resident.assign(I.N, 0);
@@ -1256,6 +1282,7 @@ WideSchedule schedule_in(const Tape &t, bool with_grad, bool save_reads, uint32_
         Lower W(I, B, with_grad, mats);
         W.run();
         WideSchedule S;
+        lds_fit = true;
         // (what follows numbers every register below kVirtual as one of the file)
         if (kSlots + uint64_t(W.n_static) > regs) return S;
         const uint32_t ck_cap = ck_slots(save_reads, mats);
@@ -1274,40 +1301,60 @@ WideSchedule schedule_in(const Tape &t, bool with_grad, bool save_reads, uint32_
                     (late_at == UINT32_MAX ? spare : early).push_back(2 * kObsSlots + half * kCkSlots + i);
         }
         if (order && !mats) order_ops(ops, W.n_virtual, W.kSink, late_at, kOrderWindow);
-        S.n_regs = place_registers(ops, W.n_virtual, W.n_static, spare, early, late_at);
+        S.n_regs = place_registers(ops, W.n_virtual, W.n_static, spare, early, late_at, regs);
+        if (S.n_regs > regs) return S;
         S.matrices = mats;
         S.lds_rows = place_matrices(ops, W.mem_size);
+        lds_fit = S.lds_rows <= lds_rows;
         S.n_ckpt_rows = W.n_rows * (mats ? 4 : 1);
         S.n_segments = uint32_t(B.cuts.size());
         S.consts = W.consts;
-        S.ok = S.n_regs <= regs && S.lds_rows <= lds_rows && S.n_ckpt_rows < (1u << 31);
-        if (S.ok && full) emit(ops, &S);
+        S.ok = lds_fit && S.n_ckpt_rows < (1u << 31);
+        *out = std::move(ops);
         return S;
     };
-    if (!with_grad) return trial(0, true);
+    std::vector<WOp> ops;
+    WideSchedule best;
+    auto encoded = [&](WideSchedule &&S) {
+        if (S.ok) emit(ops, &S);
+        return std::move(S);
+    };
+    if (!with_grad) return encoded(trial(0, &ops));
     // The largest segment size that fits the register file (doubled or halved
     // from a usual one, then bisection), and the size that cuts the trace
     // evenly into as many segments (which cuts every step of a loop at the
     // same point): the cheaper of the two.
-    if (trial(total).ok) return trial(total, true);   // the whole trace in one segment
+    constexpr uint64_t kShortest = 4;
+    std::vector<WOp> last;
+    auto fits = [&](uint64_t size) {   // `best` and `ops`: of the last size that does
+        WideSchedule S = trial(size, &last);
+        if (!S.ok) return false;
+        best = std::move(S);
+        ops.swap(last);
+        return true;
+    };
+    if (fits(total)) return encoded(std::move(best));   // the whole trace in one segment
     uint64_t lo = std::min<uint64_t>(80, total), hi = 0;   // lo fits, hi does not
-    while (!trial(lo).ok) {
+    while (!fits(lo)) {
+        // where the matrices of the shortest segments do not fit either, no
+        // length between is tried (a longer one holds more at a time)
+        if (!hi && !lds_fit && !fits(kShortest) && !lds_fit) return none;
         hi = lo;
         lo /= 2;
-        if (lo < 4) return none;
+        if (lo < kShortest) return none;
     }
     while (!hi) {
-        if (trial(2 * lo).ok) lo *= 2;
+        if (fits(2 * lo)) lo *= 2;
         else hi = 2 * lo;
     }
     while (hi - lo > std::max<uint64_t>(4, lo / 16)) {
         const uint64_t mid = lo + (hi - lo) / 2;
-        (trial(mid).ok ? lo : hi) = mid;
+        (fits(mid) ? lo : hi) = mid;
     }
-    WideSchedule best = trial(lo, true);
+    best = encoded(std::move(best));
     const uint64_t even = total / best.n_segments;
     if (even > 0 && even != lo) {
-        WideSchedule alt = trial(even, true);
+        WideSchedule alt = encoded(trial(even, &ops));
         if (alt.ok && alt.cost < best.cost) best = std::move(alt);
     }
     return best;
