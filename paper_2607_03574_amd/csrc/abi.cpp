@@ -466,14 +466,12 @@ int64_t lpad_of(int64_t L) { return (L + 63) / 64 * 64; }
 // Largest padded lane count of a wide launch (a row's bytes are a 32-bit
 // number there).
 constexpr int64_t kWideMaxLanes = (int64_t(1) << 27) - 64;
-// A wide launch of one wave must fit the static scratch array by itself, so
-// that any launch the array serves can be served in parts.
-bool wide_rows_fit(const WideProg &w) {
-    return (uint64_t(w.meta.n_ckpt_rows) + slot::kMaxBlock) * 64 * sizeof(double) <= scratch_bytes();
-}
 // Workspace rows of a wide program (the slot kernel's trash rows included, so
 // that no launch has an empty workspace).
 uint64_t wide_rows(const WideProg &w) { return uint64_t(w.meta.n_ckpt_rows) + slot::kMaxBlock; }
+// Lanes that a launch over L lanes on the static scratch array runs at a time
+// (0: the wide kernel cannot serve it there).
+int64_t wide_scratch_part(const WideProg &w, int64_t L) { return scratch_part(wide_rows(w), L, scratch_bytes()); }
 
 // The wide program of a gradient launch over L lanes, or null.  As for the
 // slot kernel's programs, a compute call needs a sizing call before it whose
@@ -485,7 +483,7 @@ ndvm_status wide_grad_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, int6
     WideProg *w = nullptr;
     const uint32_t b = reg_budget(p, waves_of(L, n_prog, slot::kMaxSlots), slot::kMaxSlots);
     ndvm_status st = wide_grad_program(tape, wide_lds_rows(b), build, &w);
-    if (st != NDVM_OK || !w || !wide_rows_fit(*w)) return st;
+    if (st != NDVM_OK || !w) return st;
     std::lock_guard<std::mutex> lk(tape->mu);
     if (build) tape->sized.insert(b);
     if (!tape->sized.count(b)) {
@@ -653,7 +651,7 @@ ndvm_status wide_many(const ndvm_tape *const *tapes, int n_prog, const DevicePro
         WideProg *w = nullptr;
         ndvm_status st = wide_grad_program(t, key, false, &w);
         if (st != NDVM_OK) return st;
-        if (!w || !wide_rows_fit(*w)) return NDVM_OK;
+        if (!w) return NDVM_OK;
     }
     for (int q = 0; q < n_prog; ++q) {
         WideProg *w = nullptr;
@@ -1018,6 +1016,14 @@ ndvm_status ndvm_workspace_bytes(const ndvm_tape *tape, int64_t L, int with_grad
             if (st != NDVM_OK) return st;
             if (w) {
                 *bytes = size_t(wide_rows(*w) * uint64_t(Lp) * sizeof(double));
+                // the slot program too, for ndvm_grad_noalloc, where one wave of
+                // the wide kernel has more rows than the scratch array and the
+                // slot kernel, whose registers hold up to twenty times as much,
+                // may have fewer; that it cannot be made is no error here
+                if (!wide_scratch_part(*w, L) &&
+                    slot_may_fit(w->meta, tape->policy == NDVM_POLICY_SAVE, reg_budget(p, waves_of(L, 1, S), S),
+                                 scratch_bytes() / (uint64_t(Lp) * sizeof(double))))
+                    (void)single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, true, &dp, &b);
                 return NDVM_OK;
             }
             st = single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, true, &dp, &b);
@@ -1148,7 +1154,7 @@ static ndvm_status wide_grad_launch(const WideProg &w, const double *params, int
     size_t need = size_t(wide_rows(w) * uint64_t(lpad_of(L)) * sizeof(double));
     if (static_ws) {
         if (need > scratch_bytes() && (!w.meta.matrices || need <= 4 * scratch_bytes())) {
-            part = int64_t(scratch_bytes() / (wide_rows(w) * sizeof(double))) / 64 * 64;
+            part = wide_scratch_part(w, L);
             need = size_t(wide_rows(w) * uint64_t(part) * sizeof(double));
         }
         const ndvm_status st = static_workspace(need, who, &ws, &ws_bytes);
@@ -1186,10 +1192,16 @@ static ndvm_status grad_impl(const ndvm_tape *tape, const double *params, int64_
     const uint32_t S = choose_slots(p, L, 1);
     WideProg *wp = nullptr;
     if ((st = wide_grad_for(const_cast<ndvm_tape *>(tape), p, L, 1, false, &wp)) != NDVM_OK) return st;
-    if (wp) return wide_grad_launch(*wp, params, L, ld_p, obs, loss, grad, ld_g, ws, ws_bytes, static_ws, stream, who);
+    const bool small = wp && static_ws && !wide_scratch_part(*wp, L);   // the array, for the wide kernel
+    if (wp && !small)
+        return wide_grad_launch(*wp, params, L, ld_p, obs, loss, grad, ld_g, ws, ws_bytes, static_ws, stream, who);
     uint32_t b = 0;
     DevProg *dp;
-    if ((st = single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, false, &dp, &b)) != NDVM_OK) return st;
+    if ((st = single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, false, &dp, &b)) != NDVM_OK) {
+        if (!small) return st;
+        // sizing made no slot program: it would not fit either
+        return static_workspace(size_t(wide_rows(*wp) * uint64_t(Lp) * sizeof(double)), who, &ws, &ws_bytes);
+    }
     uint32_t r_lds = std::min(dp->meta.n_regs, b);
     size_t need = size_t(ws_rows(*dp, b) * uint64_t(Lp) * sizeof(double));
     if (static_ws && (st = static_workspace(need, who, &ws, &ws_bytes)) != NDVM_OK) return st;

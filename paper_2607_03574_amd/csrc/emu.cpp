@@ -308,6 +308,26 @@ int64_t ndvm_emu_program(const uint8_t *tape, size_t len, int with_grad, uint32_
 }
 
 /*
+ * How the wide kernel would serve ndvm_grad_noalloc of `tape` over `lanes` lanes
+ * on an array of `bytes`: out[0] lanes at a time (0: not at all), out[1] whether
+ * the slot kernel with `budget` registers may fit the array, out[2] workspace
+ * rows.  Arguments and result otherwise as ndvm_emu_wide.
+ */
+int ndvm_emu_scratch(const uint8_t *tape, size_t len, int mode, uint32_t lds_rows, int64_t lanes, uint32_t budget,
+                     uint64_t bytes, int64_t *out) {
+    Tape t;
+    ndvm_status st = parse_tape(tape, len, &t);
+    if (st != NDVM_OK) return -int(st);
+    const WideSchedule S = schedule_wide(t, true, mode == 2, lds_rows);
+    if (!S.ok) return 1;
+    const uint64_t rows = uint64_t(S.n_ckpt_rows) + slot::kMaxBlock, padded = uint64_t(lanes + 63) / 64 * 64;
+    out[0] = scratch_part(rows, lanes, bytes);
+    out[1] = slot_may_fit(S, mode == 2, budget, bytes / (8 * padded));
+    out[2] = int64_t(rows);
+    return 0;
+}
+
+/*
  * Schedule `tape` for the wide kernel (mode: 0 forward only, 1 gradient with
  * the recompute policy, 2 with the save policy) and run its blocks for L lanes
  * on the host, micro-op by micro-op as the kernel does.  Reads of registers

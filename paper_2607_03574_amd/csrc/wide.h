@@ -35,6 +35,7 @@
 // bits 12-15 the operand roles the index applies to (kSrc: source 0, kDst:
 // destination), the form M0 takes.
 #pragma once
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <vector>
@@ -167,7 +168,27 @@ struct WideSchedule {
     uint64_t cost = 0;            // estimated cycles of a lone wave
     bool matrices = false;
     uint32_t lds_rows = 0;        // matrix elements in LDS
+    uint64_t read_elems = 0;      // elements of the values that adjoint rules read (leaves apart)
+    uint64_t ckpt_elems = 0;      // elements of the segments' stored inputs
 };
+
+// Lanes that a launch of `rows` workspace rows runs at a time on an array of
+// `bytes`: all of them, a multiple of 64, or 0 where not even 64 fit.
+constexpr int64_t scratch_part(uint64_t rows, int64_t lanes, uint64_t bytes) {
+    const uint64_t fit = bytes / (8 * rows) / 64 * 64;
+    return int64_t(fit) >= lanes ? lanes : int64_t(fit);
+}
+// Whether the slot kernel, with `budget` registers a lane, may do with `rows`
+// workspace rows where the wide program is S: an estimate with a factor of two
+// to spare, made so that the slot program need not be.  Saving, that kernel too
+// stores what the adjoint rules read, save what its registers hold.
+// Recomputing, its registers hold the values read of one segment, and each
+// segment but the first stores as many elements as one of S's.
+constexpr bool slot_may_fit(const WideSchedule &S, bool save_reads, uint32_t budget, uint64_t rows) {
+    if (save_reads) return S.read_elems <= 2 * (rows + budget);
+    const uint64_t inputs = S.n_segments > 1 ? S.ckpt_elems / (S.n_segments - 1) : 0;
+    return S.read_elems / std::max(budget, 1u) * inputs <= 2 * rows;
+}
 
 // Wide program of a tape: forward only, or forward and reverse (save_reads as
 // schedule_grad).  lds_rows: matrix elements a wave may hold in LDS.

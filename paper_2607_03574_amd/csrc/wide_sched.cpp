@@ -1263,6 +1263,15 @@ WideSchedule schedule_in(const Tape &t, bool with_grad, bool save_reads, uint32_
     for (uint32_t k = 0; k < I.N; ++k)
         if (I.kind[k] == K_COMP && I.vlive[k]) total += I.nel[k];
     total = std::max<uint64_t>(total, 1);
+    uint64_t read_elems = 0;
+    if (with_grad) {
+        std::vector<uint8_t> read(I.N, 0);
+        auto count = [&](uint32_t s) {
+            if (I.kind[s] == K_COMP && !read[s]) read[s] = 1, read_elems += I.nel[s];
+        };
+        for (uint32_t k = 0; k < I.N; ++k)
+            if (I.need_rev[k]) I.for_revreads(k, count);
+    }
     bool lds_fit = true;   // whether the last trial's matrices fitted, if its registers did
     // (a search over sizes needs the registers only; the chosen one is encoded)
     auto trial = [&](uint64_t size, std::vector<WOp> *out) {
@@ -1308,6 +1317,9 @@ WideSchedule schedule_in(const Tape &t, bool with_grad, bool save_reads, uint32_
         lds_fit = S.lds_rows <= lds_rows;
         S.n_ckpt_rows = W.n_rows * (mats ? 4 : 1);
         S.n_segments = uint32_t(B.cuts.size());
+        S.read_elems = read_elems;
+        for (const auto &v : B.livein)
+            for (uint32_t s : v) S.ckpt_elems += I.nel[s];
         S.consts = W.consts;
         S.ok = lds_fit && S.n_ckpt_rows < (1u << 31);
         *out = std::move(ops);

@@ -99,3 +99,20 @@ def wide(tape: bytes, params, obs, mode=1, lds_rows=320):
     if rc != 0:
         raise RuntimeError(f"wide emulator rc={rc}: {lib().ndvm_emu_error().decode()}")
     return loss, grad, dict(zip(WIDE_STATS, list(stats)))
+
+
+def scratch(tape: bytes, lanes, mode=1, lds_rows=320, budget=1280, nbytes=64 << 20):
+    """How the wide kernel would serve ndvm_grad_noalloc over `lanes` lanes:
+    (lanes at a time or 0, whether the slot kernel may fit, workspace rows), or
+    None for a tape it does not take."""
+    f = lib().ndvm_emu_scratch
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_char_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_uint32, ctypes.c_int64, ctypes.c_uint32,
+                  ctypes.c_uint64, ctypes.c_void_p]
+    out = (ctypes.c_int64 * 3)()
+    rc = f(tape, len(tape), mode, lds_rows, lanes, budget, nbytes, out)
+    if rc == 1:
+        return None
+    if rc != 0:
+        raise RuntimeError(f"emulator rc={rc}")
+    return out[0], bool(out[1]), out[2]

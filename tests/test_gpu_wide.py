@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from parity import compare
-from wide_cases import cases
+from wide_cases import cases, long_recurrence
 from workloads import configs
 
 pytestmark = pytest.mark.gpu
@@ -52,3 +52,27 @@ def test_noalloc_in_parts_equals_grad(nd):
     nd.grad_noalloc(tape, p, o, l1, g1)
     torch.cuda.synchronize()
     assert torch.equal(l0, l1) and torch.equal(g0, g1)
+
+
+def test_more_rows_than_the_scratch_array_holds(nd, oracle_mod):
+    """A saving program of which one wave exceeds the static scratch array: the
+    wide kernel runs it on a caller's workspace, alone and in a population
+    (its rows, fewer than the slot program's), and the array is too small."""
+    import emu
+    code = long_recurrence(90000)
+    t = nd.tape_build(code)
+    rows = emu.wide(t, np.zeros((0, 2)), np.zeros(0), 2)[2]["n_ckpt_rows"] + 4
+    p = np.array([[2.6, 0.3], [2.9, 0.6], [1.5, 0.9]])
+    L = 70
+    p = np.ascontiguousarray(p[np.arange(L) % 3])
+    ol, og, _ = oracle_mod.run(code, p, np.zeros(0))
+    P, O = torch.tensor(p, device="cuda"), torch.zeros(0, dtype=torch.float64, device="cuda")
+    tape = nd.tape_upload(t, nd.POLICY_SAVE)
+    assert nd.workspace_bytes(tape, L, True) == rows * 128 * 8 > nd.NOALLOC_SCRATCH_BYTES
+    assert nd.workspace_bytes_many([tape], L) == rows * 128 * 8
+    loss, grad = nd.grad(tape, P, O)
+    torch.cuda.synchronize()
+    compare(loss.cpu().numpy(), grad.cpu().numpy(), ol, og)
+    with pytest.raises(nd.NdvmError) as e:
+        nd.grad_noalloc(tape, P, O, loss, grad)
+    assert e.value.status == nd.E_NOMEM and "static scratch" in str(e.value)

@@ -13,7 +13,7 @@ import pytest
 import emu
 from conftest import ROOT
 from parity import compare
-from wide_cases import cases, lookups, one_element_forms
+from wide_cases import cases, long_recurrence, lookups, one_element_forms, scalars_and_a_product
 from workloads import configs
 from workloads.bytecode import Asm
 
@@ -110,6 +110,64 @@ def test_scheduling_short_programs_costs_no_more_than_for_the_slot_kernel():
         slot = least(lambda: emu.run(t, none, w.obs, budget=1280))
         wide = least(lambda: emu.wide(t, none, w.obs))
         assert wide < 1.4 * slot, (T, wide, slot)
+
+
+def _slot_budget(lanes):
+    """Registers a lane of the slot kernel at `lanes` lanes (16 lanes a wave, 256
+    CUs of 160 KB LDS, at most 16 waves each)."""
+    waves = -(-lanes // 16)
+    return 160 * 1024 // min(16, -(-waves // 256)) // 128
+
+
+def _slot_rows(t, p, obs, lanes, save):
+    """Workspace rows of the slot kernel's launch: checkpoints, trash, spills (a
+    program that does not fit takes the budget of fewer waves a CU)."""
+    b = _slot_budget(lanes)
+    st = emu.run(t, p, obs, budget=b, save=save)[2]
+    if st["n_regs"] > b:
+        b2 = 160 * 1024 // max(1, 160 * 1024 // (st["n_regs"] * 128)) // 128
+        if b2 > b:
+            b, st = b2, emu.run(t, p, obs, budget=b2, save=save)[2]
+    return st["n_ckpt_rows"] + 4 + max(0, st["n_regs"] - b)
+
+
+SCRATCH = 64 << 20
+
+
+@pytest.mark.parametrize("name", ["lotka", "logistic", "kalman", "mixed", "products"])
+def test_slot_launches_that_fit_the_scratch_array_are_expected_to(name):
+    """The estimate of the slot kernel's rows, by which a launch that exceeds the
+    scratch array on the wide kernel is served or refused, excludes no launch
+    whose slot program fits."""
+    if name in ("lotka", "logistic", "kalman"):
+        w = {"lotka": lambda: configs.lotka_volterra(L=1, T=300), "logistic": lambda: configs.logistic(L=1, T=1000),
+             "kalman": lambda: configs.kalman(L=1, T=60)}[name]()
+        t, p, obs = nd.tape_build(w.bytecode), w.params, w.obs
+    else:
+        code = scalars_and_a_product(100, 4, 30) if name == "mixed" else scalars_and_a_product(150, 3, 0)
+        t, p, obs = nd.tape_build(code), np.full((1, 4), 0.25), np.zeros(1)
+    seen = set()
+    for lanes in (64, 1000, 4096, 8192, 16384, 32768):
+        for mode in (1, 2):
+            b = _slot_budget(lanes)
+            part, may, rows = emu.scratch(t, lanes, mode, max(320, b), b)
+            padded = -(-lanes // 64) * 64
+            assert part == min(lanes, SCRATCH // (8 * rows) // 64 * 64)
+            fits = _slot_rows(t, p, obs, lanes, mode == 2) * padded * 8 <= SCRATCH
+            assert may or not fits, (lanes, mode)
+            seen.add((fits, may))
+    assert (True, True) in seen and (False, False) in seen
+
+
+def test_rows_beyond_the_scratch_array():
+    """A wave's rows on both sides of the array's size: the wide program is made
+    either way, and the array serves the smaller one."""
+    for steps, fits in ((43000, True), (44500, False)):
+        t = nd.tape_build(long_recurrence(steps))
+        part, may, rows = emu.scratch(t, 64, 2)
+        assert (rows * 64 * 8 <= SCRATCH) == fits and part == (64 if fits else 0) and may
+    part, may, rows = emu.scratch(nd.tape_build(long_recurrence(90000)), 64, 2)
+    assert part == 0 and not may
 
 
 def test_programs_left_to_the_slot_kernel():

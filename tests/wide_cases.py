@@ -61,6 +61,24 @@ def large(A):
     return A.loadl(31).index(1, 2).mul().halt().bytes()
 
 
+def long_recurrence(steps):
+    """x <- p0 x (1 - x), steps times (three values a rule reads each)."""
+    return Asm(2, 0).param(1).storel(0).loop(steps).loadl(0).push(1.0).loadl(0).sub().mul().param(0).mul().storel(0) \
+        .endloop().loadl(0).halt().bytes()
+
+
+def scalars_and_a_product(steps, side, n):
+    """A step: a product of side x side matrices, scaled, and n scalar updates."""
+    A = Asm(4, 1)
+    for i in range(side * side):
+        A.param(i % 4)
+    A.pack(side, side).storel(0).param(0).storel(2).param(1).storel(3).loadl(0).storel(5).loop(steps)
+    A.loadl(0).loadl(5).matmul().param(3).mul().storel(5)
+    for _ in range(n):
+        A.loadl(2).param(2).mul().loadl(3).add().param(3).mul().storel(2)
+    return A.endloop().loadl(5).index(0, 0).loadl(2).add().halt().bytes()
+
+
 def lookup(params, n):
     """(p0 * table - y)^2, the table nested branches of n constant leaves over
     thresholds of the other parameters: parameters and constants (which the
