@@ -202,9 +202,10 @@ ndvm_status ndvm_grad(const ndvm_tape *tape, const double *params, int64_t L,
  * results and errors as ndvm_grad, with the same preparation
  * (ndvm_workspace_bytes(tape, L, 1) for this L, made beforehand, where
  * allocation is allowed); a launch whose workspace would exceed the array is
- * rejected with NDVM_E_NOMEM before anything is enqueued, except that a scalar
- * program's launch may run in parts of its lanes, each within the array, one
- * after the other on `stream`.  Nothing in the
+ * rejected with NDVM_E_NOMEM before anything is enqueued, except that one of up
+ * to four times the array (up to 128 times where the program's stored values
+ * alone are few enough for the array) may run in parts of its lanes, each within
+ * the array, one after the other on `stream`.  Nothing in the
  * array needs to start at zero (every row is written before it is read), and
  * it keeps the last call's contents.  All calls on one GPU share the array:
  * calls that can overlap on one GPU (several streams, several threads) race

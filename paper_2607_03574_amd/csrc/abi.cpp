@@ -469,9 +469,14 @@ constexpr int64_t kWideMaxLanes = (int64_t(1) << 27) - 64;
 // Workspace rows of a wide program (the slot kernel's trash rows included, so
 // that no launch has an empty workspace).
 uint64_t wide_rows(const WideProg &w) { return uint64_t(w.meta.n_ckpt_rows) + slot::kMaxBlock; }
-// Lanes that a launch over L lanes on the static scratch array runs at a time
-// (0: the wide kernel cannot serve it there).
-int64_t wide_scratch_part(const WideProg &w, int64_t L) { return scratch_part(wide_rows(w), L, scratch_bytes()); }
+// Lanes that a gradient launch over L lanes on the static scratch array runs at
+// a time (0: not on the wide kernel); *slot_fits: the slot kernel may serve it.
+int64_t wide_scratch_part(const ndvm_tape *t, const WideProg &w, const DeviceProps &p, int64_t L, bool *slot_fits) {
+    const uint32_t b = reg_budget(p, waves_of(L, 1, slot::kMaxSlots), slot::kMaxSlots);
+    *slot_fits = slot_may_fit(w.meta, t->policy == NDVM_POLICY_SAVE, b,
+                              scratch_bytes() / (uint64_t(lpad_of(L)) * sizeof(double)));
+    return scratch_part(wide_rows(w), L, scratch_bytes(), *slot_fits);
+}
 
 // The wide program of a gradient launch over L lanes, or null.  As for the
 // slot kernel's programs, a compute call needs a sizing call before it whose
@@ -1016,13 +1021,11 @@ ndvm_status ndvm_workspace_bytes(const ndvm_tape *tape, int64_t L, int with_grad
             if (st != NDVM_OK) return st;
             if (w) {
                 *bytes = size_t(wide_rows(*w) * uint64_t(Lp) * sizeof(double));
-                // the slot program too, for ndvm_grad_noalloc, where one wave of
-                // the wide kernel has more rows than the scratch array and the
-                // slot kernel, whose registers hold up to twenty times as much,
-                // may have fewer; that it cannot be made is no error here
-                if (!wide_scratch_part(*w, L) &&
-                    slot_may_fit(w->meta, tape->policy == NDVM_POLICY_SAVE, reg_budget(p, waves_of(L, 1, S), S),
-                                 scratch_bytes() / (uint64_t(Lp) * sizeof(double))))
+                // the slot program too, for ndvm_grad_noalloc, where the wide
+                // kernel has too many rows for the scratch array and the slot
+                // kernel may not; that it cannot be made is no error here
+                bool slot_fits;
+                if (!wide_scratch_part(tape, *w, p, L, &slot_fits) && slot_fits)
                     (void)single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, true, &dp, &b);
                 return NDVM_OK;
             }
@@ -1141,25 +1144,12 @@ static ndvm_status static_workspace(size_t need, const char *who, void **ws, siz
     return NDVM_OK;
 }
 
-// A gradient launch of the wide kernel.  On the static scratch array, a
-// launch whose rows do not fit runs as several launches over parts of its
-// lanes, one after the other on `stream`: the slot kernel can need fewer rows
-// (its register budget is larger for few lanes, it stores nothing for the loss
-// and pads no matrix to quads), and no launch that fitted the array with it is
-// refused.  With matrices that is a factor of 4 at most.
+// A gradient launch of the wide kernel.  On the static scratch array it runs
+// as several launches over `part` lanes each, one after the other on `stream`.
 static ndvm_status wide_grad_launch(const WideProg &w, const double *params, int64_t L, int64_t ld_p,
                                     const double *obs, double *loss, double *grad, int64_t ld_g, void *ws,
-                                    size_t ws_bytes, bool static_ws, void *stream, const char *who) {
-    int64_t part = L;
-    size_t need = size_t(wide_rows(w) * uint64_t(lpad_of(L)) * sizeof(double));
-    if (static_ws) {
-        if (need > scratch_bytes() && (!w.meta.matrices || need <= 4 * scratch_bytes())) {
-            part = wide_scratch_part(w, L);
-            need = size_t(wide_rows(w) * uint64_t(part) * sizeof(double));
-        }
-        const ndvm_status st = static_workspace(need, who, &ws, &ws_bytes);
-        if (st != NDVM_OK) return st;
-    }
+                                    size_t ws_bytes, int64_t part, void *stream, const char *who) {
+    const size_t need = size_t(wide_rows(w) * uint64_t(lpad_of(part)) * sizeof(double));
     if (!ws || ws_bytes < need) {
         set_error(std::string(who) + ": workspace too small");
         return NDVM_E_NOMEM;
@@ -1192,16 +1182,19 @@ static ndvm_status grad_impl(const ndvm_tape *tape, const double *params, int64_
     const uint32_t S = choose_slots(p, L, 1);
     WideProg *wp = nullptr;
     if ((st = wide_grad_for(const_cast<ndvm_tape *>(tape), p, L, 1, false, &wp)) != NDVM_OK) return st;
-    const bool small = wp && static_ws && !wide_scratch_part(*wp, L);   // the array, for the wide kernel
-    if (wp && !small)
-        return wide_grad_launch(*wp, params, L, ld_p, obs, loss, grad, ld_g, ws, ws_bytes, static_ws, stream, who);
+    int64_t part = L;   // lanes at a time
+    bool slot_fits = true;
+    if (wp && static_ws && (part = wide_scratch_part(tape, *wp, p, L, &slot_fits)) > 0 &&
+        (st = static_workspace(size_t(wide_rows(*wp) * uint64_t(lpad_of(part)) * sizeof(double)), who, &ws, &ws_bytes)) !=
+            NDVM_OK)
+        return st;
+    if (wp && part > 0)
+        return wide_grad_launch(*wp, params, L, ld_p, obs, loss, grad, ld_g, ws, ws_bytes, part, stream, who);
     uint32_t b = 0;
-    DevProg *dp;
-    if ((st = single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, false, &dp, &b)) != NDVM_OK) {
-        if (!small) return st;
-        // sizing made no slot program: it would not fit either
-        return static_workspace(size_t(wide_rows(*wp) * uint64_t(Lp) * sizeof(double)), who, &ws, &ws_bytes);
-    }
+    DevProg *dp = nullptr;
+    st = slot_fits ? single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, false, &dp, &b) : NDVM_E_NOMEM;
+    if (st != NDVM_OK)   // (a launch that the array cannot serve, or a tape that was not sized)
+        return wp ? static_workspace(size_t(wide_rows(*wp) * uint64_t(Lp) * sizeof(double)), who, &ws, &ws_bytes) : st;
     uint32_t r_lds = std::min(dp->meta.n_regs, b);
     size_t need = size_t(ws_rows(*dp, b) * uint64_t(Lp) * sizeof(double));
     if (static_ws && (st = static_workspace(need, who, &ws, &ws_bytes)) != NDVM_OK) return st;

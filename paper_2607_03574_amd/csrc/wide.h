@@ -172,12 +172,6 @@ struct WideSchedule {
     uint64_t ckpt_elems = 0;      // elements of the segments' stored inputs
 };
 
-// Lanes that a launch of `rows` workspace rows runs at a time on an array of
-// `bytes`: all of them, a multiple of 64, or 0 where not even 64 fit.
-constexpr int64_t scratch_part(uint64_t rows, int64_t lanes, uint64_t bytes) {
-    const uint64_t fit = bytes / (8 * rows) / 64 * 64;
-    return int64_t(fit) >= lanes ? lanes : int64_t(fit);
-}
 // Whether the slot kernel, with `budget` registers a lane, may do with `rows`
 // workspace rows where the wide program is S: an estimate with a factor of two
 // to spare, made so that the slot program need not be.  Saving, that kernel too
@@ -188,6 +182,19 @@ constexpr bool slot_may_fit(const WideSchedule &S, bool save_reads, uint32_t bud
     if (save_reads) return S.read_elems <= 2 * (rows + budget);
     const uint64_t inputs = S.n_segments > 1 ? S.ckpt_elems / (S.n_segments - 1) : 0;
     return S.read_elems / std::max(budget, 1u) * inputs <= 2 * rows;
+}
+// Lanes that a gradient launch of `rows` workspace rows runs at a time on the
+// static scratch array of `bytes`: all of them, or a multiple of 64 where the
+// launch needs no more than four arrays; where the slot kernel may have fitted
+// the array (its registers hold up to twelve times as much, and no rows are
+// padded to quads there: up to 87 times the rows for a recomputing recurrence on
+// 8,192 lanes), 128 arrays, so that what it took is not refused.  0 beyond that
+// and where not even 64 lanes fit.
+constexpr uint64_t kFewArrays = 4, kManyArrays = 128;
+constexpr int64_t scratch_part(uint64_t rows, int64_t lanes, uint64_t bytes, bool slot_fits) {
+    const uint64_t fit = bytes / (8 * rows) / 64 * 64, need = 8 * rows * (uint64_t(lanes + 63) / 64 * 64);
+    if (need <= bytes) return lanes;
+    return need <= (slot_fits ? kManyArrays : kFewArrays) * bytes ? int64_t(fit) : 0;
 }
 
 // Wide program of a tape: forward only, or forward and reverse (save_reads as

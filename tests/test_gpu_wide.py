@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from parity import compare
-from wide_cases import cases, long_recurrence
+from wide_cases import cases, long_recurrence, scalars_and_a_product
 from workloads import configs
 
 pytestmark = pytest.mark.gpu
@@ -52,6 +52,37 @@ def test_noalloc_in_parts_equals_grad(nd):
     nd.grad_noalloc(tape, p, o, l1, g1)
     torch.cuda.synchronize()
     assert torch.equal(l0, l1) and torch.equal(g0, g1)
+
+
+@pytest.mark.parametrize("name,L,steps", [("kalman", 2003, 60), ("mixed", 8000, 200)])
+def test_noalloc_of_matrix_programs_in_parts(nd, name, L, steps):
+    """Programs with matrices that need two and six times the scratch array, the
+    last part ragged; beyond four only because the program recomputes from few
+    values (the Kalman filter that saves is refused there)."""
+    if name == "kalman":
+        w = configs.kalman(L=L, T=steps)
+        code, p, obs, policy = w.bytecode, w.params, w.obs, nd.POLICY_SAVE
+    else:
+        code, obs, policy = scalars_and_a_product(steps, 4, 30), np.zeros(1), nd.POLICY_RECOMPUTE
+        p = np.random.default_rng(3).uniform(0.2, 0.3, (L, 4))
+    tape = nd.tape_upload(nd.tape_build(code), policy)
+    P, O = torch.tensor(p, device="cuda"), torch.tensor(obs, device="cuda")
+    need = nd.workspace_bytes(tape, L, True) / nd.NOALLOC_SCRATCH_BYTES
+    assert (1.5 < need < 4) if name == "kalman" else (4 < need < 8)
+    l0, g0 = nd.grad(tape, P, O)
+    l1, g1 = torch.empty_like(l0), torch.empty_like(g0)
+    nd.grad_noalloc(tape, P, O, l1, g1)
+    torch.cuda.synchronize()
+    assert torch.equal(l0, l1) and torch.equal(g0, g1) and not g0.isnan().any()
+    if name == "kalman":
+        P = P.repeat(4, 1)
+        assert nd.workspace_bytes(tape, 4 * L, True) > 4 * nd.NOALLOC_SCRATCH_BYTES
+        l1, g1 = torch.full((4 * L,), -7.25, dtype=torch.float64, device="cuda"), torch.empty_like(P)
+        with pytest.raises(nd.NdvmError) as e:
+            nd.grad_noalloc(tape, P, O, l1, g1)
+        assert e.value.status == nd.E_NOMEM and "static scratch" in str(e.value)
+        torch.cuda.synchronize()
+        assert torch.all(l1 == -7.25)
 
 
 def test_more_rows_than_the_scratch_array_holds(nd, oracle_mod):

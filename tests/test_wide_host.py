@@ -152,11 +152,31 @@ def test_slot_launches_that_fit_the_scratch_array_are_expected_to(name):
             b = _slot_budget(lanes)
             part, may, rows = emu.scratch(t, lanes, mode, max(320, b), b)
             padded = -(-lanes // 64) * 64
-            assert part == min(lanes, SCRATCH // (8 * rows) // 64 * 64)
+            need = 8 * rows * padded
+            whole = min(lanes, SCRATCH // (8 * rows) // 64 * 64)
+            assert part == (lanes if need <= SCRATCH else whole if need <= (128 if may else 4) * SCRATCH else 0)
             fits = _slot_rows(t, p, obs, lanes, mode == 2) * padded * 8 <= SCRATCH
             assert may or not fits, (lanes, mode)
             seen.add((fits, may))
     assert (True, True) in seen and (False, False) in seen
+
+
+@pytest.mark.parametrize("name,lanes,mode,served", [
+    # what the slot kernel took stays served: 13 rows there, 9 arrays here; 583 and 6 arrays, a program with matrices
+    ("logistic2000", 32768, 1, True), ("mixed200", 8192, 1, True),
+    # what it refused is refused again beyond four arrays, however few the lanes of a part
+    ("kalman200", 16384, 1, False), ("lotka1000", 4096, 2, False), ("long43000", 4096, 2, False), ("lotka300", 9999, 2, False),
+    # up to four arrays in parts
+    ("lotka1000", 13007, 1, True), ("kalman60", 4096, 2, True)])
+def test_scratch_launches_in_parts(name, lanes, mode, served):
+    kind, n = name.rstrip("0123456789"), int(name.lstrip("abcdefghijklmnopqrstuvwxyz"))
+    code = {"lotka": lambda: configs.lotka_volterra(L=1, T=n).bytecode, "kalman": lambda: configs.kalman(L=1, T=n).bytecode,
+            "logistic": lambda: configs.logistic(L=1, T=n).bytecode, "long": lambda: long_recurrence(n),
+            "mixed": lambda: scalars_and_a_product(n, 4, 30)}[kind]()
+    b = _slot_budget(lanes)
+    part, _, rows = emu.scratch(nd.tape_build(code), lanes, mode, max(320, b), b)
+    assert 8 * rows * lanes > SCRATCH
+    assert (part >= 64 and part % 64 == 0 and 8 * rows * part <= SCRATCH) if served else part == 0
 
 
 def test_rows_beyond_the_scratch_array():
