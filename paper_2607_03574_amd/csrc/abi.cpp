@@ -473,8 +473,7 @@ uint64_t wide_rows(const WideProg &w) { return uint64_t(w.meta.n_ckpt_rows) + sl
 // a time (0: not on the wide kernel); *slot_fits: the slot kernel may serve it.
 int64_t wide_scratch_part(const ndvm_tape *t, const WideProg &w, const DeviceProps &p, int64_t L, bool *slot_fits) {
     const uint32_t b = reg_budget(p, waves_of(L, 1, slot::kMaxSlots), slot::kMaxSlots);
-    *slot_fits = slot_may_fit(w.meta, t->policy == NDVM_POLICY_SAVE, b,
-                              scratch_bytes() / (uint64_t(lpad_of(L)) * sizeof(double)));
+    *slot_fits = slot_may_fit(w.meta, t->policy == NDVM_POLICY_SAVE, b, L, scratch_bytes());
     return scratch_part(wide_rows(w), L, scratch_bytes(), *slot_fits);
 }
 
@@ -1025,7 +1024,7 @@ ndvm_status ndvm_workspace_bytes(const ndvm_tape *tape, int64_t L, int with_grad
                 // kernel has too many rows for the scratch array and the slot
                 // kernel may not; that it cannot be made is no error here
                 bool slot_fits;
-                if (!wide_scratch_part(tape, *w, p, L, &slot_fits) && slot_fits)
+                if (L > 0 && !wide_scratch_part(tape, *w, p, L, &slot_fits) && slot_fits)
                     (void)single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, true, &dp, &b);
                 return NDVM_OK;
             }

@@ -320,8 +320,8 @@ int ndvm_emu_scratch(const uint8_t *tape, size_t len, int mode, uint32_t lds_row
     if (st != NDVM_OK) return -int(st);
     const WideSchedule S = schedule_wide(t, true, mode == 2, lds_rows);
     if (!S.ok) return 1;
-    const uint64_t rows = uint64_t(S.n_ckpt_rows) + slot::kMaxBlock, padded = uint64_t(lanes + 63) / 64 * 64;
-    out[1] = slot_may_fit(S, mode == 2, budget, bytes / (8 * padded));
+    const uint64_t rows = uint64_t(S.n_ckpt_rows) + slot::kMaxBlock;
+    out[1] = slot_may_fit(S, mode == 2, budget, lanes, bytes);
     out[0] = scratch_part(rows, lanes, bytes, out[1]);
     out[2] = int64_t(rows);
     return 0;

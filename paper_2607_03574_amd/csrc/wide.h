@@ -172,13 +172,16 @@ struct WideSchedule {
     uint64_t ckpt_elems = 0;      // elements of the segments' stored inputs
 };
 
-// Whether the slot kernel, with `budget` registers a lane, may do with `rows`
-// workspace rows where the wide program is S: an estimate with a factor of two
-// to spare, made so that the slot program need not be.  Saving, that kernel too
-// stores what the adjoint rules read, save what its registers hold.
-// Recomputing, its registers hold the values read of one segment, and each
+constexpr uint64_t padded_lanes(int64_t lanes) { return uint64_t(lanes + 63) / 64 * 64; }
+// Whether a launch of the slot kernel over `lanes` lanes, with `budget` registers
+// each, may fit an array of `bytes` where the wide program is S: an estimate with
+// a factor of two to spare, made so that the slot program need not be.  Saving,
+// that kernel too stores what the adjoint rules read, save what its registers
+// hold.  Recomputing, its registers hold the values read of one segment, and each
 // segment but the first stores as many elements as one of S's.
-constexpr bool slot_may_fit(const WideSchedule &S, bool save_reads, uint32_t budget, uint64_t rows) {
+constexpr bool slot_may_fit(const WideSchedule &S, bool save_reads, uint32_t budget, int64_t lanes, uint64_t bytes) {
+    if (lanes == 0) return true;
+    const uint64_t rows = bytes / (8 * padded_lanes(lanes));
     if (save_reads) return S.read_elems <= 2 * (rows + budget);
     const uint64_t inputs = S.n_segments > 1 ? S.ckpt_elems / (S.n_segments - 1) : 0;
     return S.read_elems / std::max(budget, 1u) * inputs <= 2 * rows;
@@ -192,7 +195,7 @@ constexpr bool slot_may_fit(const WideSchedule &S, bool save_reads, uint32_t bud
 // and where not even 64 lanes fit.
 constexpr uint64_t kFewArrays = 4, kManyArrays = 128;
 constexpr int64_t scratch_part(uint64_t rows, int64_t lanes, uint64_t bytes, bool slot_fits) {
-    const uint64_t fit = bytes / (8 * rows) / 64 * 64, need = 8 * rows * (uint64_t(lanes + 63) / 64 * 64);
+    const uint64_t fit = bytes / (8 * rows) / 64 * 64, need = 8 * rows * padded_lanes(lanes);
     if (need <= bytes) return lanes;
     return need <= (slot_fits ? kManyArrays : kFewArrays) * bytes ? int64_t(fit) : 0;
 }

@@ -147,6 +147,7 @@ def test_slot_launches_that_fit_the_scratch_array_are_expected_to(name):
         code = scalars_and_a_product(100, 4, 30) if name == "mixed" else scalars_and_a_product(150, 3, 0)
         t, p, obs = nd.tape_build(code), np.full((1, 4), 0.25), np.zeros(1)
     seen = set()
+    assert emu.scratch(t, 0)[:2] == (0, True)
     for lanes in (64, 1000, 4096, 8192, 16384, 32768):
         for mode in (1, 2):
             b = _slot_budget(lanes)
