@@ -83,6 +83,7 @@ constexpr uint64_t lds_bytes(uint32_t depth, uint32_t n_locals, uint32_t n_loops
 // them room), and of the words the IFLT frames and the flags; the stack's, the
 // locals' and the loops' words are held in registers.
 constexpr uint32_t kAdjointRows = 12;
+constexpr uint32_t kDumpWords = 64;   // one per lane, for what is stored unpredicated
 constexpr uint32_t launch_rows(uint32_t depth, uint32_t n_locals, uint32_t n_params) {
     const uint32_t fwd = depth + n_locals, rev = n_params + kAdjointRows;
     return n_params + (fwd > rev ? fwd : rev);
@@ -90,12 +91,15 @@ constexpr uint32_t launch_rows(uint32_t depth, uint32_t n_locals, uint32_t n_par
 constexpr uint64_t launch_lds_bytes(uint32_t depth, uint32_t n_locals, uint32_t n_frames, uint32_t n_nodes,
                                  uint32_t n_params) {
     return 512ull * launch_rows(depth, n_locals, n_params) +
-           4ull * (n_frames * (kFrameFixed + 2 * (depth + n_locals)) + 64 + (n_nodes + 31) / 32);
+           4ull * (n_frames * (kFrameFixed + 2 * (depth + n_locals)) + kDumpWords + (n_nodes + 31) / 32);
 }
 
 // Limits the host validator enforces.
 constexpr uint32_t kMaxDepth = 64, kMaxLocals = 32, kMaxFrames = 32, kMaxLoops = 32;
 constexpr uint64_t kMaxLdsBytes = 64 * 1024;   // structural state of a wave
+// LDS that a launch of an accepted program may ask for: the adjoint rows and the
+// words that nothing reads come on top of the structural state
+constexpr uint64_t kMaxLaunchLdsBytes = kMaxLdsBytes + 512 * kAdjointRows + 4 * kDumpWords;
 constexpr uint64_t kMaxNodes = 1u << 22;   // node * 64 + lane fits 32 bits
 
 struct Args {

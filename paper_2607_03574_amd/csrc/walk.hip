@@ -655,7 +655,7 @@ __global__ void __launch_bounds__(64) ndvm_walk(Args A) {
     W.GC = W.GP + A.n_params * 64;
     W.frm = (AS_LDS uint32_t *)(W.VP + walk::launch_rows(A.depth, A.n_locals, A.n_params) * 64);
     W.dump = W.frm + A.n_frames * W.fsz;
-    W.flg = W.dump + 64;
+    W.flg = W.dump + walk::kDumpWords;
     uint8_t *slot = A.ws + uint64_t(blockIdx.x) * A.n_nodes_max * walk::ws_bytes_per_node();
     W.V = (AS_HBM double *)slot;
     W.G = W.V + uint64_t(A.n_nodes_max) * 64;
@@ -688,12 +688,15 @@ __global__ void __launch_bounds__(64) ndvm_walk(Args A) {
 hipError_t launch_walk(const walk::Args &A, uint32_t grid, hipStream_t stream) {
     if (grid == 0) return hipSuccess;
     static std::once_flag once[64];
+    static hipError_t raised[64];   // the LDS limit, per device
     int dev = 0;
     (void)hipGetDevice(&dev);
-    std::call_once(once[dev & 63], []() {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&ndvm_walk), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  int(walk::kMaxLdsBytes + 512 * walk::kAdjointRows));
+    hipError_t &st = raised[dev & 63];
+    std::call_once(once[dev & 63], [&st]() {
+        st = hipFuncSetAttribute(reinterpret_cast<const void *>(&ndvm_walk), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 int(walk::kMaxLaunchLdsBytes));
     });
+    if (st != hipSuccess) return st;
     hipLaunchKernelGGL(ndvm_walk, dim3(grid), dim3(64), size_t(A.lds_bytes), stream, A);
     return hipGetLastError();
 }

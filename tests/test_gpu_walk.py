@@ -61,6 +61,17 @@ def test_random_programs(nd, oracle_mod, L, seed):
     assert tot["n_lanes"] == 48 * L
 
 
+def test_program_at_the_lds_limit(nd, oracle_mod):
+    """The most structural state the validator accepts: its launch asks for the
+    most LDS, some 70 KiB a wave."""
+    from test_walk_host import at_the_lds_limit
+    bc = at_the_lds_limit()
+    p = np.random.default_rng(5).normal(size=(65, 63))
+    loss, grad = walk(nd, [bc], p[None], np.zeros(0))
+    r = judge(oracle_mod, bc, p, np.zeros(0), loss[0], grad[0])
+    assert r["n_strict"] == 65
+
+
 @pytest.mark.parametrize("name,kw", [("exp_decay", {}), ("logistic_euler", dict(L=300)),
                                      ("lotka_volterra_rk4", dict(L=130, T=40))])
 def test_benchmark_programs(nd, oracle_mod, name, kw):

@@ -105,6 +105,44 @@ def test_nesting_is_measured():
     assert info["n_frames"] == 2 and info["n_params"] == 2
 
 
+def at_the_lds_limit():
+    """63 parameters summed, then a loop of sums: 65,536 bytes of structural state."""
+    A = Asm(63, 0).param(0)
+    for i in range(1, 63):
+        A.param(i).add()
+    return A.loop(7900).param(1).add().endloop().halt().bytes()
+
+
+def test_launch_lds_stays_within_the_limit_set(tmp_path):
+    """No program set the validator accepts asks a launch for more LDS than the
+    kernel's limit is raised to: over the extents of the layout, each with the
+    most nodes that the structural state leaves room for."""
+    src = tmp_path / "lds.cpp"
+    src.write_text(f'''
+#include "{ROOT}/paper_2607_03574_amd/csrc/walk.h"
+#include <cstdio>
+using namespace ndvm::walk;
+int main() {{
+    unsigned long long most = 0;
+    for (uint32_t d = 1; d <= kMaxDepth; ++d) for (uint32_t l = 0; l <= kMaxLocals; l += 4)
+        for (uint32_t f = 0; f <= kMaxFrames; f += 4) for (uint32_t o = 0; o <= kMaxLoops; o += 8)
+            for (uint32_t p = 0; p < 128; ++p) {{
+                if (lds_bytes(d, l, o, f, 0, p) > kMaxLdsBytes) break;
+                const uint32_t n = uint32_t(kMaxLdsBytes - lds_bytes(d, l, o, f, 0, p)) / 4 * 32;
+                if (lds_bytes(d, l, o, f, n, p) > kMaxLdsBytes) return 1;
+                const auto b = launch_lds_bytes(d, l, f, n, p);
+                most = b > most ? b : most;
+            }}
+    printf("%llu %llu", most, (unsigned long long)kMaxLaunchLdsBytes);
+}}''')
+    exe = str(tmp_path / "lds")
+    subprocess.run(["g++", "-std=c++17", "-O1", str(src), "-o", exe], check=True)
+    most, limit = map(int, subprocess.run([exe], check=True, capture_output=True, text=True).stdout.split())
+    assert 65536 + 512 * 12 < most <= limit
+    info = nd.walk_measure(at_the_lds_limit())
+    assert info["n_params"] == 63 and info["depth"] == 2 and 512 * 126 + 4 * (2 + 3 + -(-info["n_nodes"] // 32)) == 65536
+
+
 def test_walk_library_functions(tmp_path):
     """The walker calls its library functions past their first instruction, a
     wait, by a call that states what it changes: the functions keep to that
