@@ -373,3 +373,29 @@ def test_library_functions_keep_to_their_registers(code):
                 if kind == "s" and (lo == "30" or (one == "27" and f not in scalar)):
                     continue                      # the return address, the immediate
                 assert top < (26 if kind == "s" else most), (f, t)
+
+
+def test_build_refuses_functions_its_calls_do_not_fit():
+    """The build itself checks the functions that are entered past their first
+    instruction: a listing with another first instruction, a longer one, a
+    register the interpreter holds, scratch memory or no such function fails."""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("_b", os.path.join(ROOT, "paper_2607_03574_amd", "build.py"))
+    b = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(b)
+    assert len(b.CALLED["wide.hip"]) == 27 and set(b.CALLED["walk.hip"]) == {"ndvm_walk_sin", "ndvm_walk_cos", "ndvm_walk_pow"}
+    wait = "\ts_waitcnt vmcnt(0) expcnt(0) lgkmcnt(0)   // 000000001000: BF8C0000"
+    end = "\ts_setpc_b64 s[30:31]   // 000000001010: BE801D1E"
+
+    def listing(body):
+        return "\n".join(f"0000000000001000 <{f}>:\n{body if f == 'ndvm_walk_pow' else wait}\n{end}" for f in b.CALLED["walk.hip"])
+
+    b.check_called("walk.hip", listing(wait + "\n\tv_mul_f64 v[38:39], v[0:1], v[2:3]   // 000000001004: D2810000 00020500"))
+    for bad in ("\ts_waitcnt lgkmcnt(0)   // 000000001000: BF8CC07F", wait + " 00000000",
+                wait + "\n\tv_mul_f64 v[39:40], v[0:1], v[2:3]   // 000000001004: D2810000 00020500",
+                wait + "\n\ts_mov_b32 s32, 0   // 000000001004: BEA00080",
+                wait + "\n\tscratch_store_dword off, v0, s2   // 000000001004: DC704000 00020000"):
+        with pytest.raises(RuntimeError):
+            b.check_called("walk.hip", listing(bad))
+    with pytest.raises(RuntimeError):
+        b.check_called("walk.hip", listing(wait).replace("ndvm_walk_cos", "ndvm_walk_cot"))
