@@ -683,10 +683,15 @@ __global__ void __launch_bounds__(64) ndvm_walk(Args A) {
     }
 }
 
+// Clears the status word (a kernel: a memset node of a captured graph may not
+// take effect on its later replays).
+__global__ void ndvm_walk_clear(int *status) { *status = 0; }
+
 }  // namespace
 
 hipError_t launch_walk(const walk::Args &A, uint32_t grid, hipStream_t stream) {
-    if (grid == 0) return hipSuccess;
+    hipLaunchKernelGGL(ndvm_walk_clear, dim3(1), dim3(1), 0, stream, A.status);
+    if (grid == 0) return hipGetLastError();
     static std::once_flag once[64];
     static hipError_t raised[64];   // the LDS limit, per device
     int dev = 0;

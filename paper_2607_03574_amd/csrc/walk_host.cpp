@@ -549,10 +549,6 @@ ndvm_status ndvm_walk_grad(const ndvm_walk *w, const double *params, int64_t L, 
         A.n_items = uint64_t(w->n_prog) * uint64_t((L + 63) / 64);
         A.status = static_cast<int *>(workspace);
         const hipStream_t s = static_cast<hipStream_t>(stream);
-        if (hipMemsetAsync(workspace, 0, sizeof(int), s) != hipSuccess) {
-            set_error("ndvm_walk_grad: clearing the status word failed");
-            return NDVM_E_DEVICE;
-        }
         const hipError_t e = launch_walk(A, wave_slots(*w, A.n_items), s);
         if (e != hipSuccess) {
             set_error(std::string("walker launch failed: ") + hipGetErrorString(e));

@@ -169,3 +169,11 @@ def test_walk_library_functions(tmp_path):
     kernel = text[text.index("ndvm_walkENS_4walk4ArgsE:"):]
     assert kernel.count("s_swappc_b64") == len(re.findall(r"ndvm_walk_\w+@rel32@hi\+16\n\s*s_swappc_b64 s\[30:31\]", kernel))
     assert "s_endpgm" in kernel and not re.search(r"\bscratch_|\bflat_(load|store)", kernel)
+
+
+def test_no_memset_is_enqueued():
+    """No compute call enqueues a memset, which a capture would record as a node
+    that may not take effect on later replays."""
+    csrc = os.path.join(ROOT, "paper_2607_03574_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        assert not re.search(r"hipMemset\w*\(", open(os.path.join(csrc, f)).read()), f
