@@ -242,13 +242,13 @@ def test_many_programs_mixing_a_spilling_program(nd, oracle_mod):
 
 
 def test_register_hungry_program_runs_in_rounds_instead_of_spilling(nd, oracle_mod):
-    """A Kalman filter needs about 315 registers per lane.  At 32,768 lanes,
-    every wave resident would leave a budget of 160 and push the rest to HBM
-    rows; the launch instead keeps the program of 320 registers (the
-    workspace holds the same rows per lane as at 16,384 lanes, none for
-    spilled registers) and runs its waves in two rounds.  Results: bit for
-    bit those of a 16,384-lane launch on the same lanes, and the oracle on a
-    sample of lanes."""
+    """A Kalman filter does not fit what 32,768 lanes would have with every wave
+    resident: its matrices need some 260 elements of LDS a lane, half the LDS a
+    wave is 160 (on the slot kernel, which this was written for: about 315
+    registers against a budget of 160).  The launch keeps the program of 320 (the
+    workspace holds the same rows per lane as at 16,384 lanes, none for spilled
+    registers) and runs its waves in two rounds.  Results: bit for bit those of a
+    16,384-lane launch on the same lanes, and the oracle on a sample of lanes."""
     w = configs.build("kalman_cv4", L=32768, T=12)
     tape = nd.tape_upload(nd.tape_build(w.bytecode))
     assert nd.workspace_bytes(tape, 32768) == 2 * nd.workspace_bytes(tape, 16384)

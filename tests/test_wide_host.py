@@ -112,6 +112,25 @@ def test_scheduling_short_programs_costs_no_more_than_for_the_slot_kernel():
         assert wide < 1.4 * slot, (T, wide, slot)
 
 
+@pytest.mark.parametrize("mode", [1, 2])
+def test_half_the_lds_a_wave(oracle_mod, mode):
+    """Products of a step fit half the LDS a wave with shorter segments, at a cost
+    that two waves a SIMD repay; a Kalman filter does not, however short."""
+    obs, p = np.zeros(1), np.random.default_rng(2).uniform(0.2, 0.3, (2, 4))
+    for side, n in ((4, 0), (3, 0), (4, 4)):
+        code = scalars_and_a_product(60, side, n)
+        t = nd.tape_build(code)
+        full, half = (emu.wide(t, p, obs, mode, lds_rows=r) for r in (320, 160))
+        assert half[2]["lds_rows"] <= 160 and half[2]["cost"] * 7 < full[2]["cost"] * 10
+        if mode == 1:
+            assert full[2]["lds_rows"] > 160 and half[2]["n_segments"] > full[2]["n_segments"]
+        ol, og, _ = oracle_mod.run(code, p, obs)
+        compare(half[0], half[1], ol, og)
+    for T in (12, 50, 200):
+        w = configs.kalman(L=1, T=T)
+        assert emu.wide(nd.tape_build(w.bytecode), w.params[:0], w.obs, mode, lds_rows=160) is None
+
+
 def _slot_budget(lanes):
     """Registers a lane of the slot kernel at `lanes` lanes (16 lanes a wave, 256
     CUs of 160 KB LDS, at most 16 waves each)."""
