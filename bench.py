@@ -181,6 +181,15 @@ def build_flattened(name, torch, device):
 POLICIES = {"recompute": 2, "save": 1}   # NDVM_POLICY_RECOMPUTE, NDVM_POLICY_SAVE
 
 
+def replay_kernel(workload, branch_skip=False):
+    """The replay kernel that runs a workload's gradients: the wide kernel, its
+    variant for programs with matrices, or (programs with branches uploaded for
+    branch skipping) the slot kernel."""
+    if branch_skip and workload == "random_programs":
+        return "ndvm_replay"
+    return "ndvm_wide_matrix" if workload == "kalman_cv4" else "ndvm_wide"
+
+
 def build_inputs(name, torch, device, policy="recompute", branch_skip=False):
     """The workload's device inputs and one step.  Also times the host work
     per program that the lane-gradient rate leaves out: trace production
@@ -352,7 +361,7 @@ def calibration_bench(args):
                    "lanes_improved": improved},
         "roofline": {"bound": "alu", "achieved": flops / gpu_s / 1e12, "peak": PEAK_FP64 / 1e12,
                      "unit": "TFLOP/s", "frac": flops / gpu_s / PEAK_FP64, "traffic": None,
-                     "kernel": "ndvm_replay + ndvm_adam", "kernel_ms": gpu_s * 1e3},
+                     "kernel": replay_kernel(args.workload) + " + ndvm_adam", "kernel_ms": gpu_s * 1e3},
     }
     if not args.no_cpu_baseline:
         from oracle import adam
@@ -445,13 +454,14 @@ def main():
     if args.policy == "save" and args.workload != "random_programs":
         # the save policy needs a store and a load of every value the adjoint
         # rules read: the schedule's checkpoint rows (workspace rows less the
-        # trash rows; no spills at these budgets)
+        # trash rows; a program with matrices pads each value's to a multiple
+        # of four, 5% on the Kalman filter)
         L, P = meta["lanes"], meta["params"]
         rows = host["workspace_bytes"] // (8 * ((L + 63) // 64 * 64)) - 4
         B = float(L * (8 * (2 * P + 1) + 16 * rows))
         meta["saved_doubles_per_lane"] = int(rows)
     roof = roofline(B, flops, kern_s, None if args.branch_skip else profiled_traffic(args.workload, args.policy))
-    roof.update(kernel="ndvm_replay", kernel_ms=kern_s * 1e3, kernel_ms_median=res["kernel_median_s"] * 1e3,
+    roof.update(kernel=replay_kernel(args.workload, args.branch_skip), kernel_ms=kern_s * 1e3, kernel_ms_median=res["kernel_median_s"] * 1e3,
                 kernel_ms_iqr=res["kernel_iqr_s"] * 1e3)
     out = {
         "metric": "lane-gradient evals/sec (fwd+rev) on 1 MI355X",
