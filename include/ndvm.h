@@ -16,9 +16,10 @@
  * Here the structural walk happens once per program on the host
  * (ndvm_tape_build) and yields a lane-invariant tape in which numeric
  * branches are per-lane selects.  ndvm_tape_upload schedules the tape for the
- * GPU; ndvm_forward / ndvm_grad replay it on the device for L lanes (16
- * lanes per wave, each lane's independent operations spread over 4 threads),
- * and ndvm_grad_many does so for many programs in a single launch.
+ * GPU; ndvm_forward / ndvm_grad replay it on the device for L lanes (64 lanes
+ * per wave, one thread each, or 16 with four threads each, whichever kernel the
+ * program and the launch suit; the bits are the same), and ndvm_grad_many does
+ * so for many programs in a single launch.
  * ndvm_adam_step is the optimiser step of a calibration loop driven by
  * ndvm_grad.
  *
@@ -154,7 +155,10 @@ ndvm_status ndvm_tape_info_get(const ndvm_tape *tape, ndvm_tape_info *out);
  * registers that do not fit in LDS.  This is the preparation call of a lane
  * count: with with_grad = 1 it schedules the tape for that launch shape and
  * copies the device program to the GPU (synchronously; once per tape and
- * register budget, then cached), so that ndvm_grad itself only enqueues.
+ * register budget, then cached), so that ndvm_grad itself only enqueues; with
+ * with_grad = 0, for a tape of ndvm_tape_upload_many and few lanes, it may do so
+ * with a second forward program that suits such launches (ndvm_tape_upload
+ * makes it at once; without it ndvm_forward gives the same results).
  * Errors: NDVM_E_ARG (null handle/pointer, L < 0), NDVM_E_NOMEM,
  * NDVM_E_DEVICE, NDVM_E_UNSUPPORTED (program too large for the device format).
  */

@@ -481,6 +481,42 @@ int64_t wide_scratch_part(const ndvm_tape *t, const WideProg &w, const DevicePro
     return scratch_part(wide_rows(w), L, scratch_bytes(), *slot_fits);
 }
 
+// Whether a slot program runs a launch of `waves` of its waves sooner than the
+// wide program w (slot_wins).
+bool wins(const DeviceProps &p, const DevProg &dp, int64_t waves, const WideProg &w) {
+    const size_t lds = std::max(dp.meta.n_regs, 1u) * reg_bytes(slot::kMaxSlots);
+    if (lds > p.lds_per_block) return false;   // it spills
+    const uint64_t resident = p.lds_per_cu / lds;
+    return slot_wins(dp.meta.lone, resident, uint64_t(waves), uint64_t(p.cus), w.meta.lone);
+}
+bool few_waves(const DeviceProps &p, int64_t waves) { return waves <= int64_t(kLoneWaves) * p.cus; }
+
+// The slot forward program of a tape whose forward program is a wide one, null
+// where it is beyond the slot format or (not `build`) was not made.
+ndvm_status fwd_slot(ndvm_tape *tape, bool build, hipStream_t stream, DevProg **out) {
+    *out = nullptr;
+    if (build) {
+        const ndvm_status st = fwd_program(tape, slot::kMaxSlots, stream, out);
+        return st == NDVM_E_UNSUPPORTED ? NDVM_OK : st;
+    }
+    std::lock_guard<std::mutex> lk(tape->mu);
+    auto it = tape->fwd.find(slot::kMaxSlots);
+    if (it != tape->fwd.end()) *out = it->second.get();
+    return NDVM_OK;
+}
+
+// The slot program of a losses launch over L lanes that the wide program would
+// run too, where it is sooner done there, else null; made by the sizing call.
+ndvm_status fwd_slot_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, bool build, DevProg **out) {
+    *out = nullptr;
+    const int64_t waves = waves_of(L, 1, slot::kMaxSlots);
+    if (L == 0 || !few_waves(p, waves) || !slot_may_win(tape->wide_fwd->meta, false)) return NDVM_OK;
+    DevProg *dp = nullptr;
+    const ndvm_status st = fwd_slot(tape, build, nullptr, &dp);
+    if (dp && wins(p, *dp, waves, *tape->wide_fwd)) *out = dp;
+    return st;
+}
+
 // The wide program of a gradient launch over L lanes, or null.  As for the
 // slot kernel's programs, a compute call needs a sizing call before it whose
 // lane count gives the same register budget.
@@ -500,6 +536,36 @@ ndvm_status wide_grad_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, int6
         return NDVM_E_ARG;
     }
     *out = w;
+    return NDVM_OK;
+}
+
+// Whether the slot program of a gradient that the wide program w would run is
+// worth making (or, in a compute call, may have been made).
+ndvm_status grad_slot_likely(ndvm_tape *tape, const WideProg &w, bool build, bool *likely) {
+    *likely = false;
+    if (!tape->wide_fwd || !slot_may_win(w.meta, true)) return NDVM_OK;
+    DevProg *fp = nullptr;
+    const ndvm_status st = fwd_slot(tape, build, nullptr, &fp);
+    *likely = fp && slot_leads(fp->meta.lone, tape->wide_fwd->meta.lone);
+    return st;
+}
+
+// The slot program of a gradient launch over L lanes that the wide program w
+// would run too, where it is sooner done there, else null; made by the sizing
+// call.
+ndvm_status grad_slot_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, const WideProg &w, bool build,
+                          DevProg **out, uint32_t *b) {
+    *out = nullptr;
+    const uint32_t S = slot::kMaxSlots;
+    const int64_t waves = waves_of(L, 1, S);
+    bool likely = false;
+    ndvm_status st;
+    if (L == 0 || !few_waves(p, waves) || (st = grad_slot_likely(tape, w, build, &likely)) != NDVM_OK || !likely)
+        return L == 0 || !few_waves(p, waves) ? NDVM_OK : st;
+    DevProg *dp = nullptr;
+    st = single_grad_program(tape, p, L, S, build, &dp, b);
+    if (st != NDVM_OK) return !build || st == NDVM_E_UNSUPPORTED ? NDVM_OK : st;
+    if (dp->meta.n_regs <= *b && wins(p, *dp, waves, w)) *out = dp;
     return NDVM_OK;
 }
 
@@ -671,6 +737,39 @@ ndvm_status wide_many(const ndvm_tape *const *tapes, int n_prog, const DevicePro
     return NDVM_OK;
 }
 
+// Whether a population of few waves, all of whose programs the wide kernel
+// takes, is sooner done on the slot kernel: the launch lasts as long as its
+// longest wave.  The slot programs are made (by the sizing call) only where the
+// longest wide program's may well be shorter.
+ndvm_status slot_many_wins(const ndvm_tape *const *tapes, int n_prog, const DeviceProps &p, int64_t L, uint32_t S,
+                           uint32_t b, bool build, const std::vector<WideProg *> &progs, bool *win) {
+    *win = false;
+    const int64_t waves = waves_of(L, n_prog, S);
+    if (n_prog == 0 || L == 0 || !few_waves(p, waves)) return NDVM_OK;
+    const auto longer = [&](const WideProg *x, const WideProg *y) { return x->meta.lone < y->meta.lone; };
+    const size_t at = size_t(std::max_element(progs.begin(), progs.end(), longer) - progs.begin());
+    bool likely;
+    ndvm_status st = grad_slot_likely(const_cast<ndvm_tape *>(tapes[at]), *progs[at], build, &likely);
+    if (st != NDVM_OK || !likely) return st;
+    std::map<const ndvm_tape *, Schedule> pre;
+    if (build && (st = schedule_many(tapes, n_prog, S, b, &pre)) != NDVM_OK)
+        return st == NDVM_E_UNSUPPORTED ? NDVM_OK : st;
+    uint64_t lone = 0;
+    uint32_t regs = 0;
+    for (int q = 0; q < n_prog; ++q) {
+        DevProg *dp;
+        auto pi = pre.find(tapes[q]);
+        Schedule *ps = pi != pre.end() && pi->second.code.size() ? &pi->second : nullptr;
+        st = grad_program(const_cast<ndvm_tape *>(tapes[q]), S, b, build, &dp, ps);
+        if (st != NDVM_OK) return build ? st : NDVM_OK;
+        lone = std::max(lone, dp->meta.lone);
+        regs = std::max(regs, dp->meta.n_regs);
+    }
+    *win = regs <= b && slot_wins(lone, p.lds_per_cu / (std::max(regs, 1u) * reg_bytes(S)), uint64_t(waves),
+                                  uint64_t(p.cus), progs[at]->meta.lone);
+    return NDVM_OK;
+}
+
 ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bool build, ManyLaunch *out) {
     DeviceProps p;
     ndvm_status st = device_props(&p);
@@ -681,6 +780,9 @@ ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bo
     std::vector<uint64_t> key, cost(static_cast<size_t>(n_prog));
     std::vector<WideProg *> wide;
     if ((st = wide_many(tapes, n_prog, p, L, build, &wide, &out->wide)) != NDVM_OK) return st;
+    bool slot = false;
+    if (out->wide && (st = slot_many_wins(tapes, n_prog, p, L, S, b, build, wide, &slot)) != NDVM_OK) return st;
+    out->wide = out->wide && !slot;
     uint64_t row = 0;
     if (out->wide) {
         std::vector<wide::Prog> t(static_cast<size_t>(n_prog));
@@ -894,10 +996,14 @@ ndvm_status ndvm_tape_upload(const uint8_t *bytes, size_t len, int policy, void 
         h->id = g_next_id++;
         // schedule the forward program now: scheduling limits surface at upload
         WideSchedule ws = wide_schedule_of(h.get(), false, kWideLdsRows);
+        DevProg *fp = nullptr;
         if (ws.ok) {
             st = upload_wide(std::move(ws), h->tape, false, static_cast<hipStream_t>(stream), &h->wide_fwd);
+            // the slot program for launches of few waves (of a population's
+            // tapes it is made when one is sized for losses)
+            if (st == NDVM_OK && slot_may_win(h->wide_fwd->meta, false))
+                st = fwd_slot(h.get(), true, static_cast<hipStream_t>(stream), &fp);
         } else {
-            DevProg *fp = nullptr;
             st = fwd_program(h.get(), 4, static_cast<hipStream_t>(stream), &fp);
         }
         if (st != NDVM_OK) return st;
@@ -1023,7 +1129,9 @@ ndvm_status ndvm_workspace_bytes(const ndvm_tape *tape, int64_t L, int with_grad
             st = wide_grad_for(const_cast<ndvm_tape *>(tape), p, L, 1, true, &w);
             if (st != NDVM_OK) return st;
             if (w) {
-                *bytes = size_t(wide_rows(*w) * uint64_t(Lp) * sizeof(double));
+                DevProg *sp = nullptr;
+                if ((st = grad_slot_for(const_cast<ndvm_tape *>(tape), p, L, *w, true, &sp, &b)) != NDVM_OK) return st;
+                *bytes = size_t((sp ? ws_rows(*sp, b) : wide_rows(*w)) * uint64_t(Lp) * sizeof(double));
                 // the slot program too, for ndvm_grad_noalloc, where the wide
                 // kernel has too many rows for the scratch array and the slot
                 // kernel may not; that it cannot be made is no error here
@@ -1038,7 +1146,9 @@ ndvm_status ndvm_workspace_bytes(const ndvm_tape *tape, int64_t L, int with_grad
         } else {
             uint32_t bf = uint32_t(p.lds_per_block / reg_bytes(S));
             if (tape->wide_fwd) {
-                *bytes = size_t(wide_rows(*tape->wide_fwd) * uint64_t(Lp) * sizeof(double));
+                if ((st = fwd_slot_for(const_cast<ndvm_tape *>(tape), p, L, true, &dp)) != NDVM_OK) return st;
+                rows = std::max(wide_rows(*tape->wide_fwd), dp ? ws_rows(*dp, bf) : 0);
+                *bytes = size_t(rows * uint64_t(Lp) * sizeof(double));
                 return NDVM_OK;
             }
             st = fwd_program(const_cast<ndvm_tape *>(tape), S, nullptr, &dp);
@@ -1099,24 +1209,27 @@ ndvm_status ndvm_forward(const ndvm_tape *tape, const double *params, int64_t L,
         DeviceProps p;
         if ((st = device_props(&p)) != NDVM_OK) return st;
         const uint32_t S = choose_slots(p, L, 1);
+        const int64_t Lp = lpad_of(L);
+        const uint32_t bf = uint32_t(p.lds_per_block / reg_bytes(S));
+        auto bytes = [&](uint64_t rows) { return size_t(rows * uint64_t(Lp) * sizeof(double)); };
+        DevProg *fp = nullptr;
         if (tape->wide_fwd) {
-            const int64_t Lp = lpad_of(L);
-            const size_t need = size_t(wide_rows(*tape->wide_fwd) * uint64_t(Lp) * sizeof(double));
-            if (!ws || ws_bytes < need) {
-                set_error("ndvm_forward: workspace too small");
-                return NDVM_E_NOMEM;
+            if ((st = fwd_slot_for(const_cast<ndvm_tape *>(tape), p, L, false, &fp)) != NDVM_OK) return st;
+            if (!fp || !ws || ws_bytes < bytes(ws_rows(*fp, bf))) {
+                if (!ws || ws_bytes < bytes(wide_rows(*tape->wide_fwd))) {
+                    set_error("ndvm_forward: workspace too small");
+                    return NDVM_E_NOMEM;
+                }
+                const LaunchArgs A{obs, params, loss, loss, static_cast<double *>(ws), ld_p, 0, L, Lp, 0, 0};
+                return check_wide_launch(A, nullptr, tape->wide_fwd->prog, 1, tape->wide_fwd->prog.lds_bytes,
+                                         static_cast<hipStream_t>(stream));
             }
-            const LaunchArgs A{obs, params, loss, loss, static_cast<double *>(ws), ld_p, 0, L, Lp, 0, 0};
-            return check_wide_launch(A, nullptr, tape->wide_fwd->prog, 1, tape->wide_fwd->prog.lds_bytes,
-                                     static_cast<hipStream_t>(stream));
-        }
-        DevProg *fp;
-        if ((st = fwd_program(const_cast<ndvm_tape *>(tape), S, static_cast<hipStream_t>(stream), &fp)) != NDVM_OK)
+        } else if ((st = fwd_program(const_cast<ndvm_tape *>(tape), S, static_cast<hipStream_t>(stream), &fp)) != NDVM_OK) {
             return st;
+        }
         const DevProg &dp = *fp;
-        uint32_t r_lds = std::min<uint32_t>(dp.meta.n_regs, uint32_t(p.lds_per_block / reg_bytes(S)));
-        int64_t Lp = lpad_of(L);
-        size_t need = size_t(ws_rows(dp, r_lds) * uint64_t(Lp) * sizeof(double));
+        const uint32_t r_lds = std::min(dp.meta.n_regs, bf);
+        const size_t need = bytes(ws_rows(dp, r_lds));
         if (need && (!ws || ws_bytes < need)) {
             set_error("ndvm_forward: workspace too small");
             return NDVM_E_NOMEM;
@@ -1185,6 +1298,10 @@ static ndvm_status grad_impl(const ndvm_tape *tape, const double *params, int64_
     const uint32_t S = choose_slots(p, L, 1);
     WideProg *wp = nullptr;
     if ((st = wide_grad_for(const_cast<ndvm_tape *>(tape), p, L, 1, false, &wp)) != NDVM_OK) return st;
+    DevProg *dp = nullptr;
+    uint32_t b = 0;
+    if (wp && (st = grad_slot_for(const_cast<ndvm_tape *>(tape), p, L, *wp, false, &dp, &b)) != NDVM_OK) return st;
+    if (dp && (!static_ws || ws_rows(*dp, b) * uint64_t(Lp) * sizeof(double) <= scratch_bytes())) wp = nullptr;
     int64_t part = L;   // lanes at a time
     bool slot_fits = true;
     if (wp && static_ws && (part = wide_scratch_part(tape, *wp, p, L, &slot_fits)) > 0 &&
@@ -1193,8 +1310,6 @@ static ndvm_status grad_impl(const ndvm_tape *tape, const double *params, int64_
         return st;
     if (wp && part > 0)
         return wide_grad_launch(*wp, params, L, ld_p, obs, loss, grad, ld_g, ws, ws_bytes, part, stream, who);
-    uint32_t b = 0;
-    DevProg *dp = nullptr;
     st = slot_fits ? single_grad_program(const_cast<ndvm_tape *>(tape), p, L, S, false, &dp, &b) : NDVM_E_NOMEM;
     if (st != NDVM_OK)   // (a launch that the array cannot serve, or a tape that was not sized)
         return wp ? static_workspace(size_t(wide_rows(*wp) * uint64_t(Lp) * sizeof(double)), who, &ws, &ws_bytes) : st;
@@ -1241,9 +1356,12 @@ static ndvm_status points_layout(const ndvm_tape *tape, int64_t L, int64_t N, bo
     const int64_t F = L * N;
     const uint32_t S = choose_slots(p, F, 1);
     if ((st = wide_grad_for(const_cast<ndvm_tape *>(tape), p, F, 1, build, wp)) != NDVM_OK) return st;
-    if (!*wp &&
-        (st = single_grad_program(const_cast<ndvm_tape *>(tape), p, F, S, build, dp, b)) != NDVM_OK)
+    if (*wp) {
+        if ((st = grad_slot_for(const_cast<ndvm_tape *>(tape), p, F, **wp, build, dp, b)) != NDVM_OK) return st;
+        if (*dp) *wp = nullptr;
+    } else if ((st = single_grad_program(const_cast<ndvm_tape *>(tape), p, F, S, build, dp, b)) != NDVM_OK) {
         return st;
+    }
     *replay_bytes = (*wp ? wide_rows(**wp) : ws_rows(**dp, *b)) * uint64_t(lpad_of(F)) * sizeof(double);
     *total = *replay_bytes + uint64_t(F) * (1 + tape->tape.n_params) * sizeof(double);
     return NDVM_OK;

@@ -308,6 +308,29 @@ int64_t ndvm_emu_program(const uint8_t *tape, size_t len, int with_grad, uint32_
 }
 
 /*
+ * Which kernel runs a launch of `lanes` lanes of `tape` (mode 0 losses, 1
+ * gradients, 2 saving gradients) on a GPU of `cus` CUs of 160 KB LDS, `budget`
+ * slot registers a lane: out[0] 1 slot, 0 wide; out[1], out[2] estimated cycles of
+ * a lone wave of either; out[3] the wide program's cycles in library functions.
+ * Result as ndvm_emu_wide.
+ */
+int ndvm_emu_route(const uint8_t *tape, size_t len, int mode, int64_t lanes, uint32_t budget, uint32_t cus, uint64_t *out) {
+    Tape t;
+    ndvm_status st = parse_tape(tape, len, &t);
+    if (st != NDVM_OK) return -int(st);
+    const WideSchedule S = schedule_wide(t, mode != 0, mode == 2, 320);
+    if (!S.ok) return 1;
+    const Schedule D = mode ? schedule_grad(t, budget, 4, mode == 2) : schedule_forward(t, 4, budget);
+    const bool leads = !mode || slot_leads(schedule_forward(t, 4, 1280).lone, schedule_wide(t, false, mode == 2, 320).lone);
+    out[0] = slot_may_win(S, mode != 0) && leads && D.n_regs <= budget &&
+             slot_wins(D.lone, 1280 / std::max(D.n_regs, 1u), uint64_t(lanes + 15) / 16, cus, S.lone);
+    out[1] = D.lone;
+    out[2] = S.lone;
+    out[3] = S.calls;
+    return 0;
+}
+
+/*
  * How the wide kernel would serve ndvm_grad_noalloc of `tape` over `lanes` lanes
  * on an array of `bytes`: out[0] lanes at a time (0: not at all), out[1] whether
  * the slot kernel with `budget` registers may fit the array, out[2] workspace

@@ -652,6 +652,31 @@ struct UEmit {
 
 constexpr uint32_t kTemps = 24;
 
+// Cycles of an instruction of a wave alone on its SIMD: least squares over the
+// times of 132 programs (sums and chains of one to five operations, random
+// trees, the benchmark models), losses, gradients and saving gradients, 64
+// lanes; their times follow within 7%.  (Forms of matrices are not among them.)
+uint32_t lone_cycles(uint32_t form) {
+    using namespace slot;
+    switch (form) {
+    case MAC: return 150;
+    case ACC: return 212;
+    case LDPARAM: return 227;
+    case CKLD: return 319;
+    case CMPLT: case SELP: case MACG: case GATEGT: case MSUB: case RSUB: case ABSF: return 365;
+    case DIV: case LDOBS: return 395;
+    case ACCSEL: case SQRTCF: return 440;
+    case ACCD: case ACCND: case ACCABS: case EXPF: return 490;
+    case LOGCF: return 714;
+    case LOGF: return 886;
+    case UN: return 1106;
+    case POWF: return 1742;
+    case CKST: return 1941;
+    case STLOSS: case STGRAD: case END: case LDCONST: case ZERO: return 0;
+    default: return 400;
+    }
+}
+
 // Build the forward phase (shared by both programs) and, for the gradient
 // program, the reverse phase; returns the slot program with registers
 // assigned and micro-ops packed S to an instruction.
@@ -1597,6 +1622,7 @@ Schedule build(const Info &I, Builder &B, bool with_grad, uint32_t S, uint32_t r
         }
         Sch.code[hdr_off + i] = hdr;
         Sch.n_slots_used += cnt;
+        Sch.lone += lone_cycles(f);
         Sch.n_mac += f == MAC;
         Sch.n_acc += f == ACC;
         Sch.n_msub += f == MSUB;

@@ -23,6 +23,7 @@ struct Schedule {
     uint64_t ckpt_elems_stored = 0, ckpt_elems_loaded = 0;
     uint32_t n_skips = 0;         // skippable branch arms (SKIP instructions)
     uint64_t n_mac = 0, n_acc = 0, n_msub = 0, n_block = 0;   // instructions of the most frequent forms
+    uint64_t lone = 0;            // estimated cycles of a wave alone on its SIMD (programs without matrices)
 };
 
 // Smallest branch arm (in value elements) laid out behind a skip test: a

@@ -165,7 +165,8 @@ struct WideSchedule {
     uint32_t n_regs = 0, n_ckpt_rows = 0, n_segments = 1, n_blocks = 0;
     uint32_t first[3] = {0, 0, 0};
     uint64_t n_uops = 0;
-    uint64_t cost = 0;            // estimated cycles of a lone wave
+    uint64_t cost = 0;            // estimated cycles of a lone wave, by which programs are chosen
+    uint64_t lone = 0, calls = 0; // measured ones, and those of library functions (programs without matrices)
     bool matrices = false;
     uint32_t lds_rows = 0;        // matrix elements in LDS
     uint64_t read_elems = 0;      // elements of the values that adjoint rules read (leaves apart)
@@ -199,6 +200,38 @@ constexpr int64_t scratch_part(uint64_t rows, int64_t lanes, uint64_t bytes, boo
     if (need <= bytes) return lanes;
     return need <= (slot_fits ? kManyArrays : kFewArrays) * bytes ? int64_t(fit) : 0;
 }
+
+// A launch of few waves lasts as long as one wave.  A wave of the slot kernel
+// (16 lanes) computes up to four independent library functions at a time, one of
+// the wide kernel (64 lanes) one: of programs that spend their time there, losses
+// above all, the slot kernel's is done earlier.  Sums of 64 terms on 4,096 lanes,
+// us, slot against wide kernel: losses of powers of powers 40 against 82, of
+// powers 27 against 48, of exponential, log and root 27 against 46, of sines of
+// cosines 31 against 42, of products 21 against 14; gradients 160 against 156, 95
+// against 93, 82 against 82, 94 against 95, 57 against 39 (of sines of sines of
+// sines 110 against 125; of a random tree whose parameters do not reach its
+// functions 228 against 285).  Whether the slot kernel wins, from the cycles
+// of a lone wave of both: as many of its waves per CU as its registers leave
+// room for run at a time, one per SIMD (each one more costs 4% and 0.4 us).
+// Over 96 programs other than those the cycles were measured on, 64 to 16,384
+// lanes, the kernel chosen takes at most 1.06 times as long as the other, losses,
+// and 1.08, gradients, 1.001 on the mean (the wide kernel alone up to 2.4 and 1.13).
+constexpr uint32_t kLoneWaves = 4;   // per CU: beyond that the wide kernel's lanes a wave count for more
+constexpr bool slot_wins(uint64_t slot_cycles, uint64_t resident, uint64_t waves, uint64_t cus, uint64_t wide_cycles) {
+    const uint64_t per_cu = (waves + cus - 1) / cus, at_once = std::min<uint64_t>(kLoneWaves, std::max<uint64_t>(resident, 1));
+    const uint64_t rounds = (per_cu + at_once - 1) / at_once, more = std::min(at_once, per_cu) - 1;
+    return per_cu > 0 && per_cu <= kLoneWaves && rounds * (slot_cycles * (100 + 4 * more) / 100) + 1000 * more < wide_cycles;
+}
+// Whether that may be so, so that the slot program is worth making: `share`, in
+// percent, of the wide program's cycles in library functions.  No program with
+// less (losses 40, gradients 60) ran more than 3% faster on the slot kernel.
+constexpr bool slot_may_win(const WideSchedule &S, bool with_grad) {
+    return !S.matrices && S.calls * 100 >= S.lone * (with_grad ? 60 : 40);
+}
+// A gradient's slot program, whose schedule is dear, is worth making only where
+// the forward program's wave is done in 85% of the wide one's cycles (no gradient
+// was faster on the slot kernel with less of a lead there).
+constexpr bool slot_leads(uint64_t slot_forward, uint64_t wide_forward) { return slot_forward * 100 <= wide_forward * 85; }
 
 // Wide program of a tape: forward only, or forward and reverse (save_reads as
 // schedule_grad).  lds_rows: matrix elements a wave may hold in LDS.

@@ -103,6 +103,42 @@ uint32_t class_cost(uint32_t cls) {
 }
 constexpr uint32_t kDispatchCost = 62;
 
+// Measured cycles of a lone wave per micro-op and per block: least squares over
+// the launches named at the slot kernel's lone_cycles, times within 13%
+// (gradients 10%); class_cost stays what the choice between programs was tuned on.
+uint32_t lone_cycles(uint32_t cls) {
+    switch (cls) {
+    case FMA: return 27;
+    case DUAL: return 70;
+    case SEL: return 84;
+    case SELADJ: return 122;
+    case DIV: return 86;
+    case DIVADJ: return 189;
+    case ACCD: return 151;
+    case CKST: return 10;
+    case LDK0: case LDK1: return 70;
+    case LDO0: case LDO1: case STGRAD: return 5;
+    case WAIT: case WAITPF: return 172;
+    case PF: return 40;
+    case EXP: return 331;
+    case SIN: return 530;
+    case COS: return 482;
+    case LOGC: return 554;
+    case SQRTC: return 239;
+    case POW: return 1289;
+    case ACCSIN: return 621;
+    case ACCCOS: return 681;
+    case ACCLOG: return 269;
+    case ACCABS: return 199;
+    case ACCPOW: return 679;
+    case ACCSQRT: return 307;
+    case ABS: return 101;
+    default: return 0;
+    }
+}
+bool is_call(uint32_t cls) { return cls >= EXP && cls <= ACCSQRT; }
+constexpr uint32_t kLoneDispatch = 43;
+
 struct Lower {
     const Info &I;
     Builder &B;
@@ -1188,7 +1224,10 @@ void emit(const std::vector<WOp> &in, WideSchedule *S) {
         for (uint32_t i = 0; i < blocks[b].second; ++i) encode(ops[blocks[b].first + i], &S->code);
         S->code.push_back(entry_of(b + 1));
         S->code.push_back(start_of(b + 2));
-        S->cost += kDispatchCost + uint64_t(blocks[b].second) * class_cost(ops[blocks[b].first].cls);
+        const uint32_t cls = ops[blocks[b].first].cls, n = blocks[b].second;
+        S->cost += kDispatchCost + uint64_t(n) * class_cost(cls);
+        S->lone += kLoneDispatch + uint64_t(n) * lone_cycles(cls);
+        if (is_call(cls)) S->calls += uint64_t(n) * lone_cycles(cls);
     }
     // what the fetches read past the program's end
     S->code.resize(std::max<size_t>(S->code.size(), fetched < UINT64_MAX / 2 ? fetched / 4 : 0), 0);

@@ -116,3 +116,20 @@ def scratch(tape: bytes, lanes, mode=1, lds_rows=320, budget=1280, nbytes=64 << 
     if rc != 0:
         raise RuntimeError(f"emulator rc={rc}")
     return out[0], bool(out[1]), out[2]
+
+
+def route(tape: bytes, lanes, mode=1, budget=1280, cus=256):
+    """Which kernel runs a launch: (whether the slot kernel, its lone wave's
+    cycles, the wide kernel's, the latter's in library functions), or None for a
+    tape the wide kernel does not take."""
+    f = lib().ndvm_emu_route
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_char_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_int64, ctypes.c_uint32, ctypes.c_uint32,
+                  ctypes.c_void_p]
+    out = (ctypes.c_uint64 * 4)()
+    rc = f(tape, len(tape), mode, lanes, budget, cus, out)
+    if rc == 1:
+        return None
+    if rc != 0:
+        raise RuntimeError(f"emulator rc={rc}")
+    return bool(out[0]), out[1], out[2], out[3]

@@ -13,7 +13,7 @@ import pytest
 import emu
 from conftest import ROOT
 from parity import compare
-from wide_cases import cases, long_recurrence, lookups, one_element_forms, scalars_and_a_product
+from wide_cases import cases, long_recurrence, lookups, one_element_forms, scalars_and_a_product, sum_of_terms
 from workloads import configs
 from workloads.bytecode import Asm
 
@@ -129,6 +129,30 @@ def test_half_the_lds_a_wave(oracle_mod, mode):
     for T in (12, 50, 200):
         w = configs.kalman(L=1, T=T)
         assert emu.wide(nd.tape_build(w.bytecode), w.params[:0], w.obs, mode, lds_rows=160) is None
+
+
+@pytest.mark.parametrize("ops,mode,slot,wide", [
+    # lanes that the slot kernel runs, lanes that the wide kernel runs, with the
+    # measured us of both (slot, wide): losses 40, 82 and 82, 85; 27, 46 and 54, 46
+    ("pow pow", 0, [1, 64, 4096, 8192], [17000, 65536]), ("exp log sqrt", 0, [64, 4096], [16384, 65536]),
+    # losses without a library function: 21, 14
+    ("mul mul mul mul", 0, [], [64, 4096, 65536]), ("div", 0, [], [64, 4096]),
+    # gradients 110, 125; 160, 156; 44, 39; saving 195, 132
+    ("sin sin sin", 1, [64, 4096, 8192], [17000]), ("pow pow", 1, [], [64, 4096, 16384]),
+    ("exp", 1, [], [64, 4096]), ("sin sin sin", 2, [], [64, 4096])])
+def test_launches_of_few_waves(ops, mode, slot, wide):
+    """Which kernel runs programs of independent library functions."""
+    t = nd.tape_build(sum_of_terms(ops, 64))
+    for lanes, want in [(n, True) for n in slot] + [(n, False) for n in wide]:
+        assert emu.route(t, lanes, mode, _slot_budget(lanes) if mode else 1280)[0] == want, lanes
+
+
+def test_timed_models_stay_on_the_wide_kernel():
+    for w in (configs.lotka_volterra(L=1, T=60), configs.logistic(L=1, T=60)):
+        t = nd.tape_build(w.bytecode)
+        assert not any(emu.route(t, lanes, mode)[0] for lanes in (1, 4096) for mode in (0, 1, 2))
+    t = nd.tape_build(configs.exp_decay(L=1).bytecode)
+    assert not emu.route(t, 256, 1)[0] and emu.route(t, 256, 0)[0]      # losses of 64 exponentials: 16, 18 us
 
 
 def _slot_budget(lanes):

@@ -79,6 +79,22 @@ def scalars_and_a_product(steps, side, n):
     return A.endloop().loadl(5).index(0, 0).loadl(2).add().halt().bytes()
 
 
+def sum_of_terms(ops, n):
+    """Sum over n points of (op(... op(p0 x + p1)) - y)^2: independent chains of
+    library functions ("pow" to the power p2, "div" by p3, "mul" by p3)."""
+    A = Asm(4, 2 * n).push(0.0).storel(0).loop(n)
+    A.param(0).obs(0, 1).mul().param(1).add()
+    for op in ops.split():
+        if op in ("pow", "div", "mul"):
+            A.param(2 if op == "pow" else 3)
+        getattr(A, op)()
+    return A.obs(n, 1).sub().dup().mul().loadl(0).add().storel(0).endloop().loadl(0).halt().bytes()
+
+
+def points_of_terms(n):
+    return np.concatenate([np.linspace(0.1, 1.0, n), np.linspace(0.2, 0.9, n)])
+
+
 def lookup(params, n):
     """(p0 * table - y)^2, the table nested branches of n constant leaves over
     thresholds of the other parameters: parameters and constants (which the
