@@ -517,6 +517,9 @@ ndvm_status fwd_slot_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, bool 
     return st;
 }
 
+constexpr const char *kNotSized = "the tape was not sized for this lane count: size the workspace with "
+    "ndvm_workspace_bytes (ndvm_workspace_bytes_many) for the same lane count first";
+
 // The wide program of a gradient launch over L lanes, or null.  As for the
 // slot kernel's programs, a compute call needs a sizing call before it whose
 // lane count gives the same register budget.
@@ -531,8 +534,7 @@ ndvm_status wide_grad_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, int6
     std::lock_guard<std::mutex> lk(tape->mu);
     if (build) tape->sized.insert(b);
     if (!tape->sized.count(b)) {
-        set_error("the tape was not sized for this lane count: size the workspace with "
-                  "ndvm_workspace_bytes (ndvm_workspace_bytes_many) for the same lane count first");
+        set_error(kNotSized);
         return NDVM_E_ARG;
     }
     *out = w;
@@ -690,48 +692,56 @@ ndvm_status wide_many(const ndvm_tape *const *tapes, int n_prog, const DevicePro
                       std::vector<WideProg *> *progs, bool *all) {
     *all = false;
     if (lpad_of(L) > kWideMaxLanes) return NDVM_OK;
-    // programs with matrices and without run on kernels of their own: a launch
-    // that mixes them, or with a program the wide kernel does not take, stays
-    // on the slot kernel
-    for (int q = 0; q < n_prog; ++q) {
-        if (!tapes[q]->wide_fwd || tapes[q]->matrices != tapes[0]->matrices) return NDVM_OK;
-    }
-    const uint32_t rows = wide_lds_rows(reg_budget(p, waves_of(L, n_prog, slot::kMaxSlots), slot::kMaxSlots));
-    const uint32_t key = n_prog && tapes[0]->matrices ? rows : 0;
+    const uint32_t b = reg_budget(p, waves_of(L, n_prog, slot::kMaxSlots), slot::kMaxSlots);
+    const uint32_t key = n_prog && tapes[0]->matrices ? wide_lds_rows(b) : 0;
+    progs->resize(size_t(n_prog));
     std::vector<ndvm_tape *> todo;
-    if (build) {
-        std::set<const ndvm_tape *> seen;
-        for (int q = 0; q < n_prog; ++q) {
-            ndvm_tape *t = const_cast<ndvm_tape *>(tapes[q]);
-            std::lock_guard<std::mutex> lk(t->mu);
-            if (!t->wide_grad.count(key) && seen.insert(t).second) todo.push_back(t);
-        }
-    }
-    std::vector<WideSchedule> res(todo.size());
-    std::vector<ndvm_status> code(todo.size(), NDVM_OK);
-    std::vector<std::string> msg(todo.size());
-    for_all(todo.size(), [&](size_t i) { res[i] = wide_schedule_of(todo[i], true, key); }, &code, &msg);
-    for (size_t i = 0; i < todo.size(); ++i) {
-        if (code[i] != NDVM_OK) {
-            set_error(msg[i]);
-            return code[i];
-        }
-        WideProg *w;
-        ndvm_status st = wide_grad_program(todo[i], key, true, &w, &res[i]);
-        if (st != NDVM_OK) return st;
-    }
+    bool unsized = false;
+    // One look at every program (a call of many programs and little work lasts as
+    // long as these looks: 1,000 programs, 227 us a call with four of them).
+    // Programs with matrices and without run on kernels of their own: a launch
+    // that mixes them, or with a program the wide kernel does not take, stays
+    // on the slot kernel.
     for (int q = 0; q < n_prog; ++q) {
         ndvm_tape *t = const_cast<ndvm_tape *>(tapes[q]);
-        WideProg *w = nullptr;
-        ndvm_status st = wide_grad_program(t, key, false, &w);
-        if (st != NDVM_OK) return st;
-        if (!w) return NDVM_OK;
+        if (!t->wide_fwd || t->matrices != tapes[0]->matrices) return NDVM_OK;
+        std::lock_guard<std::mutex> lk(t->mu);
+        auto it = t->wide_grad.find(key);
+        if (it == t->wide_grad.end()) {
+            if (!build) return NDVM_OK;
+            todo.push_back(t);
+        } else if (!it->second) {
+            return NDVM_OK;
+        } else {
+            (*progs)[size_t(q)] = it->second.get();
+            unsized = unsized || !t->sized.count(b);
+        }
     }
-    for (int q = 0; q < n_prog; ++q) {
-        WideProg *w = nullptr;
-        ndvm_status st = wide_grad_for(const_cast<ndvm_tape *>(tapes[q]), p, L, n_prog, build, &w);
-        if (st != NDVM_OK) return st;
-        progs->push_back(w);
+    if (!todo.empty()) {
+        std::sort(todo.begin(), todo.end());
+        todo.erase(std::unique(todo.begin(), todo.end()), todo.end());
+        std::vector<WideSchedule> res(todo.size());
+        std::vector<ndvm_status> code(todo.size(), NDVM_OK);
+        std::vector<std::string> msg(todo.size());
+        for_all(todo.size(), [&](size_t i) { res[i] = wide_schedule_of(todo[i], true, key); }, &code, &msg);
+        for (size_t i = 0; i < todo.size(); ++i) {
+            if (code[i] != NDVM_OK) {
+                set_error(msg[i]);
+                return code[i];
+            }
+            WideProg *w;
+            ndvm_status st = wide_grad_program(todo[i], key, true, &w, &res[i]);
+            if (st != NDVM_OK) return st;
+        }
+        return wide_many(tapes, n_prog, p, L, build, progs, all);
+    }
+    if (unsized && !build) {
+        set_error(kNotSized);
+        return NDVM_E_ARG;
+    }
+    for (int q = 0; unsized && q < n_prog; ++q) {
+        std::lock_guard<std::mutex> lk(const_cast<ndvm_tape *>(tapes[q])->mu);
+        const_cast<ndvm_tape *>(tapes[q])->sized.insert(b);
     }
     *all = true;
     return NDVM_OK;
@@ -776,8 +786,9 @@ ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bo
     if (st != NDVM_OK) return st;
     const uint32_t S = choose_slots(p, L, n_prog);
     const uint32_t b = reg_budget(p, waves_of(L, n_prog, S), S);
-    std::vector<uint8_t> table;   // the device table's bytes
+    std::vector<uint8_t> table;   // the device table's bytes (of a wide launch made where it is missing)
     std::vector<uint64_t> key, cost(static_cast<size_t>(n_prog));
+    key.reserve(2 * size_t(n_prog) + 1);
     std::vector<WideProg *> wide;
     if ((st = wide_many(tapes, n_prog, p, L, build, &wide, &out->wide)) != NDVM_OK) return st;
     bool slot = false;
@@ -785,19 +796,13 @@ ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bo
     out->wide = out->wide && !slot;
     uint64_t row = 0;
     if (out->wide) {
-        std::vector<wide::Prog> t(static_cast<size_t>(n_prog));
         for (int q = 0; q < n_prog; ++q) {
-            t[q] = wide[q]->prog;
-            t[q].ckpt_row0 = row;
-            t[q].trash_row = row + wide[q]->meta.n_ckpt_rows;
             row += wide_rows(*wide[q]);
             cost[q] = wide[q]->meta.cost;
             out->lds_bytes = std::max(out->lds_bytes, wide[q]->prog.lds_bytes);
             key.push_back(tapes[q]->id);
             key.push_back((uint64_t(S) << 32) | b | uint64_t(1) << 63);
         }
-        table.resize(t.size() * sizeof(wide::Prog));
-        if (n_prog) std::memcpy(table.data(), t.data(), table.size());
     } else {
         std::vector<ProgStatic> t(static_cast<size_t>(n_prog), ProgStatic{});
         uint32_t r_launch = 0;
@@ -875,6 +880,18 @@ ndvm_status many_launch(const ndvm_tape *const *tapes, int n_prog, int64_t L, bo
         set_error("no program table for this program set and lane count: size the workspace with "
                   "ndvm_workspace_bytes_many for the same programs and lane count first");
         return NDVM_E_ARG;
+    }
+    if (out->wide) {
+        std::vector<wide::Prog> t(static_cast<size_t>(n_prog));
+        row = 0;
+        for (int q = 0; q < n_prog; ++q) {
+            t[q] = wide[q]->prog;
+            t[q].ckpt_row0 = row;
+            t[q].trash_row = row + wide[q]->meta.n_ckpt_rows;
+            row += wide_rows(*wide[q]);
+        }
+        table.resize(t.size() * sizeof(wide::Prog));
+        std::memcpy(table.data(), t.data(), table.size());
     }
     void *d_table = nullptr;
     if (hipMalloc(&d_table, table.size()) != hipSuccess) {
