@@ -483,11 +483,11 @@ int64_t wide_scratch_part(const ndvm_tape *t, const WideProg &w, const DevicePro
 
 // Whether a slot program runs a launch of `waves` of its waves sooner than the
 // wide program w (slot_wins).
-bool wins(const DeviceProps &p, const DevProg &dp, int64_t waves, const WideProg &w) {
+bool wins(const DeviceProps &p, const DevProg &dp, int64_t waves, const WideProg &w, bool losses) {
     const size_t lds = std::max(dp.meta.n_regs, 1u) * reg_bytes(slot::kMaxSlots);
     if (lds > p.lds_per_block) return false;   // it spills
     const uint64_t resident = p.lds_per_cu / lds;
-    return slot_wins(dp.meta.lone, resident, uint64_t(waves), uint64_t(p.cus), w.meta.lone);
+    return slot_wins(dp.meta.lone, resident, uint64_t(waves), uint64_t(p.cus), w.meta.lone, w.meta.matrices, losses);
 }
 bool few_waves(const DeviceProps &p, int64_t waves) { return waves <= int64_t(kLoneWaves) * p.cus; }
 
@@ -513,7 +513,7 @@ ndvm_status fwd_slot_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, bool 
     if (L == 0 || !few_waves(p, waves) || !slot_may_win(tape->wide_fwd->meta, false)) return NDVM_OK;
     DevProg *dp = nullptr;
     const ndvm_status st = fwd_slot(tape, build, nullptr, &dp);
-    if (dp && wins(p, *dp, waves, *tape->wide_fwd)) *out = dp;
+    if (dp && wins(p, *dp, waves, *tape->wide_fwd, true)) *out = dp;
     return st;
 }
 
@@ -567,7 +567,7 @@ ndvm_status grad_slot_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, cons
     DevProg *dp = nullptr;
     st = single_grad_program(tape, p, L, S, build, &dp, b);
     if (st != NDVM_OK) return !build || st == NDVM_E_UNSUPPORTED ? NDVM_OK : st;
-    if (dp->meta.n_regs <= *b && wins(p, *dp, waves, w)) *out = dp;
+    if (dp->meta.n_regs <= *b && wins(p, *dp, waves, w, false)) *out = dp;
     return NDVM_OK;
 }
 
@@ -776,7 +776,7 @@ ndvm_status slot_many_wins(const ndvm_tape *const *tapes, int n_prog, const Devi
         regs = std::max(regs, dp->meta.n_regs);
     }
     *win = regs <= b && slot_wins(lone, p.lds_per_cu / (std::max(regs, 1u) * reg_bytes(S)), uint64_t(waves),
-                                  uint64_t(p.cus), progs[at]->meta.lone);
+                                  uint64_t(p.cus), progs[at]->meta.lone, progs[at]->meta.matrices, false);
     return NDVM_OK;
 }
 

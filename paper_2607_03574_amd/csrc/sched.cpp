@@ -655,10 +655,20 @@ constexpr uint32_t kTemps = 24;
 // Cycles of an instruction of a wave alone on its SIMD: least squares over the
 // times of 132 programs (sums and chains of one to five operations, random
 // trees, the benchmark models), losses, gradients and saving gradients, 64
-// lanes; their times follow within 7%.  (Forms of matrices are not among them.)
-uint32_t lone_cycles(uint32_t form) {
+// lanes; their times follow within 7%.  Forms of matrices (imm: their shape) from
+// 29 programs with 3x3 and 4x4 matrices, within 17%.
+uint32_t lone_cycles(uint32_t form, uint32_t imm) {
     using namespace slot;
+    const uint32_t K = imm & 7u, N = (imm >> 3) & 7u;
+    const bool three = K == 3 || N == 3, vec = K == 1 || N == 1;
     switch (form) {
+    case DOTB: return three ? 1275 : vec ? 480 : 680;
+    case DOTBACC: return three ? 1940 : vec ? 400 : 960;
+    case DOT: return 390;
+    case DOTACC: return 1390;
+    case NZ: return 1250;
+    case DET2: return 300;
+    case ZERO: case LDCONST: return 245;
     case MAC: return 150;
     case ACC: return 212;
     case LDPARAM: return 227;
@@ -672,7 +682,7 @@ uint32_t lone_cycles(uint32_t form) {
     case UN: return 1106;
     case POWF: return 1742;
     case CKST: return 1941;
-    case STLOSS: case STGRAD: case END: case LDCONST: case ZERO: return 0;
+    case STLOSS: case STGRAD: case END: return 0;
     default: return 400;
     }
 }
@@ -1622,7 +1632,7 @@ Schedule build(const Info &I, Builder &B, bool with_grad, uint32_t S, uint32_t r
         }
         Sch.code[hdr_off + i] = hdr;
         Sch.n_slots_used += cnt;
-        Sch.lone += lone_cycles(f);
+        Sch.lone += lone_cycles(f, hdr >> kImmShift);
         Sch.n_mac += f == MAC;
         Sch.n_acc += f == ACC;
         Sch.n_msub += f == MSUB;

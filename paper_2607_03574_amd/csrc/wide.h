@@ -166,7 +166,7 @@ struct WideSchedule {
     uint32_t first[3] = {0, 0, 0};
     uint64_t n_uops = 0;
     uint64_t cost = 0;            // estimated cycles of a lone wave, by which programs are chosen
-    uint64_t lone = 0, calls = 0; // measured ones, and those of library functions (programs without matrices)
+    uint64_t lone = 0, calls = 0; // measured ones, and those of library functions (and elements, with matrices)
     bool matrices = false;
     uint32_t lds_rows = 0;        // matrix elements in LDS
     uint64_t read_elems = 0;      // elements of the values that adjoint rules read (leaves apart)
@@ -217,16 +217,26 @@ constexpr int64_t scratch_part(uint64_t rows, int64_t lanes, uint64_t bytes, boo
 // lanes, the kernel chosen takes at most 1.06 times as long as the other, losses,
 // and 1.08, gradients, 1.001 on the mean (the wide kernel alone up to 2.4 and 1.13).
 constexpr uint32_t kLoneWaves = 4;   // per CU: beyond that the wide kernel's lanes a wave count for more
-constexpr bool slot_wins(uint64_t slot_cycles, uint64_t resident, uint64_t waves, uint64_t cus, uint64_t wide_cycles) {
+// (With matrices a wave of either kernel has 16 lanes: no more of the one than of
+// the other; and losses, whose estimates are rougher, take a lead of 10%.)
+constexpr bool slot_wins(uint64_t slot_cycles, uint64_t resident, uint64_t waves, uint64_t cus, uint64_t wide_cycles,
+                         bool matrices, bool losses) {
     const uint64_t per_cu = (waves + cus - 1) / cus, at_once = std::min<uint64_t>(kLoneWaves, std::max<uint64_t>(resident, 1));
-    const uint64_t rounds = (per_cu + at_once - 1) / at_once, more = std::min(at_once, per_cu) - 1;
-    return per_cu > 0 && per_cu <= kLoneWaves && rounds * (slot_cycles * (100 + 4 * more) / 100) + 1000 * more < wide_cycles;
+    const uint64_t rounds = (per_cu + at_once - 1) / at_once, more = matrices ? 0 : std::min(at_once, per_cu) - 1;
+    return per_cu > 0 && per_cu <= kLoneWaves && rounds * (slot_cycles * (100 + 4 * more + (matrices && losses ? 10 : 0)) / 100) + 1000 * more < wide_cycles;
 }
-// Whether that may be so, so that the slot program is worth making: `share`, in
-// percent, of the wide program's cycles in library functions.  No program with
-// less (losses 40, gradients 60) ran more than 3% faster on the slot kernel.
+// Programs with matrices hold the scalars of a lane in each of its four threads:
+// where they pack and take apart matrices around library functions and divisions
+// the slot kernel's wave is done earlier too (an extended Kalman filter of four
+// states, 24 steps, 4,096 lanes, us, losses 94 against 134, gradients 438 against
+// 505, saving 559 against 455; a linear one, 40 steps, 200 against 199, 1,069
+// against 782).
+// Whether that may be so, so that the slot program is worth making: by the share
+// of the wide program's cycles in library functions (and elements of matrices).  No
+// program with less than 40%, gradients 60%, ran more than 3% faster on the slot
+// kernel; with matrices than 20%, gradients 43%, more than 9%.
 constexpr bool slot_may_win(const WideSchedule &S, bool with_grad) {
-    return !S.matrices && S.calls * 100 >= S.lone * (with_grad ? 60 : 40);
+    return S.calls * 100 >= S.lone * (S.matrices ? with_grad ? 43 : 20 : with_grad ? 60 : 40);
 }
 // A gradient's slot program, whose schedule is dear, is worth making only where
 // the forward program's wave is done in 85% of the wide one's cycles (no gradient

@@ -105,7 +105,8 @@ constexpr uint32_t kDispatchCost = 62;
 
 // Measured cycles of a lone wave per micro-op and per block: least squares over
 // the launches named at the slot kernel's lone_cycles, times within 13%
-// (gradients 10%); class_cost stays what the choice between programs was tuned on.
+// (gradients 10%, programs with matrices 20%); class_cost stays what the choice
+// between programs was tuned on.
 uint32_t lone_cycles(uint32_t cls) {
     switch (cls) {
     case FMA: return 27;
@@ -133,10 +134,25 @@ uint32_t lone_cycles(uint32_t cls) {
     case ACCPOW: return 679;
     case ACCSQRT: return 307;
     case ABS: return 101;
+    case STE: return 46;
+    case STE4: return 76;
+    case LDE: case CKSTM: return 155;
+    case MM: return 420;
+    case MMA: case MMB: return 830;
+    case VADD: case VACC: return 460;
+    case TRANS: case TRANSACC: return 620;
+    case INV2: case VSCALE: return 560;
+    case INV2ACC: case LOGDETACC: return 700;
+    case VACCS: return 1000;
+    case SDOT: return 1200;
+    case DET2: return 400;
     default: return 0;
     }
 }
 bool is_call(uint32_t cls) { return cls >= EXP && cls <= ACCSQRT; }
+// what else a program with matrices does four times, once a thread of a lane, or
+// waits for alone
+bool is_element(uint32_t cls) { return cls == STE || cls == LDE || cls == DIV || cls == DIVADJ || cls == ACCD; }
 constexpr uint32_t kLoneDispatch = 43;
 
 struct Lower {
@@ -1227,7 +1243,7 @@ void emit(const std::vector<WOp> &in, WideSchedule *S) {
         const uint32_t cls = ops[blocks[b].first].cls, n = blocks[b].second;
         S->cost += kDispatchCost + uint64_t(n) * class_cost(cls);
         S->lone += kLoneDispatch + uint64_t(n) * lone_cycles(cls);
-        if (is_call(cls)) S->calls += uint64_t(n) * lone_cycles(cls);
+        if (is_call(cls) || (S->matrices && is_element(cls))) S->calls += uint64_t(n) * lone_cycles(cls);
     }
     // what the fetches read past the program's end
     S->code.resize(std::max<size_t>(S->code.size(), fetched < UINT64_MAX / 2 ? fetched / 4 : 0), 0);

@@ -6,9 +6,10 @@ import numpy as np
 import pytest
 
 import emu
-from parity import compare
+from parity import compare, judge
 from test_gpu_points import check
-from wide_cases import branch, lookups, one_element_forms, points_of_terms, scalars_and_a_product, sum_of_terms
+from wide_cases import (branch, extended_filter, lookups, one_element_forms, points_of_terms,
+                        scalars_and_a_product, sum_of_terms)
 from workloads import configs
 from workloads.bytecode import Asm
 
@@ -157,24 +158,28 @@ def test_half_the_lds_a_wave(nd, oracle_mod):
     compare(loss.cpu().numpy(), grad.cpu().numpy(), ol, og)
 
 
-@pytest.mark.parametrize("ops", ["pow pow", "sin sin sin"])
+@pytest.mark.parametrize("ops", ["pow pow", "sin sin sin", "extended filter"])
 def test_few_waves_of_library_functions(nd, oracle_mod, ops):
     """Losses, and gradients of three sines, of a launch of few waves run on the
     slot kernel; they are the bits of the same lanes in a launch of many, which
     the wide kernel runs, also without a workspace, in a population and with a
     workspace that was sized for gradients only."""
-    code, obs, L, M = sum_of_terms(ops, 64), points_of_terms(64), 333, 66000
+    L, M = 333, 66000
+    code, obs, P = {"extended filter": lambda: (extended_filter(24, 4, 2), np.linspace(0.1, 0.9, 48), 6),
+                    }.get(
+                        ops, lambda: (sum_of_terms(ops, 64), points_of_terms(64), 4))()
     t = nd.tape_build(code)
-    rows = np.random.default_rng(6).uniform(0.5, 1.0, (M, 4))
+    rows = np.random.default_rng(6).uniform(0.5, 1.0, (M, P))
     p, o, few = dev(rows), dev(obs), dev(rows[:L])
     tape, other = nd.tape_upload(t), nd.tape_upload_many([t])[0]
     lanes = {n: -(-n // 64) * 64 for n in (L, M)}
-    wide = emu.wide(t, np.zeros((0, 4)), obs)[2]["n_ckpt_rows"] + 4
-    slot = emu.run(t, np.zeros((0, 4)), obs, budget=1280)[2]["n_ckpt_rows"] + 4
+    def wide(rows):
+        return emu.wide(t, np.zeros((0, P)), obs, 1, lds_rows=rows)[2]["n_ckpt_rows"] + 4
+    slot = emu.run(t, np.zeros((0, P)), obs, budget=1280)[2]["n_ckpt_rows"] + 4
     on_slot = emu.route(t, L, 1)[0]
-    assert on_slot == (ops == "sin sin sin") and emu.route(t, L, 0)[0] and slot != wide
-    assert nd.workspace_bytes(tape, L, True) == (slot if on_slot else wide) * lanes[L] * 8
-    assert nd.workspace_bytes(tape, M, True) == wide * lanes[M] * 8
+    assert on_slot == (ops != "pow pow") and emu.route(t, L, 0)[0] and slot != wide(1280)
+    assert nd.workspace_bytes(tape, L, True) == (slot if on_slot else wide(1280)) * lanes[L] * 8
+    assert nd.workspace_bytes(tape, M, True) in [wide(r) * lanes[M] * 8 for r in (320, 160)]
     loss, grad = nd.grad(tape, p, o)
     l0 = nd.forward(tape, p, o)
     l1, g1 = nd.grad(tape, few, o)
@@ -183,7 +188,7 @@ def test_few_waves_of_library_functions(nd, oracle_mod, ops):
     nd.grad_noalloc(tape, few, o, l3, g3)
     work = torch.empty(nd.workspace_bytes(other, L, True), dtype=torch.uint8, device="cuda")
     l4 = torch.empty_like(l1)      # (no sizing call for losses: the wide kernel)
-    assert nd._forward(other.handle, few.data_ptr(), L, 4, o.data_ptr(), o.numel(), l4.data_ptr(), work.data_ptr(),
+    assert nd._forward(other.handle, few.data_ptr(), L, P, o.data_ptr(), o.numel(), l4.data_ptr(), work.data_ptr(),
                        work.numel(), torch.cuda.current_stream().cuda_stream) == nd.OK
     lm, gm = nd.grad_many([tape, other], torch.stack([few, few]), o)
     torch.cuda.synchronize()
@@ -192,8 +197,8 @@ def test_few_waves_of_library_functions(nd, oracle_mod, ops):
     assert torch.equal(l0, loss)
     for x in (g1, g3, gm[0], gm[1]):
         assert torch.equal(x, grad[:L])
-    ol, og, _ = oracle_mod.run(code, rows[:L], obs)
-    compare(l1.cpu().numpy(), g1.cpu().numpy(), ol, og)
+    # (the filter's sines amplify the last ulps of a math library: the judge's rule)
+    judge(oracle_mod, code, rows[:L], obs, l1.cpu().numpy(), g1.cpu().numpy())
 
 
 def test_points_of_a_term_of_library_functions(nd, oracle_mod):

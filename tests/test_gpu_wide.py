@@ -40,6 +40,26 @@ def test_cases_equal_oracle(nd, oracle_mod, L):
             compare(loss.cpu().numpy(), grads[0], ol, grads[1])
 
 
+def test_cases_of_many_waves(nd):
+    """The same cases on as many lanes as leave them to the wide kernel, whatever
+    their operations: the bits of the small launches, in every copy of a row."""
+    L = 16 * 4 * 256 + 65
+    for name, code, obs, rows in cases():
+        if rows.shape[1] == 0:
+            continue
+        few = rows[np.arange(65) % len(rows)]
+        P, p, O = (torch.tensor(np.ascontiguousarray(x), device="cuda") for x in (rows[np.arange(L) % len(rows)], few, obs))
+        t = nd.tape_build(code)
+        for policy in (nd.POLICY_RECOMPUTE, nd.POLICY_SAVE):
+            print(name, policy, flush=True)
+            tape = nd.tape_upload(t, policy)
+            big, small = [*nd.grad(tape, P, O), nd.forward(tape, P, O)], [*nd.grad(tape, p, O), nd.forward(tape, p, O)]
+            torch.cuda.synchronize()
+            for a, b in zip(big, small):
+                b = b[:len(rows)].repeat([-(-L // len(rows))] + [1] * (b.dim() - 1))[:L]
+                assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(), b.nan_to_num()), name
+
+
 def test_noalloc_in_parts_equals_grad(nd):
     """A scalar launch whose rows exceed the static scratch array runs in parts
     of its lanes (the last one ragged), with the results of one launch."""

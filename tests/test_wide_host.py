@@ -13,7 +13,8 @@ import pytest
 import emu
 from conftest import ROOT
 from parity import compare
-from wide_cases import cases, long_recurrence, lookups, one_element_forms, scalars_and_a_product, sum_of_terms
+from wide_cases import (cases, extended_filter, long_recurrence, lookups, one_element_forms,
+                        scalars_and_a_product, sum_of_terms)
 from workloads import configs
 from workloads.bytecode import Asm
 
@@ -143,6 +144,21 @@ def test_half_the_lds_a_wave(oracle_mod, mode):
 def test_launches_of_few_waves(ops, mode, slot, wide):
     """Which kernel runs programs of independent library functions."""
     t = nd.tape_build(sum_of_terms(ops, 64))
+    for lanes, want in [(n, True) for n in slot] + [(n, False) for n in wide]:
+        assert emu.route(t, lanes, mode, _slot_budget(lanes) if mode else 1280)[0] == want, lanes
+
+
+@pytest.mark.parametrize("name,mode,slot,wide", [
+    # losses 94, 134 and 90, 109; 8,192 lanes 178, 134
+    ("ekf4", 0, [1, 4096], [8192, 65536]), ("ekf3", 0, [64, 4096], [8192]),
+    # gradients 541, 631 and 483, 403; saving 674, 568
+    ("ekf4", 1, [64, 8192], [32768]), ("ekf3", 1, [], [64, 4096]), ("ekf4", 2, [], [64, 4096]),
+    # a linear filter: losses 200, 199, gradients 1,069, 782; products and scalars: 46, 25, 228, 142
+    ("kalman", 0, [], [1, 4096]), ("kalman", 1, [], [64, 4096]), ("products", 0, [], [64]), ("products", 1, [], [64, 4096])])
+def test_launches_of_few_waves_with_matrices(name, mode, slot, wide):
+    code = {"ekf4": lambda: extended_filter(24, 4, 2), "ekf3": lambda: extended_filter(24, 3, 1),
+            "kalman": lambda: configs.kalman(L=1, T=40).bytecode, "products": lambda: scalars_and_a_product(20, 4, 12)}[name]()
+    t = nd.tape_build(code)
     for lanes, want in [(n, True) for n in slot] + [(n, False) for n in wide]:
         assert emu.route(t, lanes, mode, _slot_budget(lanes) if mode else 1280)[0] == want, lanes
 

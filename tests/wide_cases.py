@@ -95,6 +95,42 @@ def points_of_terms(n):
     return np.concatenate([np.linspace(0.1, 1.0, n), np.linspace(0.2, 0.9, n)])
 
 
+def extended_filter(steps, n, m):
+    """An extended Kalman filter's loss: n states, each a sine of its neighbour
+    away from the last, m of them observed one after another; transitions and
+    Jacobians packed from scalars each step."""
+    A = Asm(6, steps * m)
+    for p in (4, 5):      # the first covariance, the process noise
+        for i in range(n * n):
+            A.param(p) if i % (n + 1) == 0 else A.push(0.0)
+        A.pack(n, n).storel(6 + p)
+    for i in range(n):
+        A.param(i % 4)
+    A.pack(n, 1).storel(12).push(0.0).storel(20).loop(steps)
+    for i in range(n):
+        A.loadl(12).index(i, 0).storel(i)
+    for i in range(n):
+        A.loadl(i).loadl((i + 1) % n).sin().param(3).mul().add()
+    A.pack(n, 1).storel(12)
+    for i in range(n):
+        for j in range(n):
+            if j == i:
+                A.push(1.0)
+            elif j == (i + 1) % n:
+                A.loadl(j).cos().param(3).mul()
+            else:
+                A.push(0.0)
+    A.pack(n, n).storel(13).loadl(13).loadl(10).matmul().loadl(13).transpose().matmul().loadl(11).add().storel(10)
+    for q in range(m):
+        A.obs(q, m).loadl(12).index(q, 0).sub().storel(21).loadl(10).index(q, q).param(4).add().storel(22)
+        A.loadl(21).loadl(22).div().storel(23)
+        for i in range(n):
+            A.loadl(10).index(i, q)
+        A.pack(n, 1).loadl(23).mul().loadl(12).add().storel(12)
+        A.loadl(21).dup().mul().loadl(22).div().loadl(22).log().add().loadl(20).add().storel(20)
+    return A.endloop().loadl(20).halt().bytes()
+
+
 def lookup(params, n):
     """(p0 * table - y)^2, the table nested branches of n constant leaves over
     thresholds of the other parameters: parameters and constants (which the
