@@ -544,8 +544,8 @@ ndvm_status wide_grad_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, int6
 // Whether the slot program of a gradient that the wide program w would run is
 // worth making (or, in a compute call, may have been made).
 ndvm_status grad_slot_likely(ndvm_tape *tape, const WideProg &w, bool build, bool *likely) {
-    *likely = false;
-    if (!tape->wide_fwd || !slot_may_win(w.meta, true)) return NDVM_OK;
+    *likely = short_segments(w.meta);
+    if (*likely || !tape->wide_fwd || !slot_may_win(w.meta, true)) return NDVM_OK;
     DevProg *fp = nullptr;
     const ndvm_status st = fwd_slot(tape, build, nullptr, &fp);
     *likely = fp && slot_leads(fp->meta.lone, tape->wide_fwd->meta.lone);

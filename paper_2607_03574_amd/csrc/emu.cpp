@@ -321,7 +321,7 @@ int ndvm_emu_route(const uint8_t *tape, size_t len, int mode, int64_t lanes, uin
     const WideSchedule S = schedule_wide(t, mode != 0, mode == 2, mode ? std::max(320u, budget) : 320u);
     if (!S.ok) return 1;
     const Schedule D = mode ? schedule_grad(t, budget, 4, mode == 2) : schedule_forward(t, 4, budget);
-    const bool leads = !mode || slot_leads(schedule_forward(t, 4, 1280).lone, schedule_wide(t, false, mode == 2, 320).lone);
+    const bool leads = !mode || short_segments(S) || slot_leads(schedule_forward(t, 4, 1280).lone, schedule_wide(t, false, mode == 2, 320).lone);
     out[0] = slot_may_win(S, mode != 0) && leads && D.n_regs <= budget &&
              slot_wins(D.lone, 1280 / std::max(D.n_regs, 1u), uint64_t(lanes + 15) / 16, cus, S.lone, S.matrices, mode == 0);
     out[1] = D.lone;

@@ -169,6 +169,7 @@ struct WideSchedule {
     uint64_t lone = 0, calls = 0; // measured ones, and those of library functions (and elements, with matrices)
     bool matrices = false;
     uint32_t lds_rows = 0;        // matrix elements in LDS
+    uint64_t values = 0;          // elements of the computed values
     uint64_t read_elems = 0;      // elements of the values that adjoint rules read (leaves apart)
     uint64_t ckpt_elems = 0;      // elements of the segments' stored inputs
 };
@@ -235,7 +236,14 @@ constexpr bool slot_wins(uint64_t slot_cycles, uint64_t resident, uint64_t waves
 // of the wide program's cycles in library functions (and elements of matrices).  No
 // program with less than 40%, gradients 60%, ran more than 3% faster on the slot
 // kernel; with matrices than 20%, gradients 43%, more than 9%.
+// A gradient whose registers leave room for segments of a few values only
+// restores and recomputes for most of its time, where the slot kernel's registers
+// hold whole steps: a network of 8 hidden units (25 parameters, 8 values a
+// segment) on 40 points, 4,096 lanes, 215 against 275 us; of 6 (48 values) 164
+// against 146; no program of 24 values or more a segment was slower.
+constexpr bool short_segments(const WideSchedule &S) { return S.n_segments > 1 && S.values < 16 * uint64_t(S.n_segments); }
 constexpr bool slot_may_win(const WideSchedule &S, bool with_grad) {
+    if (with_grad && short_segments(S)) return true;
     return S.calls * 100 >= S.lone * (S.matrices ? with_grad ? 43 : 20 : with_grad ? 60 : 40);
 }
 // A gradient's slot program, whose schedule is dear, is worth making only where

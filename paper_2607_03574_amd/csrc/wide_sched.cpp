@@ -1372,6 +1372,7 @@ WideSchedule schedule_in(const Tape &t, bool with_grad, bool save_reads, uint32_
         lds_fit = S.lds_rows <= lds_rows;
         S.n_ckpt_rows = W.n_rows * (mats ? 4 : 1);
         S.n_segments = uint32_t(B.cuts.size());
+        S.values = total;
         S.read_elems = read_elems;
         for (const auto &v : B.livein)
             for (uint32_t s : v) S.ckpt_elems += I.nel[s];

@@ -8,7 +8,7 @@ import pytest
 import emu
 from parity import compare, judge
 from test_gpu_points import check
-from wide_cases import (branch, extended_filter, lookups, one_element_forms, points_of_terms,
+from wide_cases import (branch, extended_filter, lookups, network, one_element_forms, points_of_terms,
                         scalars_and_a_product, sum_of_terms)
 from workloads import configs
 from workloads.bytecode import Asm
@@ -158,7 +158,7 @@ def test_half_the_lds_a_wave(nd, oracle_mod):
     compare(loss.cpu().numpy(), grad.cpu().numpy(), ol, og)
 
 
-@pytest.mark.parametrize("ops", ["pow pow", "sin sin sin", "extended filter"])
+@pytest.mark.parametrize("ops", ["pow pow", "sin sin sin", "extended filter", "network"])
 def test_few_waves_of_library_functions(nd, oracle_mod, ops):
     """Losses, and gradients of three sines, of a launch of few waves run on the
     slot kernel; they are the bits of the same lanes in a launch of many, which
@@ -166,7 +166,7 @@ def test_few_waves_of_library_functions(nd, oracle_mod, ops):
     workspace that was sized for gradients only."""
     L, M = 333, 66000
     code, obs, P = {"extended filter": lambda: (extended_filter(24, 4, 2), np.linspace(0.1, 0.9, 48), 6),
-                    }.get(
+                    "network": lambda: (network(8, 40), points_of_terms(40), 25)}.get(
                         ops, lambda: (sum_of_terms(ops, 64), points_of_terms(64), 4))()
     t = nd.tape_build(code)
     rows = np.random.default_rng(6).uniform(0.5, 1.0, (M, P))

@@ -13,7 +13,7 @@ import pytest
 import emu
 from conftest import ROOT
 from parity import compare
-from wide_cases import (cases, extended_filter, long_recurrence, lookups, one_element_forms,
+from wide_cases import (cases, extended_filter, long_recurrence, lookups, network, one_element_forms,
                         scalars_and_a_product, sum_of_terms)
 from workloads import configs
 from workloads.bytecode import Asm
@@ -161,6 +161,15 @@ def test_launches_of_few_waves_with_matrices(name, mode, slot, wide):
     t = nd.tape_build(code)
     for lanes, want in [(n, True) for n in slot] + [(n, False) for n in wide]:
         assert emu.route(t, lanes, mode, _slot_budget(lanes) if mode else 1280)[0] == want, lanes
+
+
+@pytest.mark.parametrize("units,slot", [(6, False), (8, True), (10, True)])
+def test_launches_of_few_waves_with_short_segments(units, slot):
+    """Gradients, 40 points, 4,096 lanes, us: 164, 146; 215, 275; 271, 355."""
+    t = nd.tape_build(network(units, 40))
+    for lanes in (1, 4096, 16384):
+        assert emu.route(t, lanes, 1, _slot_budget(lanes))[0] == slot
+    assert not emu.route(t, 16385, 1, _slot_budget(16385))[0] and not emu.route(t, 4096, 2)[0]
 
 
 def test_timed_models_stay_on_the_wide_kernel():

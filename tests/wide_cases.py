@@ -95,6 +95,16 @@ def points_of_terms(n):
     return np.concatenate([np.linspace(0.1, 1.0, n), np.linspace(0.2, 0.9, n)])
 
 
+def network(units, n):
+    """Squared residuals of a hidden layer over n points: 3 units + 1 parameters,
+    of whose adjoints the register file of the wide kernel has little room left."""
+    A = Asm(3 * units + 1, 2 * n).push(0.0).storel(0).loop(n).param(3 * units).storel(1)
+    for h in range(units):
+        A.push(1.0).obs(0, 1).param(h).mul().param(units + h).add().exp().push(1.0).add().div()
+        A.param(2 * units + h).mul().loadl(1).add().storel(1)
+    return A.loadl(1).obs(n, 1).sub().dup().mul().loadl(0).add().storel(0).endloop().loadl(0).halt().bytes()
+
+
 def extended_filter(steps, n, m):
     """An extended Kalman filter's loss: n states, each a sine of its neighbour
     away from the last, m of them observed one after another; transitions and
