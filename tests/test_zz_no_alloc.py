@@ -2,8 +2,8 @@
 C ABI: its results equal ndvm_grad's bit for bit (the same kernels, the static
 scratch array instead of a caller workspace) on two calls in a row, the second
 with a smaller input, and again after the array holds another program's
-rows; a launch that needs more than the array is rejected before anything is
-enqueued."""
+rows; a launch that needs many times the array is rejected before anything is
+enqueued (one of up to four times runs in parts: test_gpu_wide.py)."""
 import numpy as np
 import pytest
 
@@ -56,7 +56,8 @@ def test_noalloc_equals_grad_two_calls(nd, oracle_mod, name, kw, L2):
 
 
 def test_noalloc_rejects_launch_beyond_scratch(nd):
-    """Kalman, 200 steps, 16384 lanes: about 1.9 GB of checkpoint rows."""
+    """Kalman, 200 steps, 16384 lanes: about 0.53 GB of checkpoint rows (1.9 GB on
+    the slot kernel)."""
     w = configs.kalman(L=16384)
     tape = nd.tape_upload(nd.tape_build(w.bytecode))
     L = w.params.shape[0]
