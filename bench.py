@@ -361,7 +361,7 @@ def calibration_bench(args):
                    "lanes_improved": improved},
         "roofline": {"bound": "alu", "achieved": flops / gpu_s / 1e12, "peak": PEAK_FP64 / 1e12,
                      "unit": "TFLOP/s", "frac": flops / gpu_s / PEAK_FP64, "traffic": None,
-                     "kernel": replay_kernel(args.workload) + " + ndvm_adam", "kernel_ms": gpu_s * 1e3},
+                     "kernel": replay_kernel(w.name) + " + ndvm_adam", "kernel_ms": gpu_s * 1e3},
     }
     if not args.no_cpu_baseline:
         from oracle import adam

@@ -560,10 +560,10 @@ ndvm_status grad_slot_for(ndvm_tape *tape, const DeviceProps &p, int64_t L, cons
     *out = nullptr;
     const uint32_t S = slot::kMaxSlots;
     const int64_t waves = waves_of(L, 1, S);
-    bool likely = false;
-    ndvm_status st;
-    if (L == 0 || !few_waves(p, waves) || (st = grad_slot_likely(tape, w, build, &likely)) != NDVM_OK || !likely)
-        return L == 0 || !few_waves(p, waves) ? NDVM_OK : st;
+    if (L == 0 || !few_waves(p, waves)) return NDVM_OK;
+    bool likely;
+    ndvm_status st = grad_slot_likely(tape, w, build, &likely);
+    if (st != NDVM_OK || !likely) return st;
     DevProg *dp = nullptr;
     st = single_grad_program(tape, p, L, S, build, &dp, b);
     if (st != NDVM_OK) return !build || st == NDVM_E_UNSUPPORTED ? NDVM_OK : st;

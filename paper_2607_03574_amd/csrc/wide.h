@@ -226,22 +226,22 @@ constexpr bool slot_wins(uint64_t slot_cycles, uint64_t resident, uint64_t waves
     const uint64_t rounds = (per_cu + at_once - 1) / at_once, more = matrices ? 0 : std::min(at_once, per_cu) - 1;
     return per_cu > 0 && per_cu <= kLoneWaves && rounds * (slot_cycles * (100 + 4 * more + (matrices && losses ? 10 : 0)) / 100) + 1000 * more < wide_cycles;
 }
-// Programs with matrices hold the scalars of a lane in each of its four threads:
-// where they pack and take apart matrices around library functions and divisions
-// the slot kernel's wave is done earlier too (an extended Kalman filter of four
-// states, 24 steps, 4,096 lanes, us, losses 94 against 134, gradients 438 against
-// 505, saving 559 against 455; a linear one, 40 steps, 200 against 199, 1,069
-// against 782).
-// Whether that may be so, so that the slot program is worth making: by the share
-// of the wide program's cycles in library functions (and elements of matrices).  No
-// program with less than 40%, gradients 60%, ran more than 3% faster on the slot
-// kernel; with matrices than 20%, gradients 43%, more than 9%.
 // A gradient whose registers leave room for segments of a few values only
 // restores and recomputes for most of its time, where the slot kernel's registers
 // hold whole steps: a network of 8 hidden units (25 parameters, 8 values a
 // segment) on 40 points, 4,096 lanes, 215 against 275 us; of 6 (48 values) 164
 // against 146; no program of 24 values or more a segment was slower.
 constexpr bool short_segments(const WideSchedule &S) { return S.n_segments > 1 && S.values < 16 * uint64_t(S.n_segments); }
+// Whether the slot kernel may win, so that its program is worth making: by the
+// share of the wide program's cycles in library functions.  No program with less
+// than 40% there, gradients 60%, ran more than 3% faster on the slot kernel.
+// Programs with matrices hold the scalars of a lane in each of its four threads:
+// where they pack and take apart matrices around library functions and divisions
+// (the share counts all these) the slot kernel's wave is done earlier too: an
+// extended Kalman filter of four states, 24 steps, 4,096 lanes, us, losses 94
+// against 134, gradients 438 against 505, saving 559 against 455; a linear one, 40
+// steps, 200 against 199, 1,069 against 782.  None with less than 20%, gradients
+// 43%, ran more than 9% faster on the slot kernel.
 constexpr bool slot_may_win(const WideSchedule &S, bool with_grad) {
     if (with_grad && short_segments(S)) return true;
     return S.calls * 100 >= S.lone * (S.matrices ? with_grad ? 43 : 20 : with_grad ? 60 : 40);
